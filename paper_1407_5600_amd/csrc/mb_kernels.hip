@@ -795,7 +795,9 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
 }
 
 // Spreading: one block per box tile (FX x FY x FZ binning tiles, btl), one
-// velocity component at a time.  The box tile's own records (those of its
+// velocity component at a time, or, on a grid of three rows, one block per
+// box tile and component (spread_boxes); a box tile without records only
+// writes zeros.  The box tile's own records (those of its
 // cells) add all 27 of their contributions to an LDS box of the nodes they
 // can reach, [lo-1, lo+T+1] per axis, so no record is read by more than one
 // block and no contribution is masked.  The box is written to the box
@@ -833,6 +835,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
          const int* __restrict__ offs, int L, Tiles btl, Tiles tl, int det,
          T* __restrict__ E) {
     constexpr int NT = spread_threads<T>(FX * FY * FZ);
+    const int comp = gridDim.y == 3 ? (int)blockIdx.y : -1;  // one component, or all
     constexpr int NR = FX * FY * FZ;  // binning tiles of this box tile
     constexpr int EX = TX + 3, EY = TY + 3, EZ = TZ + 3;
     constexpr int EV = EX * EY * EZ;
@@ -843,7 +846,6 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     double* accd = reinterpret_cast<double*>(acc);
     const TileBox tb = tile_box(btl, L);
     const int tile = tb.tile;
-    for (int i = threadIdx.x; i < EV; i += NT) acc[i] = 0ull;
     // the records of this box tile: its binning tiles are numbered
     // consecutively (box-tile major), so their records form one range
     int first, total;
@@ -853,6 +855,14 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         first = offs[g];
         total = offs[g + NR] - first;
     }
+    if (total == 0) {  // no records: an empty box
+        for (int a = comp < 0 ? 0 : comp; a <= (comp < 0 ? 2 : comp); ++a) {
+            T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
+            for (int i = threadIdx.x; i < EV; i += NT) st32(Ea, (unsigned)i, T(0));
+        }
+        return;
+    }
+    for (int i = threadIdx.x; i < EV; i += NT) acc[i] = 0ull;
     // The k-th record a thread takes is the sorted record q(k) of the box
     // tile.  For float32 fields q(k) = (k * P) mod total with P = 263 (269
     // where 263 divides total, 1 where 269 does too), a bijection since P is
@@ -907,6 +917,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     const int npass = mode == 2 ? 2 : 1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
+      if (comp >= 0 && a != comp) continue;
       for (int pass = 0; pass < npass; ++pass) {
         for (int k = threadIdx.x, q = q0; k < total; k += NT, q = adv(q)) {
             RecG<T> r = r0;
@@ -1866,10 +1877,22 @@ hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
     const Tiles& t = g->tiles;
     const Tiles& b = g->btiles;
     bool ok = false;
+    // One block per box tile and component while that leaves at most three
+    // blocks per CU (256 of them): the kernel is then a chain of dependent
+    // phases on a mostly idle chip, and a block that does one component has
+    // a third of it (float64: 64^3 with 4,583 particles, 64 box tiles, 21.0
+    // -> 12.2 us; one particle in 32^3 10.2 -> 6.3; sixteen 32^3 boxes of
+    // 276 particles 15.4 -> 11.5; 96^3, 216 box tiles, the step 2 us less).
+    // With more box tiles the records read and the maxima formed three times
+    // cost more than the overlap gives (128^3, 512 box tiles: 21.8 -> 29.4 us
+    // mixed, 32.5 -> 40.2 float64).
+    constexpr int kSplitBoxTiles = 256;
+    const int nbt = b.n * b.nbox;
+    const dim3 grid(nbt, nbt <= kSplitBoxTiles ? 3 : 1);
 #define MB_BOX(SX, SY, SZ, FX, FY, FZ)                                                   \
     if (!ok && b.tx == SX && b.ty == SY && b.tz == SZ && SX == FX * t.tx &&              \
         SY == FY * t.ty && SZ == FZ * t.tz) {                                            \
-        MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ>), b.n * b.nbox,   \
+        MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ>), grid,   \
                   spread_threads<T>(FX * FY * FZ), 0, rec_geo<T>(g), rec_force<T>(g),    \
                   g->d_offs, g->L, b, t, g->d.deterministic, (T*)g->d_box);              \
         ok = true;                                                                       \
