@@ -1106,11 +1106,14 @@ k_interp(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
     const TileBox tb = tile_box(tl, L);
     const int tile = tb.gt;
     const int N = L * L * L;  // 3 L^3 < 2^31 for L <= 512
-    if (bn.count && threadIdx.x < 27) lcount[threadIdx.x] = 0;
-    v += (size_t)tb.box * 3 * N;
     // the tile's own records
     const int first = offs[tile];
     const int total = offs[tile + 1] - first;
+    // nothing to interpolate, move or bin, and no sums asked for (the boxes
+    // of a pair sweep hold 26 blobs in a few of their 64^3 / 1024 tiles)
+    if (total == 0 && !part) return;
+    if (bn.count && threadIdx.x < 27) lcount[threadIdx.x] = 0;
+    v += (size_t)tb.box * 3 * N;
     const int sx = threadIdx.x % EX;  // staging: x slot and first row
     const int sr = threadIdx.x / EX;
     const int gx = wrapL(tb.lo[0] - 1 + sx, L);
