@@ -186,8 +186,34 @@ constexpr int largest_even_divisor(int L, int cap) {
         if (L % d == 0) best = d;
     return best;
 }
-// rows per block of the x passes (about 256 threads per block)
+// rows per block of the inverse x pass (about 256 threads per block)
 constexpr int rows_x(int L) { return largest_even_divisor(L, 4096 / L > 2 ? 4096 / L : 2); }
+// Rows per block of the forward x pass and elements per thread.  A block is
+// a chain (a load round per element of a thread, the transform, the store),
+// so short chains and many blocks matter most: up to L = 128, 16 rows and
+// one element per thread (L <= 24), two (<= 72) or four against eight
+// elements of 4096 / L rows before (one 32^3 box, 48 blocks of 256 threads
+// against 96 of 64: 10.0 -> 5.4 us; 64^3 float32 12.2 -> 8.0, float64 14.7
+// -> 12.7; 72^3 14.6 -> 9.1; 96^3 float64 25.0 -> 21.9; 128^3 float32 21.7
+// -> 20.5, float64 38.2 -> 34.6).  Fewer rows store shorter runs of ky (a
+// batch of 32 64^3 boxes: 69.7 us with 16 rows, 76 with 8).  Above, float32
+// takes as few elements as 512 threads allow (144^3, 16 rows: 40.9 -> 35.9
+// us; 192^3 96.5 -> 92.1; 256^3 211.7 -> 204.6), float64 stays at eight,
+// bound by its registers (256^3 339 us with eight, 344 with four).
+template <typename T>
+constexpr int rows_xf(int L) {
+    if (L <= 128 || (sizeof(T) == 4 && L == 144)) return largest_even_divisor(L, 16);
+    return rows_x(L);
+}
+template <typename T>
+constexpr int elems_xf(int L) {
+    const int n = rows_xf<T>(L) / 2 * L;
+    if (L <= 128) return L <= 24 ? 1 : (L <= 72 ? 2 : 4);
+    if (sizeof(T) == 8) return EPT;
+    int e = 3;
+    while (n % e != 0 || n / e > 512) ++e;
+    return e;
+}
 // kx columns per block of the y pass (at least 128 B contiguous per row)
 template <typename T>
 constexpr int cols_y(int L) {
@@ -218,9 +244,14 @@ constexpr int cols_z(int L) {
 template <typename T, int L>
 struct Geo {
     static constexpr int NC = L / 2 + 1;
-    static constexpr int R = rows_x(L);
+    static constexpr int R = rows_xf<T>(L);  // forward x pass: rows per block
     static constexpr int NL = R / 2;
-    static constexpr int TX = NL * L / EPT;  // threads of an x pass
+    static constexpr int EX = elems_xf<T>(L); // elements per thread
+    static constexpr int TX = NL * L / EX;   // threads
+    static constexpr int RI = rows_x(L);     // inverse x pass
+    static constexpr int NLI = RI / 2;
+    static constexpr int TXI = NLI * L / EPT;
+    static_assert(NL * L % EX == 0 && TX <= 512, "x pass");
     static constexpr int LS = line_stride(L); // LDS line stride (complex)
     static constexpr int WY = cols_y<T>(L);
     static constexpr int NCHY = (NC + WY - 1) / WY;
@@ -293,7 +324,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
     // float32 (five waves per SIMD, 1.2 rounds of blocks at 128^3); one fits
     // six waves and one round (25.4 against 26.7 us).
     constexpr int KG = 1;
-    static_assert(EPT % KG == 0, "rounds of the x pass");
+    static_assert(G::EX % KG == 0, "rounds of the x pass");
     // a wave's lanes share y when L is a multiple of the wave
     constexpr bool UNI = L % WAVE == 0 && NTHR % L == 0;
     // with UNI, a thread's x (and its neighbours and x box sources) is the
@@ -308,7 +339,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
     [[maybe_unused]] AxisSrc bxu{};
     if constexpr (UNI && BOX) bxu = box_src_x(tl, xu);
 #pragma unroll
-    for (int k0 = 0; k0 < EPT; k0 += KG) {
+    for (int k0 = 0; k0 < G::EX; k0 += KG) {
         T vc[KG][2], vn[KG][2][6], fv[KG][2];
         T eb[KG][2][4][2];
         if constexpr (UNI && KG == 1) {
@@ -481,7 +512,7 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     constexpr int NLN = 3 * W;
     __shared__ cplx<T> buf[NLN * LS];
     __shared__ cplx<T> tws[L];
-    __shared__ double red[16];
+    __shared__ double red[3 * ((NTHR + WAVE - 1) / WAVE)];
     __shared__ double mean_new[3];
     const int tid = threadIdx.x;
     // blocks of a box are consecutive (NC L / W per box); when their count
@@ -498,14 +529,30 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     psum += (size_t)box * 3 * per_c * 2;  // per_c partials per component
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     if (kx == 0 && ch == 0) {
-        for (int c = 0; c < 3; ++c) {
-            double s = 0.0;
+        // the three components' sums together: every load of a round before
+        // its adds, one reduction (each wave's sums through LDS)
+        double s[3] = {0.0, 0.0, 0.0};
+        if (!zero_mean_mode) {
+#pragma unroll 2
             for (int i = tid; i < per_c; i += NTHR) {
-                const double* p = psum + 2 * (c * per_c + i);
-                s += mv * p[0] + mf * p[1];
+                const double* p = psum + 2 * i;
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    s[c] += mv * p[2 * c * per_c] + mf * p[2 * c * per_c + 1];
             }
-            s = block_reduce<false>(s, red);
-            if (tid == 0) mean_new[c] = zero_mean_mode ? 0.0 : s;
+        }
+        constexpr int NW = (NTHR + WAVE - 1) / WAVE;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] = wave_sum(s[c]);
+        if (tid % WAVE == 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) red[3 * (tid / WAVE) + c] = s[c];
+        }
+        __syncthreads();  // (uniform over the block)
+        if (tid < 3) {
+            double t = 0.0;
+            for (int w = 0; w < NW; ++w) t += red[3 * w + tid];
+            mean_new[tid] = t;
         }
     }
     __syncthreads();  // twiddles, mean mode
@@ -564,11 +611,11 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // imaginary parts of kx = 0 and L/2 dropped), transformed, and the real and
 // imaginary parts stored as the two velocity rows.
 template <typename T, int L>
-__global__ void __launch_bounds__((Geo<T, L>::TX))
+__global__ void __launch_bounds__((Geo<T, L>::TXI))
 k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
         T* __restrict__ vout) {
     using G = Geo<T, L>;
-    constexpr int NC = G::NC, R = G::R, NL = G::NL, NTHR = G::TX, LS = G::LS;
+    constexpr int NC = G::NC, R = G::RI, NL = G::NLI, NTHR = G::TXI, LS = G::LS;
     constexpr int SS = NC + 1;  // staging row stride
     __shared__ cplx<T> stg[R * SS];
     __shared__ cplx<T> buf[NL * LS];
@@ -760,16 +807,18 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const T* f, bool boxed, T* v_o
     } else {
         MB_LAUNCH(g, K_FFT_Y_INV, s, (k_y<T, L, true>), 3 * L * G::NCHY * nbox, G::TY, 0, A,
                   tw);
-        MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), G::NBX * nbox, G::TX, 0, A, tw, v_out);
+        MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A, tw, v_out);
     }
     return hipGetLastError();
 }
 
 }  // namespace fft
 
+#ifndef MB_FFT_SIZES
 #define MB_FFT_SIZES(X) \
     X(8) X(16) X(24) X(32) X(48) X(64) X(72) X(96) X(128) X(144) X(192) \
     X(216) X(256) X(288) X(384) X(432) X(512)
+#endif
 
 template <typename T>
 hipError_t fluid_solve(mb_grid* g, const T* v_in, const T* f, T* v_out,

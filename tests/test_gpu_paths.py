@@ -61,3 +61,29 @@ def test_spread_by_component_or_by_box_tile(torch_cuda, prec, per_box):
     for b in (0, 32):
         ref = oracle.spread(oracle.params(L), q[b], F[b])
         assert rel(out[1][b], ref) <= TOL[prec]
+
+
+@pytest.mark.parametrize("L,prec", [(16, "fp64"), (72, "fp64"), (72, "mixed"), (96, "fp64"),
+                                    (96, "mixed"), (192, "mixed")])
+def test_step_at_x_pass_shapes(torch_cuda, L, prec):
+    """One step of a few particles from a random field at the edges whose
+    forward x pass has its own rows per block and elements per thread (the
+    spread boxes folded in it), and the mean mode from its partial sums."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    say("x pass shape", L, prec)
+    w = inputs.random_suspension(L, L, 5)
+    rng = np.random.default_rng(L)
+    v0 = rng.standard_normal((3, L, L, L)) + 0.5
+    if prec == "mixed":
+        v0 = v0.astype(np.float32).astype(np.float64)
+    ref = oracle.step(oracle.params(L), w.springs(), w.q, v0, w.Fext, 1)
+    g = Grid(L, precision=prec, max_blobs=w.M)
+    q, v = dev(torch, w.q), dev(torch, v0).to(g.field_dtype)
+    g.step(Springs(w.nb, w.pa, w.pb, w.r0, w.k), q, v, dev(torch, w.Fext))
+    r = rel(v.double().cpu().numpy(), ref["v"])
+    mean = v.double().mean(dim=(1, 2, 3)).cpu().numpy()
+    ref_mean = ref["v"].mean(axis=(1, 2, 3))
+    say(f"v {r:.2e} mean {rel(mean, ref_mean):.2e}")
+    assert r <= TOL[prec]
+    assert rel(mean, ref_mean) <= TOL[prec]
