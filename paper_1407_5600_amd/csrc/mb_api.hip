@@ -749,7 +749,7 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
     // the interpolation of the step before (the positions it wrote); the
     // last step leaves the counts at zero
     const bool carry = g->scheme == MB_SCHEME_EULER && M > 0;
-    double* U0_dst = reorder ? g->d_pint : U0_out;  // particle forces are done by then
+    const double* u_last = nullptr;
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         const bool last = n == nsteps - 1;
         const bool binned = carry && n > 0, bin_next = carry && !last;
@@ -764,14 +764,11 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
                                   (const double*)ffluid, u_dst, s, binned, bin_next, diag);
         if (!last && e != hipSuccess && bin_next)
             (void)zero_words(g->d_count, (size_t)g->tiles.n * g->tiles.nbox, s);
-        if (last && e == hipSuccess && U0_out)
-            e = particle_means(g, P, sp->nb, u_dst, U0_dst, s);
-        if (last && e == hipSuccess && diag_out)
-            e = diagnostics(g, M > 0 ? fb : 1, diag_out, s);
+        u_last = u_dst;
     }
-    if (reorder && e == hipSuccess)
-        e = unorder_particles(g, P, sp->nb, q, u_out ? g->d_u : nullptr, u_out,
-                              U0_out ? g->d_pint : nullptr, U0_out, s);
+    if (e == hipSuccess)
+        e = finish_call(g, P, sp->nb, reorder, q, u_last, u_out, U0_out, M > 0 ? fb : 1,
+                        diag_out, s);
     if (!check) return from_hip(e);
     return finish(g, e, s);
 }

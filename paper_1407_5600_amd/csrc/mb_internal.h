@@ -28,8 +28,8 @@ enum KernelId : int {
     K_FFT_X_INV,
     K_INTERP,
     K_INTERP_STEP,
-    K_U0,
-    K_DIAG,
+    K_U0,    // particle means and reordering at the end of a call
+    K_DIAG,  // the same with the diagnostics
     K_FOLD,
     K_INTERP_GRAD,
     K_SPRINGS_ADJ,
@@ -112,7 +112,7 @@ struct mb_grid {
                         // fused scan's published launch number
     uint32_t scan_epoch;  // launches of the springs kernel with the fused scan
     double* d_qint;     // [max_blobs][3] positions in the step calls' particle order
-    double* d_pint;     // [max_blobs][3] per-particle forces, then velocities, same order
+    double* d_pint;     // [max_blobs][3] per-particle forces, same order
     int* d_order;       // [max_blobs] caller's particle of each internal particle
     int ntiles_cap;     // tiles per box the workspace holds (all shapes)
     int L, NC;          // cells per side, complex columns L/2 + 1
@@ -259,21 +259,19 @@ hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
 template <typename T>
 hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wscale,
                             double* gout, hipStream_t s);
-hipError_t particle_means(mb_grid* g, int64_t P, int nb, const double* u,
-                          double* U0, hipStream_t s);
-hipError_t diagnostics(mb_grid* g, int force_blocks, double* diag,
-                       hipStream_t s);
 // Particle order of a step call: particles counting-sorted by the tile of
 // their last blob (the centre of the icosahedral template) into d_order
 // (internal particle -> caller's particle), and the positions q and forces
 // Fext (nullable) gathered into d_qint and d_pint in that order.
 hipError_t order_particles(mb_grid* g, int64_t P, int nb, const double* q,
                            const double* Fext, hipStream_t s);
-// Back to the caller's order: positions into q, and (each nullable) the blob
-// velocities u_int into u_out and particle velocities U0_int into U0_out.
-hipError_t unorder_particles(mb_grid* g, int64_t P, int nb, double* q, const double* u_int,
-                             double* u_out, const double* U0_int, double* U0_out,
-                             hipStream_t s);
+// End of a step call: with reordered, positions back into q in the caller's
+// order and the blob velocities u into u_out (nullable); the particle
+// velocities U0 (nullable) as means of u, in the caller's order; the
+// diagnostics (nullable) from their partials.
+hipError_t finish_call(mb_grid* g, int64_t P, int nb, bool reordered, double* q, const double* u,
+                       double* u_out, double* U0, int force_blocks, double* diag,
+                       hipStream_t s);
 size_t record_size(int precision);
 // Blocks and dynamic LDS bytes of the springs kernels for P particles.
 int springs_blocks(const SpringsDev& sp, int64_t P);

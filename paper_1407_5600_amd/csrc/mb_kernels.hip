@@ -148,46 +148,60 @@ __device__ int scan_tile_lds(int* s, int* scratch) {
 // ---------------------------------------------------------------------------
 // Binning: counting sort of blobs by tile.  Blobs are taken in `order` (the
 // sorted order of the previous binning when it covered the same blobs, so
-// that a block's blobs fall in a few consecutive tiles; the identity
-// otherwise): a block counts its blobs of tiles [t0, t0 + 64) in LDS (t0 the
-// tile of its first blob) and adds each such count to the global count with
-// one atomic; other blobs take a global atomic each.  rank is the blob's
-// place among its tile's blobs, in no particular order.  With a batch of
-// boxes, blob i belongs to box i / mbox and tiles are numbered box by box.
-constexpr int TILE_WIN = 64;
+// that a block's blobs fall in a few tiles; the identity otherwise).  A block
+// counts its blobs per tile in a small LDS hash table (open addressing, as
+// many slots as two blocks' blobs, so a free slot is always found) and adds
+// each tile's count to the global count with one atomic.  Bound by those
+// atomics where the blobs of a block lie in many tiles.  An LDS window of 64
+// tiles from the block's first blob, with a global atomic for every blob
+// outside it, missed the neighbours of a particle along y and z even with
+// the particles sorted by tile.  rank is the blob's place among its tile's
+// blobs, in no particular order.  With a batch of boxes, blob i belongs to
+// box i / mbox and tiles are numbered box by box.
+constexpr int TILE_SLOTS = 2 * BLK;
 
 __global__ void __launch_bounds__(BLK)
 k_tile_count(const double* __restrict__ q, const int* __restrict__ order,
              int64_t M, int64_t mbox, double inv_h, int L, Tiles tl, int* __restrict__ count,
              int* __restrict__ tile_of, int* __restrict__ rank) {
-    __shared__ int lcount[TILE_WIN];
-    __shared__ int lbase[TILE_WIN];
-    __shared__ int t0s;
+    __shared__ int key[TILE_SLOTS];
+    __shared__ int cnt[TILE_SLOTS];  // count, then the global base, of the slot's tile
     const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    if (threadIdx.x < TILE_WIN) lcount[threadIdx.x] = 0;
+#pragma unroll
+    for (int k = threadIdx.x; k < TILE_SLOTS; k += BLK) {
+        key[k] = -1;
+        cnt[k] = 0;
+    }
     int64_t i = -1;
     int t = 0;
     if (j < M) {
         i = order ? order[j] : j;
         const Geom g = blob_geom(q, i, inv_h, L);
-        t = (int)(i / mbox) * tl.n + tile_linear(g.c, tl);  // box i / mbox
+        const int box = mbox == M ? 0 : (int)(i / mbox);
+        t = box * tl.n + tile_linear(g.c, tl);
     }
-    if (threadIdx.x == 0) t0s = t;  // block 0's first blob exists (M > 0)
     __syncthreads();
-    const int k = t - t0s;
-    const bool local = i >= 0 && k >= 0 && k < TILE_WIN;
-    int r = 0;
-    if (local) r = atomicAdd(&lcount[k], 1);
-    else if (i >= 0) r = atomicAdd(&count[t], 1);
+    int slot = 0, r = 0;
+    if (i >= 0) {
+        slot = (int)(((uint32_t)t * 2654435761u) >> 23);  // the top 9 bits: 512 slots
+        static_assert(TILE_SLOTS == 512, "hash width");
+        for (;;) {
+            const int was = atomicCAS(&key[slot], -1, t);
+            if (was == -1 || was == t) break;
+            slot = (slot + 1) & (TILE_SLOTS - 1);
+        }
+        r = atomicAdd(&cnt[slot], 1);
+    }
     __syncthreads();
-    if (threadIdx.x < TILE_WIN) {
-        const int c = lcount[threadIdx.x];
-        lbase[threadIdx.x] = c > 0 ? atomicAdd(&count[t0s + threadIdx.x], c) : 0;
+#pragma unroll
+    for (int k = threadIdx.x; k < TILE_SLOTS; k += BLK) {
+        const int c = cnt[k];
+        if (c > 0) cnt[k] = atomicAdd(&count[key[k]], c);
     }
     __syncthreads();
     if (i >= 0) {
         tile_of[i] = t;
-        rank[i] = local ? lbase[k] + r : r;
+        rank[i] = cnt[slot] + r;
     }
 }
 
@@ -1557,21 +1571,9 @@ k_interp_grad(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
     }
 }
 
-__global__ void __launch_bounds__(BLK)
-k_u0(const double* __restrict__ u, int64_t P, int nb, double* __restrict__ U0) {
-    const int64_t p = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    if (p >= P) return;
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int b = 0; b < nb; ++b)
-        for (int c = 0; c < 3; ++c) s[c] += u[3 * (p * nb + b) + c];
-    for (int c = 0; c < 3; ++c) U0[3 * p + c] = s[c] / (double)nb;
-}
-
 // Particle order of a step call.  Each particle is counted into the tile
 // (box included) of its last blob with one global atomic; after the scan of
-// the counts, internal particle offs[tile] + rank is that particle.  The
-// gather and the scatter run one thread per float64 of the positions, so
-// both sides of every copy are runs of 3 nb contiguous values.
+// the counts, internal particle offs[tile] + rank is that particle.
 __global__ void __launch_bounds__(BLK)
 k_part_count(const double* __restrict__ q, int64_t P, int nb, int64_t pbox, double inv_h,
              int L, Tiles tl, int* __restrict__ count, int* __restrict__ tile_of,
@@ -1584,60 +1586,192 @@ k_part_count(const double* __restrict__ q, int64_t P, int nb, int64_t pbox, doub
     rank[p] = atomicAdd(&count[t], 1);
 }
 
-__global__ void __launch_bounds__(BLK)
+// Positions (and particle forces) into the internal order.  A block takes
+// ppf particles, at most PART_VALS float64 of positions: contiguous in q, and
+// a run of 3 nb values per particle in qi.  Bound by HBM (positions read and
+// written once); one thread per value of the whole array spent its time on a
+// 64-bit division by 3 nb instead.
+constexpr int PART_THREADS = 512;
+constexpr int PART_PER = 4;  // values per thread
+constexpr int PART_VALS = PART_THREADS * PART_PER;
+
+__global__ void __launch_bounds__(PART_THREADS)
 k_part_gather(const double* __restrict__ q, const double* __restrict__ Fext, int64_t P,
-              int nb, const int* __restrict__ offs, const int* __restrict__ tile_of,
+              int nb, int ppf, const int* __restrict__ offs, const int* __restrict__ tile_of,
               const int* __restrict__ rank, int* __restrict__ order,
               double* __restrict__ qi, double* __restrict__ Fi) {
-    const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    const int64_t per = 3 * (int64_t)nb;
-    if (j >= per * P) return;
-    const int64_t p = j / per;
-    const int64_t c = j - p * per;
-    const int64_t pos = (int64_t)offs[tile_of[p]] + rank[p];
-    qi[pos * per + c] = q[j];
-    if (c < 3 && Fext) Fi[3 * pos + c] = Fext[3 * p + c];
-    if (c == 0) order[pos] = (int)p;
-}
-
-__global__ void __launch_bounds__(BLK)
-k_part_scatter(const double* __restrict__ qi, const int* __restrict__ order, int64_t P,
-               int nb, double* __restrict__ q, const double* __restrict__ ui,
-               double* __restrict__ u, const double* __restrict__ U0i,
-               double* __restrict__ U0) {
-    const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    const int64_t per = 3 * (int64_t)nb;
-    if (j >= per * P) return;
-    const int64_t pi = j / per;
-    const int64_t c = j - pi * per;
-    const int64_t p = order[pi];
-    q[p * per + c] = qi[j];
-    if (u) u[p * per + c] = ui[j];
-    if (U0 && c < 3) U0[3 * p + c] = U0i[3 * pi + c];
-}
-
-__global__ void __launch_bounds__(BLK)
-k_diag(const double* __restrict__ tile_part, int ntiles,
-       const double* __restrict__ force_part, int nfb, double mom_scale,
-       double* __restrict__ diag) {
-    __shared__ double red[16];
-    double s[3] = {0.0, 0.0, 0.0}, sf[3] = {0.0, 0.0, 0.0}, mx = 0.0;
-    for (int i = threadIdx.x; i < ntiles; i += BLK) {
-        for (int c = 0; c < 3; ++c) s[c] += tile_part[4 * i + c];
-        mx = fmax(mx, tile_part[4 * i + 3]);
+    __shared__ int pos[PART_VALS / 3];
+    const int per = 3 * nb;
+    const int64_t p0 = (int64_t)blockIdx.x * ppf;
+    const int np = (int)(P - p0 < ppf ? P - p0 : ppf);
+    const int n = np * per;
+    const double* qg = q + p0 * per;
+    double x[PART_PER];
+#pragma unroll
+    for (int k = 0; k < PART_PER; ++k) {
+        const int i = threadIdx.x + k * PART_THREADS;
+        x[k] = qg[i < n ? i : 0];
     }
-    for (int i = threadIdx.x; i < nfb; i += BLK)
-        for (int c = 0; c < 3; ++c) sf[c] += force_part[3 * i + c];
-    for (int c = 0; c < 3; ++c) {
-        const double a = block_reduce<false>(s[c], red);
-        const double b = block_reduce<false>(sf[c], red);
-        if (threadIdx.x == 0) {
-            diag[c] = mom_scale * a;
-            diag[3 + c] = b;
+    for (int p = threadIdx.x; p < np; p += PART_THREADS) {
+        pos[p] = offs[tile_of[p0 + p]] + rank[p0 + p];
+        order[pos[p]] = (int)(p0 + p);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PART_PER; ++k) {
+        const int i = threadIdx.x + k * PART_THREADS;
+        const int p = i / per;
+        if (i < n) qi[(int64_t)pos[p] * per + (i - p * per)] = x[k];
+    }
+    if (Fext)
+        for (int i = threadIdx.x; i < 3 * np; i += PART_THREADS) {
+            const int p = i / 3;
+            Fi[3 * (int64_t)pos[p] + (i - 3 * p)] = Fext[3 * p0 + i];
+        }
+}
+
+// Sums over NT threads of six doubles and the maximum of a seventh; the
+// results in thread 0..6 each (value of thread k: entry k).  red: 7 doubles
+// per wave.
+template <int NT>
+__device__ __forceinline__ double diag_reduce(const double s[7], double* red) {
+    const int lane = threadIdx.x % WAVE, wid = threadIdx.x / WAVE;
+    double w[7];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) w[c] = c < 6 ? wave_sum(s[c]) : wave_max(s[c]);
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < 7; ++c) red[7 * wid + c] = w[c];
+    }
+    __syncthreads();
+    double r = 0.0;
+    if (threadIdx.x < 7) {
+        r = red[threadIdx.x];
+        for (int k = 1; k < NT / WAVE; ++k) {
+            const double x = red[7 * k + threadIdx.x];
+            r = threadIdx.x < 6 ? r + x : fmax(r, x);
         }
     }
-    const double m = block_reduce<true>(mx, red);
-    if (threadIdx.x == 0) diag[6] = m;
+    return r;
+}
+
+// The thread's share of the diagnostics' partials: entries [t0, t1) of the
+// tile partials (sum v, max |Dv|) and [f0, f1) of the springs blocks' force
+// sums.
+template <int NT>
+__device__ __forceinline__ void diag_partials(const double* __restrict__ tile_part, int t0, int t1,
+                                              const double* __restrict__ force_part, int f0,
+                                              int f1, double s[7]) {
+#pragma unroll 4
+    for (int i = t0 + threadIdx.x; i < t1; i += NT) {
+        const double2 a = reinterpret_cast<const double2*>(tile_part)[2 * i];
+        const double2 b = reinterpret_cast<const double2*>(tile_part)[2 * i + 1];
+        s[0] += a.x;
+        s[1] += a.y;
+        s[2] += b.x;
+        s[6] = fmax(s[6], b.y);
+    }
+#pragma unroll 4
+    for (int i = f0 + threadIdx.x; i < f1; i += NT) {
+        s[3] += force_part[3 * i];
+        s[4] += force_part[3 * i + 1];
+        s[5] += force_part[3 * i + 2];
+    }
+}
+
+// First level of the diagnostics where there are many partials: block b
+// reduces its share into pre[8 b .. 8 b + 6].
+__global__ void __launch_bounds__(BLK)
+k_diag_part(const double* __restrict__ tile_part, int ntiles,
+            const double* __restrict__ force_part, int nfb, double* __restrict__ pre) {
+    __shared__ double red[7 * (BLK / WAVE)];
+    const int nt = (ntiles + gridDim.x - 1) / gridDim.x, nf = (nfb + gridDim.x - 1) / gridDim.x;
+    const int b = blockIdx.x;
+    double s[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    diag_partials<BLK>(tile_part, b * nt, min((b + 1) * nt, ntiles), force_part, b * nf,
+                       min((b + 1) * nf, nfb), s);
+    const double r = diag_reduce<BLK>(s, red);
+    if (threadIdx.x < 7) pre[8 * b + threadIdx.x] = r;
+}
+
+// End of a step call, in one launch.  Blocks below nu take ppf particles
+// each (at most PART_VALS values): their positions back to the caller's
+// order (qi, order), their blob velocities u likewise (u_out) and the
+// particle velocities U0, means of u through LDS; each nullable, order null
+// where the call kept the caller's order.  The block after them reduces the
+// diagnostics (diag nullable) from the partials, or from the npre first-level
+// results in pre.
+struct Finish {
+    const double* qi;
+    const int* order;
+    double* q;
+    const double* u;
+    double* u_out;
+    double* U0;
+    int64_t P;
+    int nb, ppf, nu;
+    const double* tile_part;
+    const double* force_part;
+    const double* pre;
+    int ntiles, nfb, npre;
+    double mom_scale;
+    double* diag;
+};
+
+__global__ void __launch_bounds__(PART_THREADS)
+k_finish(Finish f) {
+    __shared__ double us[PART_VALS];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < f.nu) {
+        const int per = 3 * f.nb;
+        const int64_t p0 = (int64_t)blockIdx.x * f.ppf;
+        const int np = (int)(f.P - p0 < f.ppf ? f.P - p0 : f.ppf);
+        const int n = np * per;
+        double x[PART_PER], y[PART_PER];
+        int64_t to[PART_PER];
+#pragma unroll
+        for (int k = 0; k < PART_PER; ++k) {
+            const int i = tid + k * PART_THREADS;
+            const int ic = i < n ? i : 0;
+            if (f.qi) x[k] = f.qi[p0 * per + ic];
+            if (f.u) y[k] = f.u[p0 * per + ic];
+            if (f.order) {
+                const int p = ic / per;
+                to[k] = (int64_t)f.order[p0 + p] * per + (ic - p * per);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PART_PER; ++k) {
+            const int i = tid + k * PART_THREADS;
+            if (i < n) {
+                if (f.qi) f.q[to[k]] = x[k];
+                if (f.u_out) f.u_out[to[k]] = y[k];
+                if (f.u) us[i] = y[k];
+            }
+        }
+        if (!f.U0) return;
+        __syncthreads();
+        for (int i = tid; i < 3 * np; i += PART_THREADS) {
+            const int p = i / 3, c = i - 3 * (i / 3);
+            double s = 0.0;
+            for (int b = 0; b < f.nb; ++b) s += us[p * per + 3 * b + c];
+            const int64_t pc = f.order ? f.order[p0 + p] : p0 + p;
+            f.U0[3 * pc + c] = s / (double)f.nb;
+        }
+        return;
+    }
+    double s[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (f.pre) {
+        for (int i = tid; i < f.npre; i += PART_THREADS) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) s[c] += f.pre[8 * i + c];
+            s[6] = fmax(s[6], f.pre[8 * i + 6]);
+        }
+    } else {
+        diag_partials<PART_THREADS>(f.tile_part, 0, f.ntiles, f.force_part, 0, f.nfb, s);
+    }
+    const double r = diag_reduce<PART_THREADS>(s, us);
+    if (tid < 7) f.diag[tid] = tid < 3 ? f.mom_scale * r : r;
 }
 
 // ---------------------------------------------------------------------------
@@ -1682,6 +1816,9 @@ hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s, bool
     return hipGetLastError();
 }
 
+// Particles per block of the particle copies.
+static int particles_per_block(int nb) { return PART_VALS / (3 * nb); }
+
 hipError_t order_particles(mb_grid* g, int64_t P, int nb, const double* q,
                            const double* Fext, hipStream_t s) {
     if (P == 0) return hipSuccess;
@@ -1689,17 +1826,56 @@ hipError_t order_particles(mb_grid* g, int64_t P, int nb, const double* q,
                        P / g->tiles.nbox, 1.0 / g->d.h, g->L, g->tiles, g->d_count, g->d_tile,
                        g->d_rank);
     scan_tiles(g, s);
-    hipLaunchKernelGGL(k_part_gather, dim3(blocks_for(3 * nb * P)), dim3(BLK), 0, s, q, Fext, P,
-                       nb, g->d_offs, g->d_tile, g->d_rank, g->d_order, g->d_qint, g->d_pint);
+    const int ppf = particles_per_block(nb);
+    hipLaunchKernelGGL(k_part_gather, dim3((unsigned)((P + ppf - 1) / ppf)), dim3(PART_THREADS),
+                       0, s, q, Fext, P, nb, ppf, g->d_offs, g->d_tile, g->d_rank, g->d_order,
+                       g->d_qint, g->d_pint);
     return hipGetLastError();
 }
 
-hipError_t unorder_particles(mb_grid* g, int64_t P, int nb, double* q, const double* u_int,
-                             double* u_out, const double* U0_int, double* U0_out,
-                             hipStream_t s) {
-    if (P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_part_scatter, dim3(blocks_for(3 * nb * P)), dim3(BLK), 0, s,
-                       g->d_qint, g->d_order, P, nb, q, u_int, u_out, U0_int, U0_out);
+// Partials of the diagnostics above which a first level of kDiagBlocks
+// blocks reduces them (128^3 phi = 0.3: 2,048 tiles and 1,930 springs blocks,
+// read by the one block; 256^3 phi = 0.4: 16,384 and 20,587, 71 us by one
+// block).
+constexpr int kDiagOneLevel = 8192;
+constexpr int kDiagBlocks = 64;
+
+hipError_t finish_call(mb_grid* g, int64_t P, int nb, bool reordered, double* q, const double* u,
+                       double* u_out, double* U0, int force_blocks, double* diag,
+                       hipStream_t s) {
+    Finish f{};
+    f.P = P;
+    f.nb = nb;
+    f.ppf = particles_per_block(nb);
+    if (reordered) {
+        f.qi = g->d_qint;
+        f.order = g->d_order;
+        f.q = q;
+        f.u_out = u_out;
+    }
+    f.U0 = U0;
+    if (U0 || f.u_out) f.u = u;
+    f.nu = (f.qi || f.u) ? (int)((P + f.ppf - 1) / f.ppf) : 0;
+    f.diag = diag;
+    if (diag) {
+        const double h = g->d.h;
+        f.mom_scale = g->d.rho * h * h * h;
+        f.tile_part = g->d_tile_part;
+        f.force_part = g->d_force_part;
+        f.ntiles = g->tiles.n * g->tiles.nbox;
+        f.nfb = force_blocks;
+        // (the x pass's partial sums are free after the last solve)
+        if (f.ntiles + f.nfb > kDiagOneLevel &&
+            (int64_t)g->nblk_x * g->tiles.nbox * 2 >= 8 * kDiagBlocks) {
+            hipLaunchKernelGGL(k_diag_part, dim3(kDiagBlocks), dim3(BLK), 0, s, f.tile_part,
+                               f.ntiles, f.force_part, f.nfb, g->d_psum);
+            f.pre = g->d_psum;
+            f.npre = kDiagBlocks;
+        }
+    }
+    const int blocks = f.nu + (diag ? 1 : 0);
+    if (blocks == 0) return hipGetLastError();
+    MB_LAUNCH(g, diag ? K_DIAG : K_U0, s, k_finish, blocks, PART_THREADS, 0, f);
     return hipGetLastError();
 }
 
@@ -1951,22 +2127,6 @@ hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wsca
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-
-hipError_t particle_means(mb_grid* g, int64_t P, int nb, const double* u,
-                          double* U0, hipStream_t s) {
-    if (P == 0) return hipSuccess;
-    MB_LAUNCH(g, K_U0, s, k_u0, blocks_for(P), BLK, 0, u, P, nb, U0);
-    return hipGetLastError();
-}
-
-hipError_t diagnostics(mb_grid* g, int force_blocks, double* diag,
-                       hipStream_t s) {
-    const double h = g->d.h;
-    const double scale = g->d.rho * h * h * h;
-    MB_LAUNCH(g, K_DIAG, s, k_diag, 1, BLK, 0, g->d_tile_part, g->tiles.n * g->tiles.nbox,
-              g->d_force_part, force_blocks, scale, diag);
-    return hipGetLastError();
-}
 
 // Explicit instantiations.
 template hipError_t bin_blobs<float>(mb_grid*, int64_t, const double*, hipStream_t, bool, bool);
