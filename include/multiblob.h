@@ -175,8 +175,8 @@ mb_status mb_grid_create(const mb_grid_desc* desc, mb_grid** out);
  * spectrum, the spread boxes (sized for every tile shape that fits L, so
  * mb_grid_set_tiles and mb_grid_autotune never reallocate), the binning
  * arrays, the sorted blob records and the partial sums of the diagnostics.
- * The midpoint scheme (mb_grid_set_scheme), forced steps and the reverse
- * step keep their extra scratch outside it (allocated by the library when
+ * The midpoint scheme (mb_grid_set_scheme) and the reverse step keep their
+ * extra scratch outside it (allocated by the library when
  * first enabled or called).  0 for an invalid description or nbox. */
 size_t mb_workspace_size(const mb_grid_desc* desc, int32_t nbox);
 
@@ -287,9 +287,8 @@ mb_status mb_step_ext(mb_grid* grid, const mb_springs* springs,
  * It drives the periodic forcing f = f0 sin(k_j y) x of the viscosity
  * measurement (Sec. Stresslet and Viscosity).  f_fluid: [3][L][L][L]
  * ([nbox][3][L][L][L] for a batch), the grid's precision, on the device,
- * not NULL, unchanged by the call.  The first call allocates one field of
- * scratch in the grid (kept until mb_grid_destroy; MB_ERR_NOMEM if that
- * fails).  The diagnostics' sum F covers the blob forces only. */
+ * not NULL, unchanged by the call.  The diagnostics' sum F covers the blob
+ * forces only. */
 mb_status mb_step_forced(mb_grid* grid, const mb_springs* springs,
                          int64_t nparticles, double* q, void* v,
                          const double* Fext, const double* F_blob,
@@ -350,7 +349,7 @@ mb_status mb_spring_adjoint(const mb_springs* springs, int64_t nparticles,
  * qbar [M][3] holds dloss/dq^{n+1} on entry and dloss/dq^n on return; vbar
  * [3][L^3] likewise dloss/dv^{n+1} -> dloss/dv^n.  Accumulated:
  * Fblob_bar [M][3] (dloss/dF_blob), kbar (1 double), r0bar (npairs doubles);
- * each may be NULL.  Allocates its scratch (about 9 L^3 + 9 max_blobs
+ * each may be NULL.  Allocates its scratch (about 3 L^3 + 9 max_blobs
  * doubles) on the first call. */
 mb_status mb_step_adjoint(mb_grid* grid, const mb_springs* springs,
                           int64_t nparticles, const double* q_n,

@@ -153,10 +153,11 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // arrays (tile, rank, sorted blob, records, velocities), the springs
 // blocks' force sums, the non-finite flag, and the particle reordering of
 // the step calls (positions and a per-particle array in the calls' own
-// particle order, and that order).
+// particle order, and that order), and a byte per z plane (whether it holds
+// a force).
 struct WsLayout {
     enum { TW, DSYM, D2, SPEC, PSUM, COUNT, OFFS, BSUM, TPART, BOX, TILE, RANK, PERM,
-           REC, U, FPART, FLAG, QINT, PINT, ORDER, NREG };
+           REC, U, FPART, FLAG, QINT, PINT, ORDER, ACT, NREG };
     size_t off[NREG];
     size_t total;
     int ntiles_cap;  // tiles per box
@@ -203,6 +204,7 @@ WsLayout ws_layout(const mb_grid_desc& d, int nbox) {
     sz[WsLayout::QINT] = (size_t)cap * 3 * sizeof(double);
     sz[WsLayout::PINT] = (size_t)cap * 3 * sizeof(double);  // particles <= blobs
     sz[WsLayout::ORDER] = (size_t)cap * sizeof(int);
+    sz[WsLayout::ACT] = (size_t)nbox * L;
     size_t o = 0;
     for (int r = 0; r < WsLayout::NREG; ++r) {
         w.off[r] = o;
@@ -241,6 +243,7 @@ void ws_bind(mb_grid* g, void* base) {
     g->d_qint = (double*)(b + w.off[WsLayout::QINT]);
     g->d_pint = (double*)(b + w.off[WsLayout::PINT]);
     g->d_order = (int*)(b + w.off[WsLayout::ORDER]);
+    g->d_act = (unsigned char*)(b + w.off[WsLayout::ACT]);
     g->perm_m = -1;
 }
 
@@ -253,7 +256,7 @@ void set_scan_blocks(mb_grid* g) {
 void free_grid(mb_grid* g) {
     if (!g) return;
     if (g->ws_owned && g->ws) (void)hipFree(g->ws);
-    void* ptrs[] = {g->d_adj, g->d_adj_part, g->d_ffield, g->d_mid};
+    void* ptrs[] = {g->d_adj, g->d_adj_part, g->d_mid};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (auto& tp : g->pending) {
@@ -561,13 +564,11 @@ mb_status mb_spread(mb_grid* g, int64_t M, const double* q, const double* F,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_blobs<float>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<float>(g, M, q, F, s);
+        e = bin_records<float>(g, M, q, F, s);
         if (e == hipSuccess) e = spread_boxes<float>(g, s);
         if (e == hipSuccess) e = fold_boxes<float>(g, (float*)f_out, s);
     } else {
-        e = bin_blobs<double>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<double>(g, M, q, F, s);
+        e = bin_records<double>(g, M, q, F, s);
         if (e == hipSuccess) e = spread_boxes<double>(g, s);
         if (e == hipSuccess) e = fold_boxes<double>(g, (double*)f_out, s);
     }
@@ -586,12 +587,10 @@ mb_status mb_interpolate(mb_grid* g, int64_t M, const double* q, const void* v,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_blobs<float>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<float>(g, M, q, nullptr, s);
+        e = bin_records<float>(g, M, q, nullptr, s);
         if (e == hipSuccess) e = interpolate<float>(g, M, (const float*)v, u_out, nullptr, 0, s);
     } else {
-        e = bin_blobs<double>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<double>(g, M, q, nullptr, s);
+        e = bin_records<double>(g, M, q, nullptr, s);
         if (e == hipSuccess) e = interpolate<double>(g, M, (const double*)v, u_out, nullptr, 0, s);
     }
     return finish(g, e, s);
@@ -609,9 +608,9 @@ mb_status mb_fluid_solve(mb_grid* g, const void* v_in, const void* f,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4)
-        e = fluid_solve<float>(g, (const float*)v_in, (const float*)f, (float*)v_out, s);
+        e = fluid_solve<float>(g, (const float*)v_in, {(const float*)f}, (float*)v_out, s);
     else
-        e = fluid_solve<double>(g, (const double*)v_in, (const double*)f, (double*)v_out, s);
+        e = fluid_solve<double>(g, (const double*)v_in, {(const double*)f}, (double*)v_out, s);
     return from_hip(e);
 }
 
@@ -628,6 +627,15 @@ mb_status mb_spring_forces(const mb_springs* sp, int64_t P, const double* q,
                                   (hipStream_t)stream, nullptr));
 }
 
+// Blobs per box where boxes without blobs are neither written by the spreading
+// nor read by the solve (small boxes, binned so), else 0.  Up to 256 box tiles
+// the whole array is cheaper than marking its boxes in every block of the x
+// pass (one 32^3 box: x pass 5.4 us, masked 9.9).
+constexpr int kMaskBoxTiles = 256;
+static int masked_blobs(const mb_grid* g, int64_t M) {
+    return g->btiles.n * g->tiles.nbox > kMaskBoxTiles ? (int)(M / g->tiles.nbox) : 0;
+}
+
 // One step of the grid's scheme on fields of type T (u_dst: blob velocities
 // of the step, or null).
 extern "C++" {
@@ -636,21 +644,28 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
                             double* q, T* v, const double* Fext, const double* Gblob,
                             const T* ffluid, double* u_dst, hipStream_t s,
                             bool binned = false, bool bin_next = false, bool diag = true) {
-    T* ff = (T*)g->d_ffield;
-    // forces at positions x, spread into the boxes (and folded with the
-    // fluid force when there is one); binned: the counts of q are in place;
+    // few blobs per box: binned by box, and boxes without any neither written
+    // nor read
+    const bool small = small_boxes(g, M, &sd);
+    const int masked = small && !ffluid ? masked_blobs(g, M) : 0;
+    const bool mark = masked > 0 && g->d.mode == MB_STEADY_STOKES;
+    // forces at positions x, spread into the boxes; binned: the counts of q are in place;
     // sums: the force sums of the diagnostics.  The diagnostics' partial
     // sums (forces, momentum, max |Dv|) are formed only when diag is set
     // (the step whose diagnostics are returned).
     auto forces = [&](const double* x, bool counted, bool sums) {
-        const bool fuse = fused_scan_ok(g, s);  // the scan in the springs kernel
-        hipError_t e = bin_blobs<T>(g, M, x, s, counted, !fuse);
-        if (e == hipSuccess) e = scatter_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, fuse);
-        if (e == hipSuccess) e = spread_boxes<T>(g, s);
-        if (e == hipSuccess && ffluid) e = fold_boxes<T>(g, ff, s, ffluid);
+        hipError_t e;
+        if (small) {
+            e = bin_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, mark);
+        } else {
+            const bool fuse = fused_scan_ok(g, s);  // the scan in the springs kernel
+            e = bin_blobs<T>(g, M, x, s, counted, !fuse);
+            if (e == hipSuccess) e = scatter_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, fuse);
+        }
+        if (e == hipSuccess) e = spread_boxes<T>(g, s, masked > 0);
         return e;
     };
-    auto solve = [&]() { return fluid_solve<T>(g, v, ff, v, s, !ffluid); };
+    auto solve = [&]() { return fluid_solve<T>(g, v, {ffluid, true, masked, false}, v, s); };
     hipError_t e;
     const int dg = diag ? 1 : 0;
     if (g->scheme == MB_SCHEME_EULER) {
@@ -675,8 +690,7 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
         return e;
     }
     // q* += (dt/2) J(q^n) v^n on the records of q^n
-    if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s);
-    if (e == hipSuccess) e = scatter_records<T>(g, M, q, nullptr, s);
+    if (e == hipSuccess) e = bin_records<T>(g, M, q, nullptr, s);
     if (e == hipSuccess) e = interpolate<T>(g, M, v, nullptr, qs, 0, s, 0.5);
     // forces at q*; q += (dt/2) J(q*) v^n; solve; q += (dt/2) J(q*) v^{n+1}
     if (e == hipSuccess) e = forces(qs, false, diag);
@@ -687,13 +701,6 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
     return e;
 }
 }  // extern "C++"
-
-static hipError_t alloc_lazy(void** p, size_t bytes) {
-    if (*p) return hipSuccess;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) *p = nullptr;
-    return e;
-}
 
 // Calls of at least this many steps reorder the particles for locality.
 constexpr int kReorderMinSteps = 8;
@@ -720,10 +727,9 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
     if (nsteps == 0) return MB_OK;
     hipStream_t s = (hipStream_t)stream;
     const SpringsDev sd = springs_dev(sp);
-    const int fb = springs_blocks(sd, P);
+    const bool small = small_boxes(g, M, &sd);
+    const int fb = small ? g->tiles.nbox : springs_blocks(sd, P);  // force partials
     hipError_t e = hipSuccess;
-    if (ffluid) e = alloc_lazy(&g->d_ffield, (size_t)3 * g->N * g->tiles.nbox * g->fsz);
-    if (e != hipSuccess) return e == hipErrorOutOfMemory ? MB_ERR_NOMEM : MB_ERR_DEVICE;
     if (M == 0 && diag_out) {
         // no blobs: the force partials of the diagnostics are zero
         e = zero_words(g->d_force_part, 3 * 2, s);
@@ -733,7 +739,8 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
     // particle forces) with the particles ordered by tile, so that the blobs
     // of a tile are near one another in memory (their position updates and
     // records then share cache lines); results do not depend on the order.
-    const bool reorder = M > 0 && nsteps >= kReorderMinSteps && !Gblob && !ffluid;
+    const bool reorder =
+        M > 0 && nsteps >= kReorderMinSteps && !Gblob && !ffluid && !small;
     double* qs = q;
     const double* Fs = Fext;
     if (reorder) {
@@ -747,8 +754,9 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
     }
     // first-order steps after the first of the call take their binning from
     // the interpolation of the step before (the positions it wrote); the
-    // last step leaves the counts at zero
-    const bool carry = g->scheme == MB_SCHEME_EULER && M > 0;
+    // last step leaves the counts at zero (small boxes are binned with their
+    // forces instead)
+    const bool carry = g->scheme == MB_SCHEME_EULER && M > 0 && !small;
     const double* u_last = nullptr;
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         const bool last = n == nsteps - 1;
@@ -911,12 +919,10 @@ mb_status mb_interpolate_grad(mb_grid* g, int64_t M, const double* q, const void
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_blobs<float>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<float>(g, M, q, nullptr, s);
+        e = bin_records<float>(g, M, q, nullptr, s);
         if (e == hipSuccess) e = interpolate_grad<float>(g, (const float*)v, W, 1.0, g_inout, s);
     } else {
-        e = bin_blobs<double>(g, M, q, s);
-        if (e == hipSuccess) e = scatter_records<double>(g, M, q, nullptr, s);
+        e = bin_records<double>(g, M, q, nullptr, s);
         if (e == hipSuccess)
             e = interpolate_grad<double>(g, (const double*)v, W, 1.0, g_inout, s);
     }
@@ -960,12 +966,10 @@ mb_status mb_step_adjoint(mb_grid* g, const mb_springs* sp, int64_t P, const dou
     const size_t nf = (size_t)3 * g->N * g->tiles.nbox;
     const size_t nbl = (size_t)3 * std::max<int64_t>(g->d.max_blobs, 1);
     if (!g->d_adj) {
-        // scratch of the reverse step: fields wbar, fbar, zero; blob arrays
-        // ubar, F, Fbar
-        e = hipMalloc(&g->d_adj, (3 * nf + 3 * nbl) * sizeof(double));
-        if (e == hipSuccess) e = hipMemset(g->d_adj, 0, (3 * nf + 3 * nbl) * sizeof(double));
+        // scratch of the reverse step: the field fbar; blob arrays ubar, F,
+        // Fbar (each written before it is read)
+        e = hipMalloc((void**)&g->d_adj, (nf + 3 * nbl) * sizeof(double));
         if (e != hipSuccess) {
-            if (g->d_adj) (void)hipFree(g->d_adj);
             g->d_adj = nullptr;
             return e == hipErrorOutOfMemory ? MB_ERR_NOMEM : MB_ERR_DEVICE;
         }
@@ -988,10 +992,8 @@ mb_status mb_step_adjoint(mb_grid* g, const mb_springs* sp, int64_t P, const dou
         }
         part = g->d_adj_part;
     }
-    double* wbar = g->d_adj;
-    double* fbar = wbar + nf;
-    const double* zero = fbar + nf;  // never written after the allocation
-    double* ubar = wbar + 3 * nf;
+    double* fbar = g->d_adj;
+    double* ubar = fbar + nf;
     double* F = ubar + nbl;
     double* Fbar = F + nbl;
     const double h = g->d.h;
@@ -999,19 +1001,16 @@ mb_status mb_step_adjoint(mb_grid* g, const mb_springs* sp, int64_t P, const dou
     const SpringsDev sd = springs_dev(sp);
     const double* vn1 = (const double*)v_np1;
     double* vb = (double*)vbar;
-    // q^{n+1} = q^n + dt u^n:  ubar = ubar_loss + dt qbar
-    e = blob_axpy(3 * M, ubar_loss, g->d.dt, qbar, ubar, s);
-    // records of q^n carrying ubar (scale 1: h^3 S ubar = J^T ubar)
-    if (e == hipSuccess) e = bin_blobs<double>(g, M, q_n, s);
-    if (e == hipSuccess) e = scatter_records<double>(g, M, q_n, ubar, s, 1.0);
+    // q^{n+1} = q^n + dt u^n:  ubar = ubar_loss + dt qbar; records of q^n
+    // carrying ubar (scale 1: h^3 S ubar = J^T ubar)
+    e = bin_records<double>(g, M, q_n, qbar, s, 1.0, ubar_loss, g->d.dt, ubar);
     // u^n = J(q^n) v^{n+1}: position part
     if (e == hipSuccess && M > 0) e = interpolate_grad<double>(g, vn1, ubar, 1.0, qbar, s);
-    // wbar = vbar + J^T ubar
+    // wbar = vbar + J^T ubar: the boxes of ubar and the field vbar, summed as
+    // the solve reads them.  v^{n+1} = Q (C v^n + f^n): fbar = Q wbar, vbar =
+    // C Q wbar (Q and C commute; steady: vbar = 0)
     if (e == hipSuccess) e = spread_boxes<double>(g, s);
-    if (e == hipSuccess) e = fold_boxes<double>(g, wbar, s, vb);
-    // v^{n+1} = Q (C v^n + f^n): fbar = Q wbar, vbar = C Q wbar (Q and C
-    // commute; steady: vbar = 0)
-    if (e == hipSuccess) e = fluid_solve<double>(g, zero, wbar, fbar, s);
+    if (e == hipSuccess) e = fluid_solve<double>(g, nullptr, {vb, true, 0, true}, fbar, s);
     if (e == hipSuccess) {
         if (g->d.mode == MB_STEADY_STOKES) e = zero_words(vb, nf * 2, s);
         else e = apply_cn<double>(g, fbar, vb, s);

@@ -39,6 +39,20 @@ __device__ __forceinline__ cplx<T> mul_mi(cplx<T> a) {
     return INV ? cplx<T>{-a.y, a.x} : cplx<T>{a.y, -a.x};
 }
 
+// Sorted-blob records, in two arrays.  The geometry record holds the
+// position's fraction of its cell per axis, s = x/h - floor(x/h) in [0, 1),
+// and the packed cell: bits 0-8 x, 9-17 y, 18-26 z, 27-29 the "rounds up"
+// bit per axis (s >= 1/2).  The kernel offset of the cell-centred node set
+// is t = s - bit (nearest node c + bit), that of the component's own,
+// half-cell shifted set t = s - 1/2 (nearest node c); rec_t forms them.
+// The force record (F h^-3 per component, [pos][3]) is a separate array:
+// the interpolation reads only the geometry.
+template <typename T>
+struct __align__(16) RecG {
+    T s[3];
+    uint32_t cell;
+};
+
 // 1/sqrt(x) for a normal float64 x > 0: the hardware estimate refined by
 // two Newton steps y <- y + y (1/2 - x y^2 / 2) for the root of 1/y^2 - x,
 // each of which squares the relative error (an estimate good to 2^-14

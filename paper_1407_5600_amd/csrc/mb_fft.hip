@@ -282,11 +282,42 @@ struct Geo {
 };
 
 // ---------------------------------------------------------------------------
-template <typename T, int L, bool BOX, bool STEADY>
+// Force of the forward x pass: the field f; the boxes (f the box array); the
+// boxes plus a field; or boxes of which some may be unwritten.
+enum : int { SRC_FIELD, SRC_BOX, SRC_BOX_ADD, SRC_MASKED };
+
+// What the last two read.  add (SRC_BOX_ADD): the field added.  rec
+// (SRC_MASKED): the records of the mbox blobs of each box, from which each
+// block marks the box tiles that hold blobs.  act (SRC_MASKED in steady flow,
+// where the force is all there is): whether each z plane of each box holds any
+// force, as the binning marked it; the x and y passes pass over planes without
+// one and the z pass takes them as zero (two particles in 64^3 lie in about 7
+// of the 64 planes).
+template <typename T>
+struct ForceSrc {
+    const T* add;
+    const RecG<T>* rec;
+    int mbox;
+    const unsigned char* act;
+};
+
+// Bits of the nonzero ones of eight flags `stride` apart, read at once.
+__device__ __forceinline__ unsigned active_planes(const unsigned char* __restrict__ act,
+                                                  int stride) {
+    unsigned m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m |= act[k * stride] ? 1u << k : 0u;
+    return m;
+}
+
+template <typename T, int L, int SRC, bool STEADY>
 __global__ void __launch_bounds__((Geo<T, L>::TX))
-k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
+k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> mk,
         const cplx<T>* __restrict__ tw, T a, T b,
         cplx<T>* __restrict__ A, double* __restrict__ psum) {
+    constexpr bool BOX = SRC != SRC_FIELD;
+    constexpr bool MASKED = SRC == SRC_MASKED;
+    constexpr bool ADD = SRC == SRC_BOX_ADD;
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::R, NL = G::NL, NTHR = G::TX, LS = G::LS;
     __shared__ cplx<T> buf[NL * LS];
@@ -297,26 +328,52 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
     // within a box each XCD takes a contiguous range of (c, z, y) rows, so
     // the rows of the Laplacian's z and y neighbours, read by adjacent
     // blocks, are found in that XCD's L2
-    const int box = blockIdx.x / G::NBX;
-    const int lb = xcd_remap(blockIdx.x - box * G::NBX, G::NBX);
+    // with act a block takes the planes zi + k L/8 of which few hold a force:
+    // the planes of a few particles, neighbours, fall to different blocks,
+    // and an eighth of the blocks finds nothing to do
+    constexpr bool ACT = MASKED && STEADY;
+    const bool planes = ACT && mk.act;
+    const int per_box = planes ? G::NBX / 8 : G::NBX;
+    const int box = blockIdx.x / per_box;
+    const int lb = planes ? blockIdx.x - box * per_box : xcd_remap(blockIdx.x - box * per_box, G::NBX);
     const int yb = lb % (L / R);
-    const int cz = lb / (L / R);  // c * L + z
-    const int z = cz % L;
-    const int cbase = (cz - z) * L * L;   // component offset (elements)
+    const int nz = planes ? L / 8 : L;
+    const int comp = lb / (L / R) / nz;
+    const int z_first = lb / (L / R) % nz;
+    const int cbase = comp * L * L * L;   // component offset (elements)
     const int y0 = yb * R;
     v += (size_t)box * 3 * L * L * L;
     A += (size_t)box * 3 * L * NC * L;
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
+    if (!BOX) f += (size_t)box * 3 * L * L * L;
+    unsigned todo = planes ? active_planes(mk.act + (size_t)box * L + z_first, L / 8) : 1u;
+    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0u) {
+    const int z = z_first + (ACT ? (__ffs(todo) - 1) * (L / 8) : 0);
+    const int cz = comp * L + z;
     double sv = 0.0, sf = 0.0;
     const int zm = (z == 0 ? L - 1 : z - 1), zp = (z == L - 1 ? 0 : z + 1);
     // boxed force: the box entries of this z plane and component
     const T* Ec = nullptr;
     AxisSrc bz{};
     if (BOX) {
-        Ec = f + ((size_t)box * 3 + cz / L) * tl.n * box_volume(tl);
+        Ec = f + ((size_t)box * 3 + comp) * tl.n * box_volume(tl);
         bz = box_src_z(tl, z);
-    } else {
-        f += (size_t)box * 3 * L * L * L;
+    }
+    [[maybe_unused]] const T* add = ADD ? mk.add + (size_t)box * 3 * L * L * L : nullptr;
+    __shared__ unsigned long long occ[MASKED ? 2 : 1][MASKED ? MASK_YT : 1];
+    if constexpr (MASKED) {
+        for (int i = tid; i < 2 * MASK_YT; i += NTHR) (&occ[0][0])[i] = 0ull;
+        __syncthreads();
+        const int sx = __ffs(tl.tx) - 1, sy = __ffs(tl.ty) - 1, sz = __ffs(tl.tz) - 1;
+        for (int i = tid; i < mk.mbox; i += NTHR) {
+            const uint32_t cell = mk.rec[(size_t)box * mk.mbox + i].cell;
+            const unsigned long long bit = 1ull << ((cell & 511u) >> sx);
+            const int ty = (int)((cell >> 9) & 511u) >> sy;
+            const int tz = (int)((cell >> 18) & 511u) >> sz;
+            if (tz == bz.t[0]) atomicOr(&occ[0][ty], bit);
+            if (bz.n > 1 && tz == bz.t[1]) atomicOr(&occ[1][ty], bit);
+        }
+        __syncthreads();
     }
     // KG iterations (2 KG nodes) per round: all loads of a round, the box
     // entries included (box_entries: loads only, in uniform branches), are
@@ -354,6 +411,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
                 const int y = y0 + 2 * line + hh;
                 const int row = cbase + (z * L + y) * L;
                 if (!BOX) fv[0][hh] = at(fb, row, ox);
+                if constexpr (ADD) fv[0][hh] = at(reinterpret_cast<const char*>(add), row, ox);
                 if (!STEADY) {
                     const int ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
                     vc[0][hh] = at(vb, row, ox);
@@ -367,8 +425,11 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
             }
             if constexpr (BOX) {
 #pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-                    box_entries(Ec, bxu, box_src_y(tl, y0 + 2 * line + hh), bz, eb[0][hh]);
+                for (int hh = 0; hh < 2; ++hh) {
+                    const AxisSrc by = box_src_y(tl, y0 + 2 * line + hh);
+                    if constexpr (MASKED) box_entries_masked(Ec, bxu, by, bz, occ, eb[0][hh]);
+                    else box_entries(Ec, bxu, by, bz, eb[0][hh]);
+                }
             }
         } else {
 #pragma unroll
@@ -382,6 +443,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
                 const int y = y0 + 2 * line + hh;
                 const unsigned row = (unsigned)(cbase + (z * L + y) * L);
                 if (!BOX) fv[g][hh] = ld32(f, row + x);
+                if constexpr (ADD) fv[g][hh] = ld32(add, row + x);
                 if (!STEADY) {
                     const int ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
                     vc[g][hh] = ld32(v, row + x);
@@ -399,7 +461,10 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
                 for (int hh = 0; hh < 2; ++hh) {
                     const int y = y0 + 2 * line + hh;
                     const int yu = UNI ? __builtin_amdgcn_readfirstlane(y) : y;
-                    box_entries(Ec, bx, box_src_y(tl, yu), bz, eb[g][hh]);
+                    if constexpr (MASKED)
+                        box_entries_masked(Ec, bx, box_src_y(tl, yu), bz, occ, eb[g][hh]);
+                    else
+                        box_entries(Ec, bx, box_src_y(tl, yu), bz, eb[g][hh]);
                 }
             }
         }
@@ -412,7 +477,8 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
             T val[2];
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
-                if (BOX) fv[g][hh] = box_entries_sum(eb[g][hh]);
+                if (ADD) fv[g][hh] = box_entries_sum(eb[g][hh]) + fv[g][hh];
+                else if (BOX) fv[g][hh] = box_entries_sum(eb[g][hh]);
                 sf += (double)fv[g][hh];
                 if (STEADY) {
                     val[hh] = fv[g][hh];
@@ -459,9 +525,12 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
             ts += red[2 * w];
             tf += red[2 * w + 1];
         }
-        const size_t pb = (size_t)box * G::NBX + lb;  // component-major order
-        psum[2 * pb] = ts;
-        psum[2 * pb + 1] = tf;
+        if (!planes) {
+            const size_t pb = (size_t)box * G::NBX + lb;  // component-major order
+            psum[2 * pb] = ts;
+            psum[2 * pb + 1] = tf;
+        }
+    }
     }
 }
 
@@ -469,18 +538,27 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl,
 // length L (along ky) are contiguous in A.
 template <typename T, int L, bool INV>
 __global__ void __launch_bounds__((Geo<T, L>::TY))
-k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw) {
+k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
+    const unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, W = G::WY, NTHR = G::TY, LS = G::LS;
     __shared__ cplx<T> buf[W * LS];
     __shared__ cplx<T> tws[L];
     const int tid = threadIdx.x;
     const int ch = blockIdx.x % G::NCHY;
-    const int cz = blockIdx.x / G::NCHY;  // (box * 3 + c) * L + z
+    for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
+    // act (nullable): planes without force are neither read nor written; a
+    // block then takes the planes zi + k L/8, as the x pass
+    const int nz = act ? L / 8 : L;
+    const int bc = blockIdx.x / G::NCHY / nz;  // box * 3 + c
+    const int z0 = blockIdx.x / G::NCHY % nz;
+    unsigned todo = act ? active_planes(act + (size_t)(bc / 3) * L + z0, L / 8) : 1u;
+    for (; todo != 0; todo &= todo - 1) {
+    const int z = z0 + (__ffs(todo) - 1) * (L / 8);
+    const int cz = bc * L + z;
     const int kx0 = ch * W;
     const int wc = NC - kx0 < W ? NC - kx0 : W;
     cplx<T>* base = A + ((size_t)cz * NC + kx0) * L;
-    for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     // first stage straight from A, last stage straight back (a short last
     // chunk re-reads its first row and stores only its own rows)
     auto gload = [base, wc](int line, int e) {
@@ -489,8 +567,9 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw) {
     auto gstore = [base, wc](int line, int e, cplx<T> x) {
         if (line < wc) st32(base, (unsigned)(line * L + e), x);
     };
-    __syncthreads();  // twiddles
+    __syncthreads();  // twiddles; the plane before has left buf
     line_fft_io<T, L, INV, W, LS, NTHR, false, false, false>(buf, tws, tid, gload, gstore);
+    }
 }
 
 // z pass fused with the solve: block = (kx, WZ consecutive ky), all three
@@ -501,12 +580,13 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw) {
 // the Crank-Nicolson (c0 = N rho/dt, c1 = N eta/2) or steady (c0 = 0,
 // c1 = N eta) divide, N = L^3 folding in the inverse normalisation.  The
 // mean mode is set from float64 sums: mean(v) + (dt/rho) mean(f), or zero.
-template <typename T, int L>
+// ACT: planes with act[z] = 0 hold no force and are taken as zero, unread.
+template <typename T, int L, bool ACT>
 __global__ void __launch_bounds__((Geo<T, L>::TZ))
 k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
           const cplx<T>* __restrict__ dsym, const T* __restrict__ d2, T c0, T c1,
           int zero_mean_mode, const double* __restrict__ psum, int per_c, double mv,
-          double mf) {
+          double mf, const unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, W = G::WZ, NTHR = G::TZ, LS = G::LS;
     constexpr int NLN = 3 * W;
@@ -528,6 +608,9 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     A += (size_t)box * 3 * L * NC * L;
     psum += (size_t)box * 3 * per_c * 2;  // per_c partials per component
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
+    __shared__ unsigned char on[ACT ? L : 1];
+    if constexpr (ACT)
+        for (int i = tid; i < L; i += NTHR) on[i] = act[(size_t)box * L + i];
     if (kx == 0 && ch == 0) {
         // the three components' sums together: every load of a round before
         // its adds, one reduction (each wave's sums through LDS)
@@ -562,8 +645,10 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     // unsigned 32-bit offsets from the block's column base (the spectrum of
     // one box is below 4 GiB)
     cplx<T>* Ak = A + (size_t)kx * L + ky0;
-    auto gload = [Ak](int line, int z) {
+    const unsigned char* onz = on;
+    auto gload = [Ak, onz](int line, int z) {
         const int c = line / W, w = line - (line / W) * W;
+        if (ACT && !onz[z]) return cplx<T>{T(0), T(0)};
         return ld32(Ak, (unsigned)((c * L + z) * NC * L + w));
     };
     auto gstore = [Ak](int line, int z, cplx<T> x) {
@@ -613,7 +698,7 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 template <typename T, int L>
 __global__ void __launch_bounds__((Geo<T, L>::TXI))
 k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
-        T* __restrict__ vout) {
+        T* __restrict__ vout, unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::RI, NL = G::NLI, NTHR = G::TXI, LS = G::LS;
     constexpr int SS = NC + 1;  // staging row stride
@@ -624,6 +709,8 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     const int yb = blockIdx.x % (L / R);
     const int cz = blockIdx.x / (L / R);  // (box * 3 + c) * L + z
     const int y0 = yb * R;
+    if (act && tid == 0 && yb == 0 && cz / L % 3 == 0)
+        act[(size_t)(cz / (3 * L)) * L + cz % L] = 0;  // for the next binning
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     const cplx<T>* in = A + (size_t)cz * NC * L + y0;
     {
@@ -687,7 +774,7 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 template <typename T, int L>
 __global__ void __launch_bounds__((Geo<T, L>::TXY))
 k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
-         T* __restrict__ vout) {
+         T* __restrict__ vout, unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
     constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = G::TXY;
     __shared__ cplx<T> buf[L * PS];
@@ -695,6 +782,8 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     __shared__ cplx<T> twh[H];
     const int tid = threadIdx.x;
     const int cz = blockIdx.x;  // (box * 3 + c) * L + z
+    if (act && tid == 0 && cz / L % 3 == 0)
+        act[(size_t)(cz / (3 * L)) * L + cz % L] = 0;  // for the next binning
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     for (int i = tid; i < H; i += NTHR) twh[i] = tw[2 * i];
     // stage the half spectrum: F[kx][ky] at row ky, column kx (0..H)
@@ -768,46 +857,70 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 }
 
 template <typename T, int L>
-hipError_t solve_sized(mb_grid* g, const T* v_in, const T* f, bool boxed, T* v_out,
+hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_out,
                        hipStream_t s) {
     using G = Geo<T, L>;
     const bool steady = g->d.mode == MB_STEADY_STOKES;
+    const bool rhs = steady || F.rhs_only;  // the force alone is transformed
     const double h = g->d.h;
     const double N = (double)g->N;
     cplx<T>* A = (cplx<T>*)g->d_spec;
     const cplx<T>* tw = (const cplx<T>*)g->d_tw;
-    const T a = steady ? T(0) : (T)(g->d.rho / g->d.dt);
-    const T b = steady ? T(0) : (T)(0.5 * g->d.eta / (h * h));
-    const T* fin = boxed ? (const T*)g->d_box : f;
+    const T a = rhs ? T(0) : (T)(g->d.rho / g->d.dt);
+    const T b = rhs ? T(0) : (T)(0.5 * g->d.eta / (h * h));
+    const T* fin = F.boxed ? (const T*)g->d_box : F.f;
     const int nbox = g->tiles.nbox;
-#define MB_XF(BX, ST)                                                                     \
-    MB_LAUNCH(g, K_FFT_X_FWD, s, (k_x_fwd<T, L, BX, ST>), G::NBX * nbox, G::TX, 0, v_in, fin, \
-              g->btiles, tw, a, b, A, g->d_psum)
-    if (boxed) {
-        if (steady) MB_XF(true, true);
-        else MB_XF(true, false);
+    ForceSrc<T> mk{};
+    if (F.boxed) {
+        mk.add = F.f;
+        if (F.masked_mbox > 0 && !mk.add) {
+            mk.rec = (const RecG<T>*)g->d_rec;
+            mk.mbox = F.masked_mbox;
+            if (steady) mk.act = g->d_act;
+        }
+    }
+    unsigned char* act = mk.act ? g->d_act : nullptr;
+#define MB_XF(SR, ST)                                                                     \
+    MB_LAUNCH(g, K_FFT_X_FWD, s, (k_x_fwd<T, L, SR, ST>),                             \
+              (act ? G::NBX / 8 : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
+              g->btiles, mk, tw, a, b, A, g->d_psum)
+    if (!F.boxed) {
+        if (rhs) MB_XF(SRC_FIELD, true);
+        else MB_XF(SRC_FIELD, false);
+    } else if (mk.add) {
+        if (rhs) MB_XF(SRC_BOX_ADD, true);
+        else MB_XF(SRC_BOX_ADD, false);
+    } else if (mk.rec) {
+        if (rhs) MB_XF(SRC_MASKED, true);
+        else MB_XF(SRC_MASKED, false);
     } else {
-        if (steady) MB_XF(false, true);
-        else MB_XF(false, false);
+        if (rhs) MB_XF(SRC_BOX, true);
+        else MB_XF(SRC_BOX, false);
     }
 #undef MB_XF
-    MB_LAUNCH(g, K_FFT_Y_FWD, s, (k_y<T, L, false>), 3 * L * G::NCHY * nbox, G::TY, 0, A,
-              tw);
+    MB_LAUNCH(g, K_FFT_Y_FWD, s, (k_y<T, L, false>), 3 * (act ? L / 8 : L) * G::NCHY * nbox,
+              G::TY, 0, A,
+              tw, (const unsigned char*)act);
     const T c0 = steady ? T(0) : (T)(g->d.rho / g->d.dt * N);
     const T c1 = steady ? (T)(g->d.eta * N) : (T)(0.5 * g->d.eta * N);
-    const double mv = steady ? 0.0 : 1.0 / N;
+    const double mv = rhs ? 0.0 : 1.0 / N;
     const double mf = steady ? 0.0 : g->d.dt / g->d.rho / N;
     const int zm = (steady || g->d.zero_mean) ? 1 : 0;
-    MB_LAUNCH(g, K_FFT_Z_SPECTRAL, s, (k_z_solve<T, L>), G::NC * (L / G::WZ) * nbox, G::TZ, 0,
-              A, tw, (const cplx<T>*)g->d_dsym, (const T*)g->d_d2, c0, c1, zm,
-              g->d_psum, G::NBX / 3, mv, mf);
+#define MB_Z(AC)                                                                          \
+    MB_LAUNCH(g, K_FFT_Z_SPECTRAL, s, (k_z_solve<T, L, AC>), G::NC * (L / G::WZ) * nbox,   \
+              G::TZ, 0, A, tw, (const cplx<T>*)g->d_dsym, (const T*)g->d_d2, c0, c1, zm,   \
+              g->d_psum, G::NBX / 3, mv, mf, (const unsigned char*)act)
+    if (act) MB_Z(true);
+    else MB_Z(false);
+#undef MB_Z
     if constexpr (G::XY) {
         MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L>), G::NBXY * nbox, G::TXY, 0, A, tw,
-                  v_out);
+                  v_out, act);
     } else {
         MB_LAUNCH(g, K_FFT_Y_INV, s, (k_y<T, L, true>), 3 * L * G::NCHY * nbox, G::TY, 0, A,
-                  tw);
-        MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A, tw, v_out);
+                  tw, (const unsigned char*)nullptr);
+        MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A,
+                  tw, v_out, act);
     }
     return hipGetLastError();
 }
@@ -821,11 +934,11 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const T* f, bool boxed, T* v_o
 #endif
 
 template <typename T>
-hipError_t fluid_solve(mb_grid* g, const T* v_in, const T* f, T* v_out,
-                       hipStream_t s, bool boxed) {
+hipError_t fluid_solve(mb_grid* g, const T* v_in, const SolveForce<T>& force, T* v_out,
+                       hipStream_t s) {
     switch (g->L) {
 #define MB_CASE(n) \
-    case n: return fft::solve_sized<T, n>(g, v_in, f, boxed, v_out, s);
+    case n: return fft::solve_sized<T, n>(g, v_in, force, v_out, s);
         MB_FFT_SIZES(MB_CASE)
 #undef MB_CASE
     }
@@ -842,7 +955,7 @@ int fft_x_blocks(int L, int precision) {
     return 0;
 }
 
-template hipError_t fluid_solve<float>(mb_grid*, const float*, const float*, float*, hipStream_t, bool);
-template hipError_t fluid_solve<double>(mb_grid*, const double*, const double*, double*, hipStream_t, bool);
+template hipError_t fluid_solve<float>(mb_grid*, const float*, const SolveForce<float>&, float*, hipStream_t);
+template hipError_t fluid_solve<double>(mb_grid*, const double*, const SolveForce<double>&, double*, hipStream_t);
 
 }  // namespace mb

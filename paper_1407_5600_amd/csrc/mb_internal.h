@@ -124,6 +124,8 @@ struct mb_grid {
     void* d_d2;         // |D symbol|^2 per mode index (T)
     void* d_spec;       // [3][L(z)][NC(kx)][L(ky)] cplx<T>
     int nblk_x;         // blocks of an x pass
+    unsigned char* d_act;  // [nbox][L] z planes holding a force: set by the binning of a
+                           // masked steady solve, cleared by its last pass
     double* d_psum;     // [nblk_x][2] per-block sums of v and f (float64)
     // binning (by tile)
     int* d_count;       // [tiles] (kept zeroed between uses)
@@ -134,6 +136,7 @@ struct mb_grid {
     int* d_rank;        // [max_blobs] place among its tile's blobs
     int* d_perm;        // [max_blobs] blob of each sorted record
     int64_t perm_m;     // d_perm is a permutation of [0, perm_m) (-1: none)
+    bool binned_small;  // the last binning was by box (small_boxes)
     void* d_rec;        // [max_blobs] records
     size_t rec_size;
     mb::Tiles tiles;       // binning, spreading and interpolation tiles
@@ -143,7 +146,6 @@ struct mb_grid {
     double* d_adj;         // reverse-step scratch (allocated on first use)
     double* d_adj_part;    // per-block k / r0 derivative sums (deterministic)
     size_t adj_part_cap;   // doubles in d_adj_part
-    void* d_ffield;        // force field of forced steps (allocated on first use)
     double* d_mid;         // midpoint scheme: q* and a velocity per blob (first use)
     int scheme;            // mb_scheme of the steps
     double* d_tile_part;   // [tiles][4]  (sum v_a, max |Dv|)
@@ -195,11 +197,26 @@ hipError_t zero_words(void* p, size_t n, hipStream_t s);
 template <typename T>
 hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s,
                      bool counted = false, bool scan = true);
-// Records of the binned blobs with forces F scaled by fscale (h^-3 when
-// fscale <= 0: a force density).
+// Binning and records of the blobs at q with forces F (nullable: none) scaled
+// by fscale (h^-3 when fscale <= 0: a force density); with Fsum the forces
+// are F2 + f2scale F (F2 nullable), also stored there.
 template <typename T>
-hipError_t scatter_records(mb_grid* g, int64_t M, const double* q,
-                           const double* F, hipStream_t s, double fscale = 0.0);
+hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, hipStream_t s,
+                       double fscale = 0.0, const double* F2 = nullptr, double f2scale = 0.0,
+                       double* Fsum = nullptr);
+// Boxes of so few blobs (and tiles) that one block bins a box in LDS, and
+// whose interpolation gathers from the field directly; with sp also the box's
+// particles have to fit a block of the springs kernels.  Independent of the
+// number of boxes, so that a batch steps as its boxes would alone.
+constexpr int kSmallBlobs = 256;
+constexpr int kSmallTiles = 4096;  // 16 KB of LDS counts
+bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp);
+// Springs, binning and records of small boxes; mark: also the z planes their
+// nodes lie in (d_act).
+template <typename T>
+hipError_t bin_springs(mb_grid* g, const SpringsDev& sp, int64_t P, const double* q,
+                       const double* Fext, hipStream_t s, const double* Gblob, bool force_sums,
+                       bool mark);
 // Non-finite flag of the grid's checks (null unless check_finite).
 inline int* finite_flag(mb_grid* g) { return g->d.check_finite ? g->d_flag : nullptr; }
 // Springs and records; force_sums: also the per-block sums of the blob
@@ -237,15 +254,27 @@ hipError_t blob_add(int64_t n, const double* x, double* y, hipStream_t s);
 template <typename T>
 hipError_t apply_cn(mb_grid* g, const T* x, T* y, hipStream_t s);
 // Spreading into the per-tile boxes (g->d_box), and the field from them.
+// skip_empty: the boxes of box tiles without blobs are left unwritten (for a
+// solve of the same blobs with masked boxes).
 template <typename T>
-hipError_t spread_boxes(mb_grid* g, hipStream_t s);
+hipError_t spread_boxes(mb_grid* g, hipStream_t s, bool skip_empty = false);
 template <typename T>
-hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s, const T* add = nullptr);
-// Fluid solve; the force is f, or the boxes of the last spreading when
-// boxed is set (f unused).
+hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s);
+// Force of a fluid solve: the field f (boxed false), or the boxes of the last
+// spreading, plus the field f where it is not null.  masked_mbox > 0 (f
+// null): that many blobs per box, whose records (of the last binning) tell
+// which boxes were written (spread_boxes with skip_empty).  rhs_only: the explicit half
+// is left out (v_in = 0, unread).
 template <typename T>
-hipError_t fluid_solve(mb_grid* g, const T* v_in, const T* f, T* v_out,
-                       hipStream_t s, bool boxed = false);
+struct SolveForce {
+    const T* f = nullptr;
+    bool boxed = false;
+    int masked_mbox = 0;
+    bool rhs_only = false;
+};
+template <typename T>
+hipError_t fluid_solve(mb_grid* g, const T* v_in, const SolveForce<T>& force, T* v_out,
+                       hipStream_t s);
 // Elements of the box array: 3 components x tiles x (tx+3)(ty+3)(tz+3).
 size_t box_elems(const Tiles& t);
 // Interpolation of v at the binned blobs (u_out, q_update += dt u, both

@@ -18,20 +18,6 @@
 
 namespace mb {
 
-// Sorted-blob records, in two arrays.  The geometry record holds the
-// position's fraction of its cell per axis, s = x/h - floor(x/h) in [0, 1),
-// and the packed cell: bits 0-8 x, 9-17 y, 18-26 z, 27-29 the "rounds up"
-// bit per axis (s >= 1/2).  The kernel offset of the cell-centred node set
-// is t = s - bit (nearest node c + bit), that of the component's own,
-// half-cell shifted set t = s - 1/2 (nearest node c); rec_t forms them.
-// The force record (F h^-3 per component, [pos][3]) is a separate array:
-// the interpolation reads only the geometry.
-template <typename T>
-struct __align__(16) RecG {
-    T s[3];
-    uint32_t cell;
-};
-
 // Kernel offset of a record for velocity component a along axis b.
 template <typename T>
 __device__ __forceinline__ T rec_t(const RecG<T>& r, int a, int b) {
@@ -356,8 +342,8 @@ k_bin_scatter(const double* __restrict__ q, const double* __restrict__ F,
     write_record<T>(rec, F ? recf : nullptr, perm, pos, i, g, f, inv_vol);
 }
 
-// Spring forces of the sp.ppb particles of a block (float64), in two
-// parts.  springs_stage loads the blob positions and the incidence lists
+// Spring forces of the (at most sp.ppb) particles [p0, p0 + npart) of a
+// block (float64), in two parts.  springs_stage loads the blob positions and the incidence lists
 // into LDS (and each blob's external force, its share Fext_p / nb of its
 // particle's force plus its own G_i, into registers); springs_forces then has thread j (< nblob) sum over the pairs
 // incident to its blob the pair force on it, k (|d| - r0) d / |d| with
@@ -372,6 +358,12 @@ struct SpringsBlk {
     int* adj;      // [nb + 1] incidence starts, then [2 np] (pair << 8 | other)
 };
 
+// Particles of a block of the kernels that deal them out sp.ppb at a time.
+__device__ __forceinline__ int springs_npart(const SpringsDev& sp, int64_t P) {
+    const int64_t left = P - (int64_t)blockIdx.x * sp.ppb;
+    return (int)(left < sp.ppb ? left : sp.ppb);
+}
+
 // after_loads runs once the position loads are issued (more loads of the
 // caller, in flight with them).
 template <typename AfterLoads = NoOp>
@@ -379,13 +371,13 @@ __device__ __forceinline__ SpringsBlk springs_stage(const SpringsDev& sp,
                                                     const double* __restrict__ q,
                                                     const double* __restrict__ Fext,
                                                     const double* __restrict__ Gblob,
-                                                    int64_t P, double* smem,
+                                                    int64_t p0, int npart, double* smem,
                                                     double fe[3], double r0scale,
                                                     AfterLoads after_loads = NoOp{}) {
     SpringsBlk B;
     const int nb = sp.nb, np = sp.npairs;
-    B.p0 = (int64_t)blockIdx.x * sp.ppb;
-    B.npart = (int)(P - B.p0 < sp.ppb ? P - B.p0 : sp.ppb);
+    B.p0 = p0;
+    B.npart = npart;
     B.nblob = B.npart * nb;
     B.qs = smem;
     B.r0s = smem + 3 * sp.ppb * nb;
@@ -533,7 +525,7 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
     double fe[3];
     // the block's positions are requested before the tile's offset, which
     // waits for the tile; both arrive while the block stages its positions
-    const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, P, smem, fe, sp.k,
+    const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, p0, springs_npart(sp, P), smem, fe, sp.k,
                                        [&] { if (scan_n == 0) off = offs[tl]; });
     double F[3];
     int64_t i;
@@ -566,13 +558,136 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
     }
 }
 
+// Small boxes (BoxBin, small_boxes): one block bins all blobs of a box, in
+// LDS, and writes their records and the offsets of the box's tiles, whose
+// records start at box * mbox whatever the other boxes hold.  No counting and
+// scan kernels and no wait between blocks: a chain of one launch instead of
+// three (two in a stream under no capture) for boxes whose few blobs leave
+// each of them latency bound (one particle in 32^3: count 2.4 + springs 8.2
+// us; a captured step of 32 64^3 boxes of two particles: 4.4 + 7.7 + 4.3 +
+// 5.1 us).  SPRINGS: the forces are the springs and external forces, as
+// k_springs_scatter; else F (nullable: no forces; with F2 the force is F2 +
+// f2scale F, also stored to Fsum).  act (nullable): marks the z planes of the
+// box that hold nodes of its blobs.
+struct BoxBin {
+    int n;       // tiles per box
+    int mbox;    // blobs per box
+    int64_t M;
+    int* offs;
+    unsigned char* act;
+};
+
+template <typename T, bool SPRINGS>
+__global__ void __launch_bounds__(BLK)
+k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
+          const double* __restrict__ Fext, const double* __restrict__ Gblob, double f2scale,
+          double* __restrict__ Fsum, double inv_h, int L, double inv_vol,
+          RecG<T>* __restrict__ rec, T* __restrict__ recf, int* __restrict__ perm,
+          double* __restrict__ fpart, int* __restrict__ flag) {
+    extern __shared__ double smem[];
+    __shared__ double red[16 * 3];
+    int* wsum = reinterpret_cast<int*>(red);
+    int* hist = reinterpret_cast<int*>(smem);  // [n], before the springs' staging
+    double* rest = smem + (bb.n + 1) / 2;
+    const int tid = threadIdx.x, box = blockIdx.x;
+    const int64_t i0 = (int64_t)box * bb.mbox;
+    const bool own = tid < bb.mbox;
+    for (int i = tid; i < bb.n; i += BLK) hist[i] = 0;
+    double F[3] = {0.0, 0.0, 0.0}, x[3];
+    if constexpr (SPRINGS) {
+        double fe[3];
+        const int npart = bb.mbox / sp.nb;
+        const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, (int64_t)box * npart, npart, rest,
+                                           fe, sp.k);
+        int64_t ib;
+        springs_forces<sizeof(T) == 4 ? 1 : 2>(sp, B, fe, F, &ib);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) x[b] = B.qs[own ? 3 * tid + b : 0];
+    } else {
+        const int64_t i = i0 + (own ? tid : 0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) x[b] = q[3 * i + b];
+        // (Fext: the forces F; Gblob: F2)
+        if (Fext)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) F[b] = Fext[3 * i + b];
+        if (Fsum) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                F[b] = (Gblob ? Gblob[3 * i + b] : 0.0) + f2scale * F[b];
+                if (own) Fsum[3 * i + b] = F[b];
+            }
+        }
+        __syncthreads();  // the cleared counts
+    }
+    const Geom g = blob_geom(x, 0, inv_h, L);
+    const int t = tile_linear(g.c, tl);
+    int r = 0;
+    if (own) {
+        r = atomicAdd(&hist[t], 1);
+        if (bb.act) {
+            unsigned char* ab = bb.act + (size_t)box * L;
+            for (int o = -1; o <= 2; ++o) {
+                int z = g.c[2] + o;
+                z += z < 0 ? L : 0;
+                z -= z >= L ? L : 0;
+                ab[z] = 1;
+            }
+        }
+        if (flag && (nonfinite(x, 3) | nonfinite(F, 3))) atomicOr(flag, 1);
+    }
+    __syncthreads();
+    // exclusive scan of the counts: thread t sums K consecutive ones, then
+    // the wave and the waves before
+    const int K = (bb.n + BLK - 1) / BLK;
+    const int lane = tid % WAVE, wave = tid / WAVE;
+    int sum = 0;
+    for (int j = 0; j < K; ++j) sum += tid * K + j < bb.n ? hist[tid * K + j] : 0;
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    if (lane == WAVE - 1) wsum[wave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < wave; ++w) run += wsum[w];
+    for (int j = 0; j < K; ++j) {
+        const int e = tid * K + j;
+        if (e < bb.n) {
+            const int c = hist[e];
+            hist[e] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < bb.n; i += BLK)
+        bb.offs[(size_t)box * bb.n + i] = (int)i0 + hist[i];
+    if (box == (int)gridDim.x - 1 && tid == 0) bb.offs[(size_t)gridDim.x * bb.n] = (int)bb.M;
+    if (own) {
+        const bool forces = SPRINGS || Fext;
+        write_record<T>(rec, forces ? recf : nullptr, perm, i0 + hist[t] + r, i0 + tid, g, F,
+                        inv_vol);
+    }
+    if (fpart) {
+        double tot[3] = {own ? F[0] : 0.0, own ? F[1] : 0.0, own ? F[2] : 0.0};
+        block_reduce3(tot, red);
+        if (tid == 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) fpart[3 * box + c] = tot[c];
+        }
+    }
+}
+
 __global__ void __launch_bounds__(BLK)
 k_springs(SpringsDev sp, const double* __restrict__ q,
           const double* __restrict__ Fext, const double* __restrict__ Gblob, int64_t P,
           double* __restrict__ Fout) {
     extern __shared__ double smem[];
     double fe[3];
-    const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, P, smem, fe, sp.k);
+    const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, (int64_t)blockIdx.x * sp.ppb,
+                                       springs_npart(sp, P), smem, fe, sp.k);
     double F[3];
     int64_t i;
     springs_forces(sp, B, fe, F, &i);
@@ -603,7 +718,8 @@ k_springs_adjoint(SpringsDev sp, const double* __restrict__ q,
     extern __shared__ double smem[];
     __shared__ double red[16];
     double fe[3];
-    const SpringsBlk B = springs_stage(sp, q, nullptr, nullptr, P, smem, fe, 1.0);
+    const SpringsBlk B = springs_stage(sp, q, nullptr, nullptr, (int64_t)blockIdx.x * sp.ppb,
+                                       springs_npart(sp, P), smem, fe, 1.0);
     // Fbar of the block's blobs and the per-pair sums after the positions
     double* fb = B.qs + 3 * sp.ppb * sp.nb + sp.npairs + 
                  (sp.nb + 1 + 2 * sp.npairs + 1) / 2;
@@ -763,10 +879,9 @@ struct TileBox {
     int gt;    // tile over the batch: box * tiles per box + tile
 };
 
-// Block -> (box, tile): the blocks of a box are consecutive; within a box
+// Block b -> (box, tile): the blocks of a box are consecutive; within a box
 // the XCD-aware remap gives each XCD a contiguous range of tiles.
-__device__ __forceinline__ TileBox tile_box(const Tiles& t, int L) {
-    const int b = blockIdx.x;
+__device__ __forceinline__ TileBox tile_box(const Tiles& t, int L, int b) {
     TileBox tb;
     tb.box = b / t.n;
     int local = b - tb.box * t.n;
@@ -811,7 +926,7 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
 // Spreading: one block per box tile (FX x FY x FZ binning tiles, btl), one
 // velocity component at a time, or, on a grid of three rows, one block per
 // box tile and component (spread_boxes); a box tile without records only
-// writes zeros.  The box tile's own records (those of its
+// writes zeros, or nothing where the x pass masks such boxes (skip_empty).  The box tile's own records (those of its
 // cells) add all 27 of their contributions to an LDS box of the nodes they
 // can reach, [lo-1, lo+T+1] per axis, so no record is read by more than one
 // block and no contribution is masked.  The box is written to the box
@@ -837,46 +952,72 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
 // Threads of a spreading block covering f binning tiles: up to 1024 for
 // float32 fields, 512 for float64 ones (whose ~80 registers per thread
 // would otherwise leave room for one block per CU, not two).
-template <typename T>
+// SMALL: boxes binned by box hold at most 256 records, one per thread of a
+// block of 256; float32 then needs the 32-bit sums alone (27 KB of LDS), so
+// that the many blocks of box tiles without records pass quickly.
+template <typename T, bool SMALL>
 constexpr int spread_threads(int f) {
+    if (SMALL) return BLK;
     const int cap = sizeof(T) == 4 ? 1024 : 512;
     return f * BLK < cap ? f * BLK : cap;
 }
 
-template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ>
-__global__ void __launch_bounds__(spread_threads<T>(FX * FY * FZ))
+constexpr int SPREAD_RUN = 8;
+
+template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ, bool SMALL>
+__global__ void __launch_bounds__((spread_threads<T, SMALL>(FX * FY * FZ)))
 k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
          const int* __restrict__ offs, int L, Tiles btl, Tiles tl, int det,
-         T* __restrict__ E) {
-    constexpr int NT = spread_threads<T>(FX * FY * FZ);
+         int skip_empty, T* __restrict__ E) {
+    constexpr int NT = spread_threads<T, SMALL>(FX * FY * FZ);
     const int comp = gridDim.y == 3 ? (int)blockIdx.y : -1;  // one component, or all
     constexpr int NR = FX * FY * FZ;  // binning tiles of this box tile
     constexpr int EX = TX + 3, EY = TY + 3, EZ = TZ + 3;
     constexpr int EV = EX * EY * EZ;
     constexpr bool F32 = std::is_same<T, float>::value;
-    __shared__ unsigned long long acc[EV];
+    constexpr bool ONLY32 = F32 && SMALL;
+    constexpr int AV = ONLY32 ? (EV + 1) / 2 : EV;  // 64-bit words
+    __shared__ unsigned long long acc[AV];
     __shared__ double red[16];
     unsigned int* acc32 = reinterpret_cast<unsigned int*>(acc);
     double* accd = reinterpret_cast<double*>(acc);
-    const TileBox tb = tile_box(btl, L);
-    const int tile = tb.tile;
-    // the records of this box tile: its binning tiles are numbered
+    // skip_empty (SMALL): a block takes SPREAD_RUN box tiles in turn, most of
+    // them empty: the launch is bound by the number of blocks (32 boxes of
+    // 64^3, 26 blobs each: 6,144 blocks of one box tile and component, 21 us)
+    const int run = SMALL && skip_empty ? SPREAD_RUN : 1;
+    // the records of box tile bt: its binning tiles are numbered
     // consecutively (box-tile major), so their records form one range
-    int first, total;
-    {
-        const int tc[3] = {tb.lo[0] / tl.tx, tb.lo[1] / tl.ty, tb.lo[2] / tl.tz};
-        const int g = tb.box * tl.n + tile_index(tc, tl);  // its first binning tile
+    auto records = [&](const TileBox& b, int& first, int& total) {
+        const int tc[3] = {b.lo[0] / tl.tx, b.lo[1] / tl.ty, b.lo[2] / tl.tz};
+        const int g = b.box * tl.n + tile_index(tc, tl);  // its first binning tile
         first = offs[g];
         total = offs[g + NR] - first;
+    };
+    unsigned todo = 1u;
+    if (SMALL && run > 1) {  // which of the run hold records, read at once
+        todo = 0u;
+#pragma unroll
+        for (int br = 0; br < SPREAD_RUN; ++br) {
+            const int bt = blockIdx.x * SPREAD_RUN + br, last = btl.n * btl.nbox - 1;
+            int f0, n0;
+            records(tile_box(btl, L, bt < last ? bt : last), f0, n0);
+            todo |= bt <= last && n0 > 0 ? 1u << br : 0u;
+        }
     }
+    for (; todo != 0; todo = SMALL ? todo & (todo - 1) : 0u) {
+    const int bt = blockIdx.x * run + (SMALL ? __ffs(todo) - 1 : 0);
+    const TileBox tb = tile_box(btl, L, bt);
+    const int tile = tb.tile;
+    int first, total;
+    records(tb, first, total);
     if (total == 0) {  // no records: an empty box
         for (int a = comp < 0 ? 0 : comp; a <= (comp < 0 ? 2 : comp); ++a) {
             T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
             for (int i = threadIdx.x; i < EV; i += NT) st32(Ea, (unsigned)i, T(0));
         }
-        return;
+        continue;
     }
-    for (int i = threadIdx.x; i < EV; i += NT) acc[i] = 0ull;
+    for (int i = threadIdx.x; i < AV; i += NT) acc[i] = 0ull;
     // The k-th record a thread takes is the sorted record q(k) of the box
     // tile.  For float32 fields q(k) = (k * P) mod total with P = 263 (269
     // where 263 divides total, 1 where 269 does too), a bijection since P is
@@ -916,7 +1057,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     // mode 0: the fast fixed-point form (u32 for float, u64 for double)
     int mode, e;
     if (F32) {
-        mode = total <= 2048 ? 0 : 1;
+        mode = SMALL || total <= 2048 ? 0 : 1;
         e = fixed_exponent(fmx, total, mode == 0 ? 0x1p31 : 0x1p63, 0x1p30);
     } else {
         // up to 2^20 records one 64-bit fixed-point sum (mode 0); beyond,
@@ -965,7 +1106,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         }                                                                    \
     }
             if (F32) {
-                if (mode == 0) {
+                if (ONLY32 || mode == 0) {
 #define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)__float2int_rn((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
@@ -1008,7 +1149,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
         for (int i = threadIdx.x; i < EV; i += NT) {
             T val;
-            if (F32 && mode == 0) {
+            if (ONLY32 || (F32 && mode == 0)) {
                 val = ldexpf((float)(int)acc32[i], -e);
                 acc32[i] = 0u;
             } else if (F32 || mode == 0 || (mode == 2 && pass == 0)) {
@@ -1026,14 +1167,13 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         __syncthreads();
       }
     }
+    }
 }
 
-// The field from the boxes (the spreading call of the library), plus an
-// optional field `add`.
+// The field from the boxes (the spreading call of the library).
 template <typename T>
 __global__ void __launch_bounds__(BLK)
-k_fold(const T* __restrict__ E, int L, Tiles tl, const T* __restrict__ add,
-       T* __restrict__ f) {
+k_fold(const T* __restrict__ E, int L, Tiles tl, T* __restrict__ f) {
     const int64_t N = (int64_t)L * L * L;
     const int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x;
     if (i >= 3 * N * tl.nbox) return;
@@ -1044,8 +1184,14 @@ k_fold(const T* __restrict__ E, int L, Tiles tl, const T* __restrict__ add,
     const int x = (int)(rem % L);
     const int y = (int)((rem / L) % L);
     const int z = (int)(rem / ((int64_t)L * L));
-    const T val = box_sum(E + (size_t)box * 3 * tl.n * box_volume(tl), tl, a, x, y, z);
-    f[i] = add ? val + add[i] : val;
+    f[i] = box_sum(E + (size_t)box * 3 * tl.n * box_volume(tl), tl, a, x, y, z);
+}
+
+// Sum of the three nodes of a row with their weights; the multiply-adds of
+// the interpolation are written out, so that its kernels round alike.
+template <typename T>
+__device__ __forceinline__ T row_sum(const T w[3], T a, T b, T c) {
+    return fma(w[2], c, fma(w[1], b, w[0] * a));
 }
 
 // Binning of the moved blobs for the next step, done by the interpolation
@@ -1117,7 +1263,7 @@ k_interp(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
     __shared__ double red[4 * (NT / WAVE)];
     __shared__ int lcount[27];
     __shared__ int lbase[27];
-    const TileBox tb = tile_box(tl, L);
+    const TileBox tb = tile_box(tl, L, blockIdx.x);
     const int tile = tb.gt;
     const int N = L * L * L;  // 3 L^3 < 2^31 for L <= 512
     // the tile's own records
@@ -1278,8 +1424,7 @@ k_interp(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
 #pragma unroll
                     for (int oy = 0; oy < 3; ++oy) {
                         const T* row = base + (oz * eya + oy) * EX;
-                        const T sxv = w[0][0] * row[0] + w[0][1] * row[1] + w[0][2] * row[2];
-                        acc += (w[2][oz] * w[1][oy]) * sxv;
+                        acc = fma(w[2][oz] * w[1][oy], row_sum(w[0], row[0], row[1], row[2]), acc);
                     }
                 }
                 ua[c] = uscale * (double)acc;
@@ -1470,6 +1615,60 @@ k_interp(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
     }
 }
 
+// Field offsets (elements, within a component) of the nodes i0 - 1, i0,
+// i0 + 1 of a record per axis, for component a.
+template <typename T>
+__device__ __forceinline__ void node_offsets(const RecG<T>& r, int a, int L, unsigned o[3][3]) {
+    const unsigned stride[3] = {1u, (unsigned)L, (unsigned)(L * L)};
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const int c = (int)((r.cell >> (9 * b)) & 511u);
+        const int i0 = a == b ? c : c + (int)((r.cell >> (27 + b)) & 1u);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) o[b][k] = (unsigned)wrapL(i0 - 1 + k, L) * stride[b];
+    }
+}
+
+// Interpolation for small boxes (small_boxes): thread (record, component)
+// gathers its 27 nodes straight from the field.  A tile of k_interp stages
+// three components of 19 x 11 x 11 nodes for the few records it holds, and
+// most tiles hold none: here the launch is as small as the blobs (208 blobs
+// in 64^3 float64: 6.7 us by tiles).  Arguments as k_interp.
+template <typename T>
+__global__ void __launch_bounds__(WAVE)
+k_interp_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, int L, int mbox,
+                int64_t M, const T* __restrict__ v, double* __restrict__ u_out, double uscale,
+                double* __restrict__ q, double dt) {
+    const int64_t j = (int64_t)blockIdx.x * WAVE + threadIdx.x;
+    if (j >= 3 * M) return;
+    const int64_t pos = j / 3;
+    const int a = (int)(j - 3 * pos);
+    const RecG<T> r = rec[pos];
+    const int64_t i = 3 * (int64_t)perm[pos] + a;
+    const double q0 = q ? q[i] : 0.0;
+    const T* va = v + ((size_t)(pos / mbox) * 3 + a) * ((size_t)L * L * L);
+    unsigned o[3][3];
+    node_offsets(r, a, L, o);
+    T w[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) kernel_weights<T>(rec_t(r, a, b), w[b]);
+    T acc = T(0);
+#pragma unroll
+    for (int oz = 0; oz < 3; ++oz) {
+#pragma unroll
+        for (int oy = 0; oy < 3; ++oy) {
+            const unsigned ro = o[2][oz] + o[1][oy];
+            acc = fma(w[2][oz] * w[1][oy],
+                      row_sum(w[0], ld32(va, ro + o[0][0]), ld32(va, ro + o[0][1]),
+                              ld32(va, ro + o[0][2])),
+                      acc);
+        }
+    }
+    const double u = uscale * (double)acc;
+    if (u_out) u_out[i] = u;
+    if (q) q[i] = q0 + dt * u;
+}
+
 // Position derivative of the interpolation, contracted with blob weights:
 // g_i += wscale sum_a W_{i,a} grad_{q_i} (J_i v)_a.  One block per tile as in
 // k_interp (same staged field, one component at a time); per record and
@@ -1489,7 +1688,7 @@ k_interp_grad(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
     constexpr int NR = (EY * EZ + RP - 1) / RP;
     __shared__ T vt[EV];
     __shared__ int rowoff[EY * EZ];
-    const TileBox tb = tile_box(tl, L);
+    const TileBox tb = tile_box(tl, L, blockIdx.x);
     const int tile = tb.gt;
     const int N = L * L * L;
     v += (size_t)tb.box * 3 * N;
@@ -1802,9 +2001,36 @@ static void scan_tiles(mb_grid* g, hipStream_t s) {
               (int64_t)nt, g->d_bsum, g->d_offs);
 }
 
+bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp) {
+    const int64_t mbox = M / g->tiles.nbox;
+    return M > 0 && mbox <= kSmallBlobs && g->tiles.n <= kSmallTiles &&
+           (!sp || mbox <= (int64_t)sp->ppb * sp->nb);
+}
+
+// One launch of k_bin_box over the grid's boxes (arguments as there).
+template <typename T, bool SPRINGS>
+static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M, const double* q,
+                            const double* F, const double* F2, double f2scale, double* Fsum,
+                            double fscale, double* fpart, bool mark, hipStream_t s) {
+    BoxBin bb{};
+    bb.n = g->tiles.n;
+    bb.mbox = (int)(M / g->tiles.nbox);
+    bb.M = M;
+    bb.offs = g->d_offs;
+    bb.act = mark ? g->d_act : nullptr;
+    const size_t lds = (size_t)((bb.n + 1) / 2) * sizeof(double) + (SPRINGS ? springs_lds(sp) : 0);
+    MB_LAUNCH(g, kid, s, (k_bin_box<T, SPRINGS>), g->tiles.nbox, BLK, lds, sp, bb, g->tiles, q, F,
+              F2, f2scale, Fsum, 1.0 / g->d.h, g->L, fscale, rec_geo<T>(g), rec_force<T>(g),
+              g->d_perm, fpart, finite_flag(g));
+    g->perm_m = M;
+    g->binned_small = true;
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s, bool counted,
                      bool scan) {
+    g->binned_small = false;
     if (M > 0 && !counted) {
         // the previous sorted order, when it is a permutation of these blobs
         const int* order = g->perm_m == M ? g->d_perm : nullptr;
@@ -1880,16 +2106,34 @@ hipError_t finish_call(mb_grid* g, int64_t P, int nb, bool reordered, double* q,
 }
 
 template <typename T>
-hipError_t scatter_records(mb_grid* g, int64_t M, const double* q,
-                           const double* F, hipStream_t s, double fscale) {
-    if (M == 0) return hipSuccess;
+hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, hipStream_t s,
+                       double fscale, const double* F2, double f2scale, double* Fsum) {
     const double h = g->d.h;
     const double sc = fscale > 0.0 ? fscale : 1.0 / (h * h * h);
+    if (small_boxes(g, M, nullptr))
+        return bin_boxes<T, false>(g, K_BIN_SCATTER, SpringsDev{}, M, q, F, F2, f2scale, Fsum, sc,
+                                   nullptr, false, s);
+    hipError_t e = hipSuccess;
+    if (Fsum) {
+        e = blob_axpy(3 * M, F2, f2scale, F, Fsum, s);
+        F = Fsum;
+    }
+    if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s);
+    if (e != hipSuccess || M == 0) return e;
     MB_LAUNCH(g, K_BIN_SCATTER, s, k_bin_scatter<T>, blocks_for(M), BLK, 0, q, F,
               M, 1.0 / h, g->L, sc, g->d_offs, g->d_tile, g->d_rank,
               rec_geo<T>(g), rec_force<T>(g), g->d_perm, finite_flag(g));
     g->perm_m = M;
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t bin_springs(mb_grid* g, const SpringsDev& sp, int64_t P, const double* q,
+                       const double* Fext, hipStream_t s, const double* Gblob, bool force_sums,
+                       bool mark) {
+    const double h = g->d.h;
+    return bin_boxes<T, true>(g, K_SPRINGS_SCATTER, sp, P * sp.nb, q, Fext, Gblob, 0.0, nullptr,
+                              1.0 / (h * h * h), force_sums ? g->d_force_part : nullptr, mark, s);
 }
 
 template <typename T>
@@ -1983,6 +2227,7 @@ hipError_t init_workspace(mb_grid* g, hipStream_t s) {
     if (e == hipSuccess) e = zero_words(g->d_tile_part, nt * 4 * 2, s);
     if (e == hipSuccess) e = zero_words(g->d_force_part, (size_t)g->force_blocks_cap * 3 * 2, s);
     if (e == hipSuccess) e = zero_words(g->d_flag, 2, s);
+    if (e == hipSuccess) e = zero_words(g->d_act, (size_t)g->tiles.nbox * L / 4, s);
     return e;
 }
 
@@ -2052,7 +2297,7 @@ bool tile_shape_supported(int tx, int ty, int tz) {
     X(16, 16, 8, 1, 1, 1) X(16, 8, 16, 1, 1, 1) X(8, 16, 16, 1, 1, 1)
 
 template <typename T>
-hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
+hipError_t spread_boxes(mb_grid* g, hipStream_t s, bool skip_empty) {
     const Tiles& t = g->tiles;
     const Tiles& b = g->btiles;
     bool ok = false;
@@ -2067,17 +2312,27 @@ hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
     // mixed, 32.5 -> 40.2 float64).
     constexpr int kSplitBoxTiles = 256;
     const int nbt = b.n * b.nbox;
-    const dim3 grid(nbt, nbt <= kSplitBoxTiles ? 3 : 1);
+    // (skip_empty and small kernels: boxes binned by box; few box tiles keep
+    // the larger blocks, whose phases are shorter: 64 of 64^3 float64, 208
+    // blobs, 9.0 us against 10.3)
+    const bool small = g->binned_small && nbt > 64;
+    skip_empty = skip_empty && small;
+    const dim3 grid(skip_empty ? (nbt + SPREAD_RUN - 1) / SPREAD_RUN : nbt,
+                    small || nbt <= kSplitBoxTiles ? 3 : 1);
+#define MB_BOX_K(SX, SY, SZ, FX, FY, FZ, SM)                                             \
+    MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ, SM>), grid,           \
+              (spread_threads<T, SM>(FX * FY * FZ)), 0, rec_geo<T>(g), rec_force<T>(g),  \
+              g->d_offs, g->L, b, t, g->d.deterministic, skip_empty ? 1 : 0, (T*)g->d_box)
 #define MB_BOX(SX, SY, SZ, FX, FY, FZ)                                                   \
     if (!ok && b.tx == SX && b.ty == SY && b.tz == SZ && SX == FX * t.tx &&              \
         SY == FY * t.ty && SZ == FZ * t.tz) {                                            \
-        MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ>), grid,   \
-                  spread_threads<T>(FX * FY * FZ), 0, rec_geo<T>(g), rec_force<T>(g),    \
-                  g->d_offs, g->L, b, t, g->d.deterministic, (T*)g->d_box);              \
+        if (small) MB_BOX_K(SX, SY, SZ, FX, FY, FZ, true);                               \
+        else MB_BOX_K(SX, SY, SZ, FX, FY, FZ, false);                                    \
         ok = true;                                                                       \
     }
     MB_BOX_SHAPES(MB_BOX)
 #undef MB_BOX
+#undef MB_BOX_K
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
@@ -2090,9 +2345,9 @@ bool box_shape_supported(int sx, int sy, int sz, int tx, int ty, int tz) {
 }
 
 template <typename T>
-hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s, const T* add) {
+hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s) {
     MB_LAUNCH(g, K_FOLD, s, k_fold<T>, blocks_for(3 * g->N * g->tiles.nbox), BLK, 0,
-              (const T*)g->d_box, g->L, g->btiles, add, f);
+              (const T*)g->d_box, g->L, g->btiles, f);
     return hipGetLastError();
 }
 
@@ -2100,9 +2355,14 @@ template <typename T>
 hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
                        double* q_update, int diag, hipStream_t s, double uscale,
                        bool bin_next) {
-    (void)M;
     double* part = diag ? g->d_tile_part : nullptr;
     const int kid = q_update ? K_INTERP_STEP : K_INTERP;
+    if (g->binned_small && !part) {
+        MB_LAUNCH(g, kid, s, k_interp_direct<T>, (unsigned)((3 * M + WAVE - 1) / WAVE), WAVE, 0,
+                  rec_geo<T>(g), g->d_perm, g->L, (int)(M / g->tiles.nbox), M, v, u_out, uscale,
+                  q_update, g->d.dt);
+        return hipGetLastError();
+    }
     BinNext bn{nullptr, nullptr, nullptr};
     if (bin_next && q_update) bn = BinNext{g->d_count, g->d_tile, g->d_rank};
     const bool ok = with_tile_shape(g->tiles, [&](auto X, auto Y, auto Z) {
@@ -2131,14 +2391,16 @@ hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wsca
 // Explicit instantiations.
 template hipError_t bin_blobs<float>(mb_grid*, int64_t, const double*, hipStream_t, bool, bool);
 template hipError_t bin_blobs<double>(mb_grid*, int64_t, const double*, hipStream_t, bool, bool);
-template hipError_t scatter_records<float>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double);
-template hipError_t scatter_records<double>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double);
+template hipError_t bin_records<float>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double, const double*, double, double*);
+template hipError_t bin_records<double>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double, const double*, double, double*);
+template hipError_t bin_springs<float>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
+template hipError_t bin_springs<double>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
 template hipError_t scatter_springs<float>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
 template hipError_t scatter_springs<double>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
-template hipError_t spread_boxes<float>(mb_grid*, hipStream_t);
-template hipError_t spread_boxes<double>(mb_grid*, hipStream_t);
-template hipError_t fold_boxes<float>(mb_grid*, float*, hipStream_t, const float*);
-template hipError_t fold_boxes<double>(mb_grid*, double*, hipStream_t, const double*);
+template hipError_t spread_boxes<float>(mb_grid*, hipStream_t, bool);
+template hipError_t spread_boxes<double>(mb_grid*, hipStream_t, bool);
+template hipError_t fold_boxes<float>(mb_grid*, float*, hipStream_t);
+template hipError_t fold_boxes<double>(mb_grid*, double*, hipStream_t);
 template hipError_t interpolate<float>(mb_grid*, int64_t, const float*, double*, double*, int, hipStream_t, double, bool);
 template hipError_t interpolate<double>(mb_grid*, int64_t, const double*, double*, double*, int, hipStream_t, double, bool);
 template hipError_t interpolate_grad<float>(mb_grid*, const float*, const double*, double, double*, hipStream_t);
