@@ -564,11 +564,11 @@ mb_status mb_spread(mb_grid* g, int64_t M, const double* q, const double* F,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_records<float>(g, M, q, F, s);
+        e = bin_records<float>(g, M, q, F, s, true);
         if (e == hipSuccess) e = spread_boxes<float>(g, s);
         if (e == hipSuccess) e = fold_boxes<float>(g, (float*)f_out, s);
     } else {
-        e = bin_records<double>(g, M, q, F, s);
+        e = bin_records<double>(g, M, q, F, s, true);
         if (e == hipSuccess) e = spread_boxes<double>(g, s);
         if (e == hipSuccess) e = fold_boxes<double>(g, (double*)f_out, s);
     }
@@ -587,10 +587,10 @@ mb_status mb_interpolate(mb_grid* g, int64_t M, const double* q, const void* v,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_records<float>(g, M, q, nullptr, s);
+        e = bin_records<float>(g, M, q, nullptr, s, false);
         if (e == hipSuccess) e = interpolate<float>(g, M, (const float*)v, u_out, nullptr, 0, s);
     } else {
-        e = bin_records<double>(g, M, q, nullptr, s);
+        e = bin_records<double>(g, M, q, nullptr, s, false);
         if (e == hipSuccess) e = interpolate<double>(g, M, (const double*)v, u_out, nullptr, 0, s);
     }
     return finish(g, e, s);
@@ -608,9 +608,9 @@ mb_status mb_fluid_solve(mb_grid* g, const void* v_in, const void* f,
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4)
-        e = fluid_solve<float>(g, (const float*)v_in, {(const float*)f}, (float*)v_out, s);
+        e = fluid_solve<float>(g, (const float*)v_in, {SolveForce<float>::FIELD, (const float*)f}, (float*)v_out, s);
     else
-        e = fluid_solve<double>(g, (const double*)v_in, {(const double*)f}, (double*)v_out, s);
+        e = fluid_solve<double>(g, (const double*)v_in, {SolveForce<double>::FIELD, (const double*)f}, (double*)v_out, s);
     return from_hip(e);
 }
 
@@ -627,15 +627,6 @@ mb_status mb_spring_forces(const mb_springs* sp, int64_t P, const double* q,
                                   (hipStream_t)stream, nullptr));
 }
 
-// Blobs per box where boxes without blobs are neither written by the spreading
-// nor read by the solve (small boxes, binned so), else 0.  Up to 256 box tiles
-// the whole array is cheaper than marking its boxes in every block of the x
-// pass (one 32^3 box: x pass 5.4 us, masked 9.9).
-constexpr int kMaskBoxTiles = 256;
-static int masked_blobs(const mb_grid* g, int64_t M) {
-    return g->btiles.n * g->tiles.nbox > kMaskBoxTiles ? (int)(M / g->tiles.nbox) : 0;
-}
-
 // One step of the grid's scheme on fields of type T (u_dst: blob velocities
 // of the step, or null).
 extern "C++" {
@@ -643,12 +634,12 @@ template <typename T>
 static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t M,
                             double* q, T* v, const double* Fext, const double* Gblob,
                             const T* ffluid, double* u_dst, hipStream_t s,
-                            bool binned = false, bool bin_next = false, bool diag = true) {
-    // few blobs per box: binned by box, and boxes without any neither written
-    // nor read
+                            bool binned = false, bool bin_next = false, bool diag = true,
+                            bool field_out = true) {
+    // few blobs per box: binned by box, their force formed in the solve
     const bool small = small_boxes(g, M, &sd);
-    const int masked = small && !ffluid ? masked_blobs(g, M) : 0;
-    const bool mark = masked > 0 && g->d.mode == MB_STEADY_STOKES;
+    const bool mark = small && !ffluid && g->d.mode == MB_STEADY_STOKES;
+    const bool planes = mark && !field_out;
     // forces at positions x, spread into the boxes; binned: the counts of q are in place;
     // sums: the force sums of the diagnostics.  The diagnostics' partial
     // sums (forces, momentum, max |Dv|) are formed only when diag is set
@@ -656,22 +647,31 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
     auto forces = [&](const double* x, bool counted, bool sums) {
         hipError_t e;
         if (small) {
-            e = bin_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, mark);
+            e = bin_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, sums, mark);
         } else {
             const bool fuse = fused_scan_ok(g, s);  // the scan in the springs kernel
             e = bin_blobs<T>(g, M, x, s, counted, !fuse);
             if (e == hipSuccess) e = scatter_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, fuse);
+            if (e == hipSuccess) e = spread_boxes<T>(g, s);
         }
-        if (e == hipSuccess) e = spread_boxes<T>(g, s, masked > 0);
         return e;
     };
-    auto solve = [&]() { return fluid_solve<T>(g, v, {ffluid, true, masked, false}, v, s); };
+    auto solve = [&](bool part) {
+        SolveForce<T> F;
+        F.src = small ? SolveForce<T>::RECORDS : SolveForce<T>::BOXES;
+        F.f = ffluid;
+        F.mbox = (int)(M / g->tiles.nbox);
+        F.planes = mark;
+        F.planes_out = part;
+        return fluid_solve<T>(g, v, F, v, s);
+    };
     hipError_t e;
     const int dg = diag ? 1 : 0;
     if (g->scheme == MB_SCHEME_EULER) {
         e = forces(q, binned, diag);
-        if (e == hipSuccess) e = solve();
-        if (e == hipSuccess) e = interpolate<T>(g, M, v, u_dst, q, dg, s, 1.0, bin_next);
+        if (e == hipSuccess) e = solve(planes);
+        if (e == hipSuccess)
+            e = interpolate<T>(g, M, v, u_dst, q, dg, s, 1.0, bin_next, planes);
         return e;
     }
     // midpoint predictor-corrector: q* in d_mid, the second half of the
@@ -682,20 +682,22 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
     if (g->d.mode == MB_STEADY_STOKES) {
         // q* += (dt/2) J(q^n) v(q^n);  q += dt J(q*) v(q*)
         if (e == hipSuccess) e = forces(q, false, false);
-        if (e == hipSuccess) e = solve();
-        if (e == hipSuccess) e = interpolate<T>(g, M, v, nullptr, qs, 0, s, 0.5);
+        // (the field at q^n is read by this interpolation alone)
+        if (e == hipSuccess) e = solve(mark);
+        if (e == hipSuccess)
+            e = interpolate<T>(g, M, v, nullptr, qs, 0, s, 0.5, false, mark);
         if (e == hipSuccess) e = forces(qs, false, diag);
-        if (e == hipSuccess) e = solve();
-        if (e == hipSuccess) e = interpolate<T>(g, M, v, u_dst, q, dg, s);
+        if (e == hipSuccess) e = solve(planes);
+        if (e == hipSuccess) e = interpolate<T>(g, M, v, u_dst, q, dg, s, 1.0, false, planes);
         return e;
     }
     // q* += (dt/2) J(q^n) v^n on the records of q^n
-    if (e == hipSuccess) e = bin_records<T>(g, M, q, nullptr, s);
+    if (e == hipSuccess) e = bin_records<T>(g, M, q, nullptr, s, false);
     if (e == hipSuccess) e = interpolate<T>(g, M, v, nullptr, qs, 0, s, 0.5);
     // forces at q*; q += (dt/2) J(q*) v^n; solve; q += (dt/2) J(q*) v^{n+1}
     if (e == hipSuccess) e = forces(qs, false, diag);
     if (e == hipSuccess) e = interpolate<T>(g, M, v, u_dst, q, 0, s, 0.5);
-    if (e == hipSuccess) e = solve();
+    if (e == hipSuccess) e = solve(false);
     if (e == hipSuccess) e = interpolate<T>(g, M, v, u_dst ? u2 : nullptr, q, dg, s, 0.5);
     if (e == hipSuccess && u_dst) e = blob_add(3 * M, u2, u_dst, s);
     return e;
@@ -706,12 +708,15 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
 constexpr int kReorderMinSteps = 8;
 
 // Steps of one grid; check: report the non-finite flag at the end (false
-// inside a graph capture, where the caller checks after the replays).
+// inside a graph capture, where the caller checks after the replays);
+// field_out: the field of the last step is the caller's (false: more steps
+// follow that overwrite it, and in steady flow only what the interpolation
+// reads of it need be formed).
 static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* q,
                            void* v, const double* Fext, const double* Gblob,
                            double* u_out, double* U0_out, double* diag_out,
                            int32_t nsteps, void* stream, const void* ffluid = nullptr,
-                           bool check = true) {
+                           bool check = true, bool field_out = true) {
     if (!g || !sp || !v || P < 0 || nsteps < 0) return MB_ERR_INVALID;
     const int64_t M = P * sp->nb;
     if (M > g->d.max_blobs) return MB_ERR_INVALID;
@@ -766,10 +771,11 @@ static mb_status step_impl(mb_grid* g, const mb_springs* sp, int64_t P, double* 
         const bool diag = last && diag_out;  // partial sums only where they are read
         if (g->fsz == 4)
             e = step_once<float>(g, sd, P, M, qs, (float*)v, Fs, Gblob, (const float*)ffluid,
-                                 u_dst, s, binned, bin_next, diag);
+                                 u_dst, s, binned, bin_next, diag, last && field_out);
         else
             e = step_once<double>(g, sd, P, M, qs, (double*)v, Fs, Gblob,
-                                  (const double*)ffluid, u_dst, s, binned, bin_next, diag);
+                                  (const double*)ffluid, u_dst, s, binned, bin_next, diag,
+                                  last && field_out);
         if (!last && e != hipSuccess && bin_next)
             (void)zero_words(g->d_count, (size_t)g->tiles.n * g->tiles.nbox, s);
         u_last = u_dst;
@@ -830,11 +836,11 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     if (nsteps == 0) return MB_OK;
     // the non-finite checks of the grids that ask for them are read once,
     // after the last step
-    auto one_step = [&](hipStream_t s) -> mb_status {
+    auto one_step = [&](hipStream_t s, bool last) -> mb_status {
         for (int i = 0; i < ngrids; ++i) {
             mb_status r = step_impl(grids[i], springs[i], nparticles[i], q[i], v[i],
                                     Fext ? Fext[i] : nullptr, F_blob ? F_blob[i] : nullptr,
-                                    nullptr, nullptr, nullptr, 1, (void*)s, nullptr, false);
+                                    nullptr, nullptr, nullptr, 1, (void*)s, nullptr, false, last);
             if (r != MB_OK) return r;
         }
         return MB_OK;
@@ -855,11 +861,20 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     for (int i = 0; i < ngrids; ++i)
         if (grids[i]->perm_m != nparticles[i] * springs[i]->nb) warm = false;
     if (!warm) {
-        st = one_step(caller);
+        st = one_step(caller, nsteps == 1);
         if (st != MB_OK) return st;
         done = 1;
     }
     if (done == nsteps) return check_all(hipSuccess);
+    // steady boxes of few blobs form their whole field on the last step only:
+    // the graph holds a step before it, and the last one follows eagerly
+    bool tail = false;
+    for (int i = 0; i < ngrids; ++i) {
+        const SpringsDev sd = springs_dev(springs[i]);
+        tail = tail || (grids[i]->d.mode == MB_STEADY_STOKES &&
+                        small_boxes(grids[i], nparticles[i] * springs[i]->nb, &sd));
+    }
+    const int replays = nsteps - done - (tail ? 1 : 0);
     hipStream_t cs = nullptr;
     hipEvent_t ev = nullptr;
     hipGraph_t graph = nullptr;
@@ -873,15 +888,19 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(ev, caller);
     if (e == hipSuccess) e = hipStreamWaitEvent(cs, ev, 0);
-    if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        st = one_step(cs);
-        hipError_t ec = hipStreamEndCapture(cs, &graph);
-        if (st == MB_OK) e = ec;
+    if (replays > 0) {
+        if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+        if (e == hipSuccess) {
+            st = one_step(cs, !tail);
+            hipError_t ec = hipStreamEndCapture(cs, &graph);
+            if (st == MB_OK) e = ec;
+        }
+        if (e == hipSuccess && st == MB_OK)
+            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        for (int n = 0; n < replays && e == hipSuccess && st == MB_OK; ++n)
+            e = hipGraphLaunch(exec, cs);
     }
-    if (e == hipSuccess && st == MB_OK) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    for (int n = done; n < nsteps && e == hipSuccess && st == MB_OK; ++n)
-        e = hipGraphLaunch(exec, cs);
+    if (tail && e == hipSuccess && st == MB_OK) st = one_step(cs, true);
     if (e == hipSuccess && st == MB_OK) e = hipStreamSynchronize(cs);
     for (int i = 0; i < ngrids; ++i) grids[i]->timing = timing[i];
     if (exec) (void)hipGraphExecDestroy(exec);
@@ -919,12 +938,12 @@ mb_status mb_interpolate_grad(mb_grid* g, int64_t M, const double* q, const void
     hipStream_t s = (hipStream_t)stream;
     hipError_t e;
     if (g->fsz == 4) {
-        e = bin_records<float>(g, M, q, nullptr, s);
-        if (e == hipSuccess) e = interpolate_grad<float>(g, (const float*)v, W, 1.0, g_inout, s);
+        e = bin_records<float>(g, M, q, nullptr, s, false);
+        if (e == hipSuccess) e = interpolate_grad<float>(g, M, (const float*)v, W, 1.0, g_inout, s);
     } else {
-        e = bin_records<double>(g, M, q, nullptr, s);
+        e = bin_records<double>(g, M, q, nullptr, s, false);
         if (e == hipSuccess)
-            e = interpolate_grad<double>(g, (const double*)v, W, 1.0, g_inout, s);
+            e = interpolate_grad<double>(g, M, (const double*)v, W, 1.0, g_inout, s);
     }
     return finish(g, e, s);
 }
@@ -1003,14 +1022,21 @@ mb_status mb_step_adjoint(mb_grid* g, const mb_springs* sp, int64_t P, const dou
     double* vb = (double*)vbar;
     // q^{n+1} = q^n + dt u^n:  ubar = ubar_loss + dt qbar; records of q^n
     // carrying ubar (scale 1: h^3 S ubar = J^T ubar)
-    e = bin_records<double>(g, M, q_n, qbar, s, 1.0, ubar_loss, g->d.dt, ubar);
+    e = bin_records<double>(g, M, q_n, qbar, s, false, 1.0, ubar_loss, g->d.dt, ubar);
     // u^n = J(q^n) v^{n+1}: position part
-    if (e == hipSuccess && M > 0) e = interpolate_grad<double>(g, vn1, ubar, 1.0, qbar, s);
-    // wbar = vbar + J^T ubar: the boxes of ubar and the field vbar, summed as
-    // the solve reads them.  v^{n+1} = Q (C v^n + f^n): fbar = Q wbar, vbar =
+    if (e == hipSuccess && M > 0) e = interpolate_grad<double>(g, M, vn1, ubar, 1.0, qbar, s);
+    // wbar = vbar + J^T ubar: ubar spread and the field vbar, summed as the
+    // solve reads them.  v^{n+1} = Q (C v^n + f^n): fbar = Q wbar, vbar =
     // C Q wbar (Q and C commute; steady: vbar = 0)
-    if (e == hipSuccess) e = spread_boxes<double>(g, s);
-    if (e == hipSuccess) e = fluid_solve<double>(g, nullptr, {vb, true, 0, true}, fbar, s);
+    {
+        SolveForce<double> F;
+        F.src = g->binned_small ? SolveForce<double>::RECORDS : SolveForce<double>::BOXES;
+        F.f = vb;
+        F.mbox = (int)(M / g->tiles.nbox);
+        F.rhs_only = true;
+        if (e == hipSuccess && !g->binned_small) e = spread_boxes<double>(g, s);
+        if (e == hipSuccess) e = fluid_solve<double>(g, nullptr, F, fbar, s);
+    }
     if (e == hipSuccess) {
         if (g->d.mode == MB_STEADY_STOKES) e = zero_words(vb, nf * 2, s);
         else e = apply_cn<double>(g, fbar, vb, s);
@@ -1019,11 +1045,10 @@ mb_status mb_step_adjoint(mb_grid* g, const mb_springs* sp, int64_t P, const dou
     if (e == hipSuccess) e = spring_forces(sd, P, q_n, Fext, F, s, g, F_blob);
     // f^n = S(q^n) F^n: Fbar = h^-3 J fbar, and the position part
     if (e == hipSuccess && M > 0)
-        e = interpolate<double>(g, M, fbar, Fbar, nullptr, 0, s, 1.0 / h3);
-    if (e == hipSuccess && M > 0) e = interpolate_grad<double>(g, fbar, F, 1.0 / h3, qbar, s);
+        e = interpolate_grad<double>(g, M, fbar, F, 1.0 / h3, qbar, s, Fbar, 1.0 / h3);
     // springs: qbar, kbar, r0bar; the blob forces: Fblob_bar += Fbar
-    if (e == hipSuccess) e = springs_adjoint(sd, P, q_n, Fbar, qbar, kbar, r0bar, s, g, part);
-    if (e == hipSuccess && Fblob_bar) e = blob_add(3 * M, Fbar, Fblob_bar, s);
+    if (e == hipSuccess)
+        e = springs_adjoint(sd, P, q_n, Fbar, qbar, kbar, r0bar, s, g, part, Fblob_bar);
     return finish(g, e, s);
 }
 

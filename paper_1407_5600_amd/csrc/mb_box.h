@@ -13,11 +13,10 @@ namespace mb {
 // the node's own tile at box index l + 1 (l = v mod T), the previous tile at
 // l + T + 1 when l <= 1 and the next tile at 0 when l = T - 1 (periodic in
 // the tile index; T a power of two >= 4).  Each entry is stored as an
-// element offset: tile * tstride + box index * bstride, and its tile.
+// element offset: tile * tstride + box index * bstride.
 struct AxisSrc {
     int n;
     int off[2];
-    int t[2];
 };
 
 __device__ __forceinline__ AxisSrc axis_sources(int v, int T, int nt, int tstride,
@@ -28,15 +27,12 @@ __device__ __forceinline__ AxisSrc axis_sources(int v, int T, int nt, int tstrid
     s.n = 1;
     s.off[0] = t * tstride + (l + 1) * bstride;
     s.off[1] = 0;
-    s.t[0] = s.t[1] = t;
     if (l <= 1) {
         s.n = 2;
-        s.t[1] = t == 0 ? nt - 1 : t - 1;
-        s.off[1] = s.t[1] * tstride + (l + T + 1) * bstride;
+        s.off[1] = (t == 0 ? nt - 1 : t - 1) * tstride + (l + T + 1) * bstride;
     } else if (l == T - 1) {
         s.n = 2;
-        s.t[1] = t == nt - 1 ? 0 : t + 1;
-        s.off[1] = s.t[1] * tstride;
+        s.off[1] = (t == nt - 1 ? 0 : t + 1) * tstride;
     }
     return s;
 }
@@ -112,29 +108,6 @@ __device__ __forceinline__ void box_entries(const T* __restrict__ Ea, const Axis
             const unsigned o3 = (unsigned)(sz.off[1] + sy.off[1]);
             e[3][0] = ld32(Ea, o3 + x0);
             if (sx.n > 1) e[3][1] = ld32(Ea, o3 + x1);
-        }
-    }
-}
-// The same where only some boxes were written: bit t of occ[s][j] tells that
-// the box of x tile t, y tile j and z source s was.
-constexpr int MASK_YT = 64;  // y tiles at most (512 / 8), as x tiles
-template <typename T>
-__device__ __forceinline__ void box_entries_masked(const T* __restrict__ Ea, const AxisSrc& sx,
-                                                   const AxisSrc& sy, const AxisSrc& sz,
-                                                   const unsigned long long occ[2][MASK_YT],
-                                                   T e[4][2]) {
-    const unsigned x0 = (unsigned)sx.off[0], x1 = (unsigned)sx.off[1];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        e[k][0] = e[k][1] = T(0);
-        const int kz = k >> 1, ky = k & 1;
-        if (kz < sz.n && ky < sy.n) {
-            const unsigned long long m = occ[kz][sy.t[ky]];
-            if (m != 0) {
-                const unsigned o = (unsigned)(sz.off[kz] + sy.off[ky]);
-                if ((m >> sx.t[0]) & 1) e[k][0] = ld32(Ea, o + x0);
-                if (sx.n > 1 && ((m >> sx.t[1]) & 1)) e[k][1] = ld32(Ea, o + x1);
-            }
         }
     }
 }

@@ -53,6 +53,23 @@ struct __align__(16) RecG {
     uint32_t cell;
 };
 
+// The two record arrays in the grid's record scratch: geometry, then forces.
+template <typename T>
+inline RecG<T>* rec_geo(const mb_grid* g) {
+    return (RecG<T>*)g->d_rec;
+}
+template <typename T>
+inline T* rec_force(const mb_grid* g) {
+    const size_t cap = (size_t)(g->d.max_blobs > 1 ? g->d.max_blobs : 1);
+    return (T*)((char*)g->d_rec + cap * sizeof(RecG<T>));
+}
+
+// Kernel offset of a record for velocity component a along axis b.
+template <typename T>
+__device__ __forceinline__ T rec_t(const RecG<T>& r, int a, int b) {
+    return a == b ? r.s[b] - T(0.5) : r.s[b] - T((r.cell >> (27 + b)) & 1u);
+}
+
 // 1/sqrt(x) for a normal float64 x > 0: the hardware estimate refined by
 // two Newton steps y <- y + y (1/2 - x y^2 / 2) for the root of 1/y^2 - x,
 // each of which squares the relative error (an estimate good to 2^-14

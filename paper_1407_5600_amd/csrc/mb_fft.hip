@@ -278,18 +278,22 @@ struct Geo {
     // against 34.5)
     static constexpr int TXY_RAW = ((L * H / 8 + WAVE - 1) / WAVE) * WAVE;
     static constexpr int TXY = TXY_RAW > 1024 ? 1024 : TXY_RAW;
+    static constexpr int TXYP = TXY > 512 ? 512 : TXY;  // some planes only: a loop, no spills
     static constexpr int NBXY = 3 * L;                         // blocks per box
 };
 
 // ---------------------------------------------------------------------------
 // Force of the forward x pass: the field f; the boxes (f the box array); the
-// boxes plus a field; or boxes of which some may be unwritten.
-enum : int { SRC_FIELD, SRC_BOX, SRC_BOX_ADD, SRC_MASKED };
+// boxes plus a field; or the records of a small box.
+enum : int { SRC_FIELD, SRC_BOX, SRC_BOX_ADD, SRC_REC };
 
-// What the last two read.  add (SRC_BOX_ADD): the field added.  rec
-// (SRC_MASKED): the records of the mbox blobs of each box, from which each
-// block marks the box tiles that hold blobs.  act (SRC_MASKED in steady flow,
-// where the force is all there is): whether each z plane of each box holds any
+// What the last two read.  add: the field added (SRC_REC: nullable).  rec,
+// recf: geometry and force records of the mbox blobs of each box, from which a
+// block forms the force of its rows: the spreading writes and this pass reads
+// 1.67 values per node and a few blobs touch few of them (one particle in
+// 32^3: spreading 6.3 us; 32 boxes of 64^3 with two particles each: spreading
+// 20 us and 168 MB of mostly zero boxes).  act (SRC_REC in steady flow, where
+// the force is all there is): whether each z plane of each box holds any
 // force, as the binning marked it; the x and y passes pass over planes without
 // one and the z pass takes them as zero (two particles in 64^3 lie in about 7
 // of the 64 planes).
@@ -297,16 +301,128 @@ template <typename T>
 struct ForceSrc {
     const T* add;
     const RecG<T>* rec;
+    const T* recf;
     int mbox;
     const unsigned char* act;
 };
 
-// Bits of the nonzero ones of eight flags `stride` apart, read at once.
-__device__ __forceinline__ unsigned active_planes(const unsigned char* __restrict__ act,
-                                                  int stride) {
-    unsigned m = 0;
+// A record as the rows of one plane see it: its first nodes along x and y
+// (wrapped), the x weights, and the y weights times the z weight of the plane
+// times the force.
+template <typename T>
+struct RecLine {
+    T wx[3], wyf[3];
+    int xs, ys;
+};
+
+// The records of a box (forces recf) with nodes of component a in plane z and
+// in any of the R rows from y0, in record order, into list; returns their
+// number.  Each thread looks at one record a round (a round takes NTHR); cnt:
+// an int per wave.  Called by the whole block; ends with a barrier.
+template <typename T, int L, int R, int NTHR>
+__device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
+                                             const T* __restrict__ recf, int mbox, int a, int z,
+                                             int y0, RecLine<T>* list, int* cnt) {
+    constexpr int NW = (NTHR + WAVE - 1) / WAVE;
+    const int tid = threadIdx.x, wave = tid / WAVE;
+    int n = 0;
+    for (int b0 = 0; b0 < mbox; b0 += NTHR) {
+        const int i = b0 + tid;
+        const int ic = i < mbox ? i : 0;
+        const RecG<T> r = rec[ic];
+        const T F = recf[3 * ic + a];
+        auto first = [&](int b) {  // first node along axis b, in [0, L)
+            const int c = (int)((r.cell >> (9 * b)) & 511u) - 1;
+            const int i0 = a == b ? c : c + (int)((r.cell >> (27 + b)) & 1u);
+            return i0 < 0 ? i0 + L : (i0 >= L ? i0 - L : i0);
+        };
+        const int xs = first(0), ys = first(1);
+        int dz = z - first(2);
+        dz += dz < 0 ? L : 0;
+        int dy = ys - y0;  // first row from y0, in [0, L); L - 2, L - 1: the rows before
+        dy += dy < 0 ? L : 0;
+        const bool keep = i < mbox && dz < 3 && (dy < R || dy >= L - 2);
+        const unsigned long long m = __ballot(keep);
+        if (NW > 1) {
+            if (tid % WAVE == 0) cnt[wave] = __popcll(m);
+            __syncthreads();
+        }
+        int before = n, total = n;
+        if (NW > 1) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) m |= act[k * stride] ? 1u << k : 0u;
+            for (int w = 0; w < NW; ++w) {
+                before += w < wave ? cnt[w] : 0;
+                total += cnt[w];
+            }
+        } else {
+            total += __popcll(m);
+        }
+        if (keep) {
+            T wx[3], wy[3], wz[3];
+            kernel_weights<T>(rec_t(r, a, 0), wx);
+            kernel_weights<T>(rec_t(r, a, 1), wy);
+            kernel_weights<T>(rec_t(r, a, 2), wz);
+            T f = wz[2];  // (selected, not indexed)
+            f = dz == 1 ? wz[1] : f;
+            f = (dz == 0 ? wz[0] : f) * F;
+            RecLine<T>* e = list + before + __popcll(m & ((1ull << (tid % WAVE)) - 1));
+            e->wx[0] = wx[0];
+            e->wx[1] = wx[1];
+            e->wx[2] = wx[2];
+            e->wyf[0] = wy[0] * f;
+            e->wyf[1] = wy[1] * f;
+            e->wyf[2] = wy[2] * f;
+            e->xs = xs;
+            e->ys = ys;
+        }
+        n = total;
+        __syncthreads();
+    }
+    return n;
+}
+
+// Force of the nodes (x, y) and (x, y + 1) from the n records of a list; y0
+// the first row of the block, [rlo, rhi] the rows from y0 that the wave's lanes
+// ask for.  A wave picks the records with nodes in its rows by ballot, so that
+// the other rows of the block cost next to nothing.
+template <typename T, int L, int NTHR>
+__device__ __forceinline__ void list_force(const RecLine<T>* list, int n, int x, int y, int y0,
+                                           int rlo, int rhi, T out[2]) {
+    T f0 = T(0), f1 = T(0);
+    const int left = NTHR - (int)(threadIdx.x - threadIdx.x % WAVE);
+    const int cw = NTHR % WAVE == 0 || left >= WAVE ? WAVE : left;  // the wave's lanes
+    for (int k0 = 0; k0 < n; k0 += cw) {
+        const int i = k0 + (int)(threadIdx.x % WAVE);
+        int d = list[i < n ? i : 0].ys - y0;  // its first row from y0, in [0, L)
+        d += d < 0 ? L : 0;
+        unsigned long long m =
+            __ballot(i < n && ((d <= rhi && d + 2 >= rlo) || d - L + 2 >= rlo));
+        for (; m != 0; m &= m - 1) {
+            const RecLine<T>* e = list + k0 + (__ffsll(m) - 1);
+            int dx = x - e->xs, dy = y - e->ys;
+            dx += dx < 0 ? L : 0;
+            dy += dy < 0 ? L : 0;
+            const int dy1 = dy == L - 1 ? 0 : dy + 1;
+            if (dx < 3) {
+                const T w = e->wx[dx];
+                if (dy < 3) f0 = fma(w, e->wyf[dy], f0);
+                if (dy1 < 3) f1 = fma(w, e->wyf[dy1], f1);
+            }
+        }
+    }
+    out[0] = f0;
+    out[1] = f1;
+}
+
+// Planes of a box with marks act, dealt out to blocks eight apart (zi + 8 k:
+// the planes of a few particles, neighbours, fall to different blocks, and few
+// blocks find nothing to do): bit k of plane zi + 8 k, read at once.
+template <int L>
+__device__ __forceinline__ unsigned long long active_planes(const unsigned char* __restrict__ act,
+                                                            int zi) {
+    unsigned long long m = 0;
+#pragma unroll
+    for (int k = 0; k < L / 8; ++k) m |= act[zi + 8 * k] ? 1ull << k : 0ull;
     return m;
 }
 
@@ -315,8 +431,8 @@ __global__ void __launch_bounds__((Geo<T, L>::TX))
 k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> mk,
         const cplx<T>* __restrict__ tw, T a, T b,
         cplx<T>* __restrict__ A, double* __restrict__ psum) {
-    constexpr bool BOX = SRC != SRC_FIELD;
-    constexpr bool MASKED = SRC == SRC_MASKED;
+    constexpr bool BOX = SRC == SRC_BOX || SRC == SRC_BOX_ADD;
+    constexpr bool REC = SRC == SRC_REC;
     constexpr bool ADD = SRC == SRC_BOX_ADD;
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::R, NL = G::NL, NTHR = G::TX, LS = G::LS;
@@ -328,16 +444,14 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     // within a box each XCD takes a contiguous range of (c, z, y) rows, so
     // the rows of the Laplacian's z and y neighbours, read by adjacent
     // blocks, are found in that XCD's L2
-    // with act a block takes the planes zi + k L/8 of which few hold a force:
-    // the planes of a few particles, neighbours, fall to different blocks,
-    // and an eighth of the blocks finds nothing to do
-    constexpr bool ACT = MASKED && STEADY;
+    // with act a block takes the planes of active_planes
+    constexpr bool ACT = REC && STEADY;
     const bool planes = ACT && mk.act;
-    const int per_box = planes ? G::NBX / 8 : G::NBX;
+    const int per_box = planes ? G::NBX / (L / 8) : G::NBX;
     const int box = blockIdx.x / per_box;
     const int lb = planes ? blockIdx.x - box * per_box : xcd_remap(blockIdx.x - box * per_box, G::NBX);
     const int yb = lb % (L / R);
-    const int nz = planes ? L / 8 : L;
+    const int nz = planes ? 8 : L;
     const int comp = lb / (L / R) / nz;
     const int z_first = lb / (L / R) % nz;
     const int cbase = comp * L * L * L;   // component offset (elements)
@@ -345,10 +459,11 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     v += (size_t)box * 3 * L * L * L;
     A += (size_t)box * 3 * L * NC * L;
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
-    if (!BOX) f += (size_t)box * 3 * L * L * L;
-    unsigned todo = planes ? active_planes(mk.act + (size_t)box * L + z_first, L / 8) : 1u;
-    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0u) {
-    const int z = z_first + (ACT ? (__ffs(todo) - 1) * (L / 8) : 0);
+    if (SRC == SRC_FIELD) f += (size_t)box * 3 * L * L * L;
+    unsigned long long todo = 1;
+    if (planes) todo = active_planes<L>(mk.act + (size_t)box * L, z_first);
+    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
+    const int z = z_first + (ACT ? 8 * (__ffsll(todo) - 1) : 0);
     const int cz = comp * L + z;
     double sv = 0.0, sf = 0.0;
     const int zm = (z == 0 ? L - 1 : z - 1), zp = (z == L - 1 ? 0 : z + 1);
@@ -359,21 +474,14 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
         Ec = f + ((size_t)box * 3 + comp) * tl.n * box_volume(tl);
         bz = box_src_z(tl, z);
     }
-    [[maybe_unused]] const T* add = ADD ? mk.add + (size_t)box * 3 * L * L * L : nullptr;
-    __shared__ unsigned long long occ[MASKED ? 2 : 1][MASKED ? MASK_YT : 1];
-    if constexpr (MASKED) {
-        for (int i = tid; i < 2 * MASK_YT; i += NTHR) (&occ[0][0])[i] = 0ull;
-        __syncthreads();
-        const int sx = __ffs(tl.tx) - 1, sy = __ffs(tl.ty) - 1, sz = __ffs(tl.tz) - 1;
-        for (int i = tid; i < mk.mbox; i += NTHR) {
-            const uint32_t cell = mk.rec[(size_t)box * mk.mbox + i].cell;
-            const unsigned long long bit = 1ull << ((cell & 511u) >> sx);
-            const int ty = (int)((cell >> 9) & 511u) >> sy;
-            const int tz = (int)((cell >> 18) & 511u) >> sz;
-            if (tz == bz.t[0]) atomicOr(&occ[0][ty], bit);
-            if (bz.n > 1 && tz == bz.t[1]) atomicOr(&occ[1][ty], bit);
-        }
-        __syncthreads();
+    [[maybe_unused]] const T* add =
+        (ADD || REC) && mk.add ? mk.add + (size_t)box * 3 * L * L * L : nullptr;
+    __shared__ RecLine<T> list[REC ? kSmallBlobs : 1];
+    int nlist = 0;
+    if constexpr (REC) {
+        const size_t b0 = (size_t)box * mk.mbox;
+        nlist = plane_records<T, L, R, NTHR>(mk.rec + b0, mk.recf + 3 * b0, mk.mbox, comp, z, y0,
+                                             list, reinterpret_cast<int*>(red));
     }
     // KG iterations (2 KG nodes) per round: all loads of a round, the box
     // entries included (box_entries: loads only, in uniform branches), are
@@ -410,8 +518,10 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
             for (int hh = 0; hh < 2; ++hh) {
                 const int y = y0 + 2 * line + hh;
                 const int row = cbase + (z * L + y) * L;
-                if (!BOX) fv[0][hh] = at(fb, row, ox);
+                if (SRC == SRC_FIELD) fv[0][hh] = at(fb, row, ox);
                 if constexpr (ADD) fv[0][hh] = at(reinterpret_cast<const char*>(add), row, ox);
+                if constexpr (REC)
+                    fv[0][hh] = add ? at(reinterpret_cast<const char*>(add), row, ox) : T(0);
                 if (!STEADY) {
                     const int ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
                     vc[0][hh] = at(vb, row, ox);
@@ -427,8 +537,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) {
                     const AxisSrc by = box_src_y(tl, y0 + 2 * line + hh);
-                    if constexpr (MASKED) box_entries_masked(Ec, bxu, by, bz, occ, eb[0][hh]);
-                    else box_entries(Ec, bxu, by, bz, eb[0][hh]);
+                    box_entries(Ec, bxu, by, bz, eb[0][hh]);
                 }
             }
         } else {
@@ -442,8 +551,9 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
             for (int hh = 0; hh < 2; ++hh) {
                 const int y = y0 + 2 * line + hh;
                 const unsigned row = (unsigned)(cbase + (z * L + y) * L);
-                if (!BOX) fv[g][hh] = ld32(f, row + x);
+                if (SRC == SRC_FIELD) fv[g][hh] = ld32(f, row + x);
                 if constexpr (ADD) fv[g][hh] = ld32(add, row + x);
+                if constexpr (REC) fv[g][hh] = add ? ld32(add, row + x) : T(0);
                 if (!STEADY) {
                     const int ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
                     vc[g][hh] = ld32(v, row + x);
@@ -461,10 +571,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
                 for (int hh = 0; hh < 2; ++hh) {
                     const int y = y0 + 2 * line + hh;
                     const int yu = UNI ? __builtin_amdgcn_readfirstlane(y) : y;
-                    if constexpr (MASKED)
-                        box_entries_masked(Ec, bx, box_src_y(tl, yu), bz, occ, eb[g][hh]);
-                    else
-                        box_entries(Ec, bx, box_src_y(tl, yu), bz, eb[g][hh]);
+                    box_entries(Ec, bx, box_src_y(tl, yu), bz, eb[g][hh]);
                 }
             }
         }
@@ -475,8 +582,16 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
             const int line = e / L;
             const int x = e - line * L;
             T val[2];
+            [[maybe_unused]] T lf[2];
+            if constexpr (REC) {
+                const int w0 = __builtin_amdgcn_readfirstlane(e);  // the wave's first element
+                const int w1 = w0 + WAVE - 1 < NL * L - 1 ? w0 + WAVE - 1 : NL * L - 1;
+                list_force<T, L, NTHR>(list, nlist, x, y0 + 2 * line, y0, 2 * (w0 / L),
+                                       2 * (w1 / L) + 1, lf);
+            }
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
+                if (REC) fv[g][hh] = lf[hh] + fv[g][hh];
                 if (ADD) fv[g][hh] = box_entries_sum(eb[g][hh]) + fv[g][hh];
                 else if (BOX) fv[g][hh] = box_entries_sum(eb[g][hh]);
                 sf += (double)fv[g][hh];
@@ -548,13 +663,14 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     const int ch = blockIdx.x % G::NCHY;
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     // act (nullable): planes without force are neither read nor written; a
-    // block then takes the planes zi + k L/8, as the x pass
-    const int nz = act ? L / 8 : L;
+    // block then takes the planes of active_planes
+    const int nz = act ? 8 : L;
     const int bc = blockIdx.x / G::NCHY / nz;  // box * 3 + c
     const int z0 = blockIdx.x / G::NCHY % nz;
-    unsigned todo = act ? active_planes(act + (size_t)(bc / 3) * L + z0, L / 8) : 1u;
+    unsigned long long todo = 1;
+    if (act) todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0);
     for (; todo != 0; todo &= todo - 1) {
-    const int z = z0 + (__ffs(todo) - 1) * (L / 8);
+    const int z = z0 + 8 * (__ffsll(todo) - 1);
     const int cz = bc * L + z;
     const int kx0 = ch * W;
     const int wc = NC - kx0 < W ? NC - kx0 : W;
@@ -580,13 +696,14 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // the Crank-Nicolson (c0 = N rho/dt, c1 = N eta/2) or steady (c0 = 0,
 // c1 = N eta) divide, N = L^3 folding in the inverse normalisation.  The
 // mean mode is set from float64 sums: mean(v) + (dt/rho) mean(f), or zero.
-// ACT: planes with act[z] = 0 hold no force and are taken as zero, unread.
+// ACT: planes with act[z] = 0 hold no force and are taken as zero, unread;
+// with part_out they are not written either.
 template <typename T, int L, bool ACT>
 __global__ void __launch_bounds__((Geo<T, L>::TZ))
 k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
           const cplx<T>* __restrict__ dsym, const T* __restrict__ d2, T c0, T c1,
           int zero_mean_mode, const double* __restrict__ psum, int per_c, double mv,
-          double mf, const unsigned char* __restrict__ act) {
+          double mf, const unsigned char* __restrict__ act, int part_out) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, W = G::WZ, NTHR = G::TZ, LS = G::LS;
     constexpr int NLN = 3 * W;
@@ -651,8 +768,9 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
         if (ACT && !onz[z]) return cplx<T>{T(0), T(0)};
         return ld32(Ak, (unsigned)((c * L + z) * NC * L + w));
     };
-    auto gstore = [Ak](int line, int z, cplx<T> x) {
+    auto gstore = [Ak, onz, part_out](int line, int z, cplx<T> x) {
         const int c = line / W, w = line - (line / W) * W;
+        if (ACT && part_out && !onz[z]) return;
         st32(Ak, (unsigned)((c * L + z) * NC * L + w), x);
     };
     cplx<T>* lb = buf;
@@ -698,7 +816,7 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 template <typename T, int L>
 __global__ void __launch_bounds__((Geo<T, L>::TXI))
 k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
-        T* __restrict__ vout, unsigned char* __restrict__ act) {
+        T* __restrict__ vout, unsigned char* __restrict__ act, int part_out) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::RI, NL = G::NLI, NTHR = G::TXI, LS = G::LS;
     constexpr int SS = NC + 1;  // staging row stride
@@ -709,8 +827,14 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     const int yb = blockIdx.x % (L / R);
     const int cz = blockIdx.x / (L / R);  // (box * 3 + c) * L + z
     const int y0 = yb * R;
-    if (act && tid == 0 && yb == 0 && cz / L % 3 == 0)
-        act[(size_t)(cz / (3 * L)) * L + cz % L] = 0;  // for the next binning
+    if (act) {
+        unsigned char* pa = act + (size_t)(cz / (3 * L)) * L + cz % L;
+        if (part_out) {
+            if (!*pa) return;
+        } else if (tid == 0 && yb == 0 && cz / L % 3 == 0) {
+            *pa = 0;  // for the next binning
+        }
+    }
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     const cplx<T>* in = A + (size_t)cz * NC * L + y0;
     {
@@ -770,22 +894,32 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // for a real plane), then inverse transforms along y (L points) and j
 // (H points); Z[y][j] is the row pair (v[y][2j], v[y][2j+1]), unnormalised
 // like the rest of the solve.  Element (row, column) of the plane sits at
-// row * PS + lpad(column).
-template <typename T, int L>
-__global__ void __launch_bounds__((Geo<T, L>::TXY))
+// row * PS + lpad(column).  PLANES: only the planes with act are
+// produced (a block takes those of active_planes); else act
+// (nullable) is cleared.
+template <typename T, int L, bool PLANES>
+__global__ void __launch_bounds__((PLANES ? Geo<T, L>::TXYP : Geo<T, L>::TXY))
 k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
          T* __restrict__ vout, unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
-    constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = G::TXY;
+    constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = PLANES ? G::TXYP : G::TXY;
     __shared__ cplx<T> buf[L * PS];
     __shared__ cplx<T> tws[L];
     __shared__ cplx<T> twh[H];
     const int tid = threadIdx.x;
-    const int cz = blockIdx.x;  // (box * 3 + c) * L + z
-    if (act && tid == 0 && cz / L % 3 == 0)
-        act[(size_t)(cz / (3 * L)) * L + cz % L] = 0;  // for the next binning
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     for (int i = tid; i < H; i += NTHR) twh[i] = tw[2 * i];
+    constexpr int nz = PLANES ? 8 : L;
+    const int bc = blockIdx.x / nz, z0 = blockIdx.x % nz;  // box * 3 + c
+    unsigned long long todo = 1;
+    if (PLANES) {
+        todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0);
+    } else if (act && tid == 0 && bc % 3 == 0) {
+        act[(size_t)(bc / 3) * L + z0] = 0;  // for the next binning
+    }
+    for (; todo != 0; todo = PLANES ? todo & (todo - 1) : 0) {
+    const int cz = PLANES ? bc * L + z0 + 8 * (__ffsll(todo) - 1)  // (box * 3 + c) * L + z
+                          : (int)blockIdx.x;
     // stage the half spectrum: F[kx][ky] at row ky, column kx (0..H)
     const cplx<T>* in = A + (size_t)cz * NC * L;
     {
@@ -854,6 +988,8 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     auto ldl = [lb](int line, int e) { return lb[line * PS + lpad(e)]; };
     auto gst = [out](int line, int e, cplx<T> x) { st32(out, (unsigned)(line * H + e), x); };
     line_fft_io<T, H, true, L, PS, NTHR, false, true, false>(buf, twh, tid, ldl, gst);
+    if (PLANES) __syncthreads();  // (another plane in buf)
+    }
 }
 
 template <typename T, int L>
@@ -868,37 +1004,40 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     const cplx<T>* tw = (const cplx<T>*)g->d_tw;
     const T a = rhs ? T(0) : (T)(g->d.rho / g->d.dt);
     const T b = rhs ? T(0) : (T)(0.5 * g->d.eta / (h * h));
-    const T* fin = F.boxed ? (const T*)g->d_box : F.f;
     const int nbox = g->tiles.nbox;
     ForceSrc<T> mk{};
-    if (F.boxed) {
+    const T* fin = F.f;
+    if (F.src != SolveForce<T>::FIELD) {
+        fin = (const T*)g->d_box;
         mk.add = F.f;
-        if (F.masked_mbox > 0 && !mk.add) {
-            mk.rec = (const RecG<T>*)g->d_rec;
-            mk.mbox = F.masked_mbox;
-            if (steady) mk.act = g->d_act;
-        }
+    }
+    if (F.src == SolveForce<T>::RECORDS) {
+        mk.rec = rec_geo<T>(g);
+        mk.recf = rec_force<T>(g);
+        mk.mbox = F.mbox;
+        if (F.planes) mk.act = g->d_act;
     }
     unsigned char* act = mk.act ? g->d_act : nullptr;
+    const int part = F.planes && F.planes_out ? 1 : 0;
 #define MB_XF(SR, ST)                                                                     \
     MB_LAUNCH(g, K_FFT_X_FWD, s, (k_x_fwd<T, L, SR, ST>),                             \
-              (act ? G::NBX / 8 : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
+              (act ? G::NBX / (L / 8) : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
               g->btiles, mk, tw, a, b, A, g->d_psum)
-    if (!F.boxed) {
+    if (F.src == SolveForce<T>::FIELD) {
         if (rhs) MB_XF(SRC_FIELD, true);
         else MB_XF(SRC_FIELD, false);
+    } else if (F.src == SolveForce<T>::RECORDS) {
+        if (rhs) MB_XF(SRC_REC, true);
+        else MB_XF(SRC_REC, false);
     } else if (mk.add) {
         if (rhs) MB_XF(SRC_BOX_ADD, true);
         else MB_XF(SRC_BOX_ADD, false);
-    } else if (mk.rec) {
-        if (rhs) MB_XF(SRC_MASKED, true);
-        else MB_XF(SRC_MASKED, false);
     } else {
         if (rhs) MB_XF(SRC_BOX, true);
         else MB_XF(SRC_BOX, false);
     }
 #undef MB_XF
-    MB_LAUNCH(g, K_FFT_Y_FWD, s, (k_y<T, L, false>), 3 * (act ? L / 8 : L) * G::NCHY * nbox,
+    MB_LAUNCH(g, K_FFT_Y_FWD, s, (k_y<T, L, false>), 3 * (act ? 8 : L) * G::NCHY * nbox,
               G::TY, 0, A,
               tw, (const unsigned char*)act);
     const T c0 = steady ? T(0) : (T)(g->d.rho / g->d.dt * N);
@@ -909,18 +1048,22 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
 #define MB_Z(AC)                                                                          \
     MB_LAUNCH(g, K_FFT_Z_SPECTRAL, s, (k_z_solve<T, L, AC>), G::NC * (L / G::WZ) * nbox,   \
               G::TZ, 0, A, tw, (const cplx<T>*)g->d_dsym, (const T*)g->d_d2, c0, c1, zm,   \
-              g->d_psum, G::NBX / 3, mv, mf, (const unsigned char*)act)
+              g->d_psum, G::NBX / 3, mv, mf, (const unsigned char*)act, part)
     if (act) MB_Z(true);
     else MB_Z(false);
 #undef MB_Z
     if constexpr (G::XY) {
-        MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L>), G::NBXY * nbox, G::TXY, 0, A, tw,
-                  v_out, act);
+        if (part)
+            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * 8 * nbox, G::TXYP,
+                      0, A, tw, v_out, act);
+        else
+            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, false>), G::NBXY * nbox, G::TXY, 0, A,
+                      tw, v_out, act);
     } else {
-        MB_LAUNCH(g, K_FFT_Y_INV, s, (k_y<T, L, true>), 3 * L * G::NCHY * nbox, G::TY, 0, A,
-                  tw, (const unsigned char*)nullptr);
+        MB_LAUNCH(g, K_FFT_Y_INV, s, (k_y<T, L, true>), 3 * (part ? 8 : L) * G::NCHY * nbox,
+                  G::TY, 0, A, tw, (const unsigned char*)(part ? act : nullptr));
         MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A,
-                  tw, v_out, act);
+                  tw, v_out, act, part);
     }
     return hipGetLastError();
 }

@@ -197,26 +197,29 @@ hipError_t zero_words(void* p, size_t n, hipStream_t s);
 template <typename T>
 hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s,
                      bool counted = false, bool scan = true);
-// Binning and records of the blobs at q with forces F (nullable: none) scaled
+// Binning and records of the blobs at q (tiles false: records of small boxes
+// need not be by tile) with forces F (nullable: none) scaled
 // by fscale (h^-3 when fscale <= 0: a force density); with Fsum the forces
 // are F2 + f2scale F (F2 nullable), also stored there.
 template <typename T>
 hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, hipStream_t s,
-                       double fscale = 0.0, const double* F2 = nullptr, double f2scale = 0.0,
+                       bool tiles, double fscale = 0.0, const double* F2 = nullptr, double f2scale = 0.0,
                        double* Fsum = nullptr);
-// Boxes of so few blobs (and tiles) that one block bins a box in LDS, and
-// whose interpolation gathers from the field directly; with sp also the box's
+// Boxes of so few blobs (and tiles) that one block bins a box in LDS, the
+// solve forms their force from the records without spreading, and the
+// interpolation gathers from the field directly; with sp also the box's
 // particles have to fit a block of the springs kernels.  Independent of the
 // number of boxes, so that a batch steps as its boxes would alone.
 constexpr int kSmallBlobs = 256;
 constexpr int kSmallTiles = 4096;  // 16 KB of LDS counts
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp);
-// Springs, binning and records of small boxes; mark: also the z planes their
-// nodes lie in (d_act).
+// Springs and records of small boxes, with tiles by tile (for the spreading and
+// the interpolation that forms sums over the tiles); mark: also the z planes
+// their nodes lie in (d_act).
 template <typename T>
 hipError_t bin_springs(mb_grid* g, const SpringsDev& sp, int64_t P, const double* q,
                        const double* Fext, hipStream_t s, const double* Gblob, bool force_sums,
-                       bool mark);
+                       bool tiles, bool mark);
 // Non-finite flag of the grid's checks (null unless check_finite).
 inline int* finite_flag(mb_grid* g) { return g->d.check_finite ? g->d_flag : nullptr; }
 // Springs and records; force_sums: also the per-block sums of the blob
@@ -238,11 +241,11 @@ hipError_t spring_forces(const SpringsDev& sp, int64_t P, const double* q,
                          const double* Fext, double* F, hipStream_t s,
                          mb_grid* timing_grid, const double* Gblob = nullptr);
 // qbar += (dF/dq)^T Fbar; kbar, r0bar (nullable) accumulate the k and rest
-// length parts.
+// length parts; fsum (nullable) += Fbar.
 hipError_t springs_adjoint(const SpringsDev& sp, int64_t P, const double* q,
                            const double* Fbar, double* qbar, double* kbar,
                            double* r0bar, hipStream_t s, mb_grid* timing_grid,
-                           double* part = nullptr);
+                           double* part = nullptr, double* fsum = nullptr);
 // Doubles of per-block partial sums springs_adjoint writes to `part`
 // (then summed in block order) instead of its float64 atomics.
 size_t springs_adjoint_part_size(const SpringsDev& sp, int64_t P);
@@ -254,23 +257,29 @@ hipError_t blob_add(int64_t n, const double* x, double* y, hipStream_t s);
 template <typename T>
 hipError_t apply_cn(mb_grid* g, const T* x, T* y, hipStream_t s);
 // Spreading into the per-tile boxes (g->d_box), and the field from them.
-// skip_empty: the boxes of box tiles without blobs are left unwritten (for a
-// solve of the same blobs with masked boxes).
 template <typename T>
-hipError_t spread_boxes(mb_grid* g, hipStream_t s, bool skip_empty = false);
+hipError_t spread_boxes(mb_grid* g, hipStream_t s);
 template <typename T>
 hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s);
-// Force of a fluid solve: the field f (boxed false), or the boxes of the last
-// spreading, plus the field f where it is not null.  masked_mbox > 0 (f
-// null): that many blobs per box, whose records (of the last binning) tell
-// which boxes were written (spread_boxes with skip_empty).  rhs_only: the explicit half
-// is left out (v_in = 0, unread).
+// Force of a fluid solve.
 template <typename T>
 struct SolveForce {
+    enum Src { FIELD, BOXES, RECORDS };
+    Src src = FIELD;
+    // FIELD: the force density.  Else (nullable) a force density added to the
+    // blobs', which is the sum of the boxes of the last spreading, or (small
+    // boxes, mbox blobs each) formed from the records of the last binning.
     const T* f = nullptr;
-    bool boxed = false;
-    int masked_mbox = 0;
+    int mbox = 0;
+    // the explicit half is left out (v_in = 0, unread)
     bool rhs_only = false;
+    // RECORDS in steady flow without f: the binning marked the z planes that
+    // hold nodes of the blobs, and the transforms pass over the others
+    bool planes = false;
+    // with planes: only these are written to v_out, for a field that is
+    // interpolated at those blobs and then overwritten; the interpolation
+    // then clears the marks (else the solve does)
+    bool planes_out = false;
 };
 template <typename T>
 hipError_t fluid_solve(mb_grid* g, const T* v_in, const SolveForce<T>& force, T* v_out,
@@ -279,15 +288,18 @@ hipError_t fluid_solve(mb_grid* g, const T* v_in, const SolveForce<T>& force, T*
 size_t box_elems(const Tiles& t);
 // Interpolation of v at the binned blobs (u_out, q_update += dt u, both
 // nullable; diag: per-tile partial sums); bin_next (with q_update): also
-// bin the moved blobs into the counts of the next binning.
+// bin the moved blobs into the counts of the next binning; clear_planes
+// (small boxes): after a solve with planes_out.
 template <typename T>
 hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
                        double* q_update, int diag, hipStream_t s, double uscale = 1.0,
-                       bool bin_next = false);
-// gout += wscale sum_a W_a grad_q (J v)_a per blob, on the binned records.
+                       bool bin_next = false, bool clear_planes = false);
+// gout += wscale sum_a W_a grad_q (J v)_a per blob, on the binned records;
+// u_out (nullable): also uscale J v.
 template <typename T>
-hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wscale,
-                            double* gout, hipStream_t s);
+hipError_t interpolate_grad(mb_grid* g, int64_t M, const T* v, const double* W, double wscale,
+                            double* gout, hipStream_t s, double* u_out = nullptr,
+                            double uscale = 1.0);
 // Particle order of a step call: particles counting-sorted by the tile of
 // their last blob (the centre of the icosahedral template) into d_order
 // (internal particle -> caller's particle), and the positions q and forces

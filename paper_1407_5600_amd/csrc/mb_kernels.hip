@@ -18,12 +18,6 @@
 
 namespace mb {
 
-// Kernel offset of a record for velocity component a along axis b.
-template <typename T>
-__device__ __forceinline__ T rec_t(const RecG<T>& r, int a, int b) {
-    return a == b ? r.s[b] - T(0.5) : r.s[b] - T((r.cell >> (27 + b)) & 1u);
-}
-
 constexpr int BLK = 256;
 
 struct Geom {
@@ -558,17 +552,17 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
     }
 }
 
-// Small boxes (BoxBin, small_boxes): one block bins all blobs of a box, in
-// LDS, and writes their records and the offsets of the box's tiles, whose
-// records start at box * mbox whatever the other boxes hold.  No counting and
-// scan kernels and no wait between blocks: a chain of one launch instead of
-// three (two in a stream under no capture) for boxes whose few blobs leave
-// each of them latency bound (one particle in 32^3: count 2.4 + springs 8.2
-// us; a captured step of 32 64^3 boxes of two particles: 4.4 + 7.7 + 4.3 +
-// 5.1 us).  SPRINGS: the forces are the springs and external forces, as
-// k_springs_scatter; else F (nullable: no forces; with F2 the force is F2 +
-// f2scale F, also stored to Fsum).  act (nullable): marks the z planes of the
-// box that hold nodes of its blobs.
+// Small boxes (BoxBin, small_boxes): one block takes all blobs of a box and
+// writes their records, which start at box * mbox whatever the other boxes
+// hold: in blob order, or (offs not null) by tile, binned in LDS with the
+// offsets of the box's tiles written.  No counting and scan kernels and no
+// wait between blocks: a chain of one launch instead of two or three for
+// boxes whose few blobs leave each of them latency bound (one particle in
+// 32^3: count 2.4 + springs 8.2 us; a captured step of 32 64^3 boxes of two
+// particles: 4.4 + 7.7 + 4.3 + 5.1 us).  SPRINGS: the forces are the springs
+// and external forces, as k_springs_scatter; else F (nullable: no forces; with
+// Fsum the force is F2 + f2scale F, also stored there).  act (nullable): marks
+// the z planes of the box that hold nodes of its blobs.
 struct BoxBin {
     int n;       // tiles per box
     int mbox;    // blobs per box
@@ -588,11 +582,13 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
     __shared__ double red[16 * 3];
     int* wsum = reinterpret_cast<int*>(red);
     int* hist = reinterpret_cast<int*>(smem);  // [n], before the springs' staging
-    double* rest = smem + (bb.n + 1) / 2;
+    double* rest = smem + (bb.offs ? (bb.n + 1) / 2 : 0);
     const int tid = threadIdx.x, box = blockIdx.x;
     const int64_t i0 = (int64_t)box * bb.mbox;
     const bool own = tid < bb.mbox;
-    for (int i = tid; i < bb.n; i += BLK) hist[i] = 0;
+    const bool sort = bb.offs != nullptr;
+    if (sort)
+        for (int i = tid; i < bb.n; i += BLK) hist[i] = 0;
     double F[3] = {0.0, 0.0, 0.0}, x[3];
     if constexpr (SPRINGS) {
         double fe[3];
@@ -622,9 +618,7 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
     }
     const Geom g = blob_geom(x, 0, inv_h, L);
     const int t = tile_linear(g.c, tl);
-    int r = 0;
     if (own) {
-        r = atomicAdd(&hist[t], 1);
         if (bb.act) {
             unsigned char* ab = bb.act + (size_t)box * L;
             for (int o = -1; o <= 2; ++o) {
@@ -636,40 +630,55 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
         }
         if (flag && (nonfinite(x, 3) | nonfinite(F, 3))) atomicOr(flag, 1);
     }
-    __syncthreads();
-    // exclusive scan of the counts: thread t sums K consecutive ones, then
-    // the wave and the waves before
-    const int K = (bb.n + BLK - 1) / BLK;
-    const int lane = tid % WAVE, wave = tid / WAVE;
-    int sum = 0;
-    for (int j = 0; j < K; ++j) sum += tid * K + j < bb.n ? hist[tid * K + j] : 0;
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == WAVE - 1) wsum[wave] = incl;
-    __syncthreads();
-    int run = incl - sum;
-    for (int w = 0; w < wave; ++w) run += wsum[w];
-    for (int j = 0; j < K; ++j) {
-        const int e = tid * K + j;
-        if (e < bb.n) {
-            const int c = hist[e];
-            hist[e] = run;
-            run += c;
+    int64_t pos = i0 + tid;
+    if (sort) {  // (uniform over the grid)
+        // rank: the blobs before this one in its tile, so that the order of
+        // the records depends on the positions alone (the x pass sums in it)
+        __shared__ __align__(16) int tiles_of[BLK];
+        tiles_of[tid] = own ? t : -1;
+        if (own) atomicAdd(&hist[t], 1);
+        __syncthreads();
+        int r = 0;
+#pragma unroll 8
+        for (int j = 0; j < bb.mbox; j += 4) {  // (the same four in every lane)
+            const int4 o = *reinterpret_cast<const int4*>(tiles_of + j);
+            r += (j < tid && o.x == t) + (j + 1 < tid && o.y == t) +
+                 (j + 2 < tid && o.z == t) + (j + 3 < tid && o.w == t);
         }
+        // exclusive scan of the counts: thread t sums K consecutive ones, then
+        // the wave and the waves before
+        const int K = (bb.n + BLK - 1) / BLK;
+        const int lane = tid % WAVE, wave = tid / WAVE;
+        int sum = 0;
+        for (int j = 0; j < K; ++j) sum += tid * K + j < bb.n ? hist[tid * K + j] : 0;
+        int incl = sum;
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const int y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        if (lane == WAVE - 1) wsum[wave] = incl;
+        __syncthreads();
+        int run = incl - sum;
+        for (int w = 0; w < wave; ++w) run += wsum[w];
+        for (int j = 0; j < K; ++j) {
+            const int e = tid * K + j;
+            if (e < bb.n) {
+                const int c = hist[e];
+                hist[e] = run;
+                run += c;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < bb.n; i += BLK)
+            bb.offs[(size_t)box * bb.n + i] = (int)i0 + hist[i];
+        if (box == (int)gridDim.x - 1 && tid == 0)
+            bb.offs[(size_t)gridDim.x * bb.n] = (int)bb.M;
+        pos = i0 + hist[t] + r;
+        __syncthreads();  // wsum (red) is used again below
     }
-    __syncthreads();
-    for (int i = tid; i < bb.n; i += BLK)
-        bb.offs[(size_t)box * bb.n + i] = (int)i0 + hist[i];
-    if (box == (int)gridDim.x - 1 && tid == 0) bb.offs[(size_t)gridDim.x * bb.n] = (int)bb.M;
-    if (own) {
-        const bool forces = SPRINGS || Fext;
-        write_record<T>(rec, forces ? recf : nullptr, perm, i0 + hist[t] + r, i0 + tid, g, F,
-                        inv_vol);
-    }
+    if (own)
+        write_record<T>(rec, SPRINGS || Fext ? recf : nullptr, perm, pos, i0 + tid, g, F, inv_vol);
     if (fpart) {
         double tot[3] = {own ? F[0] : 0.0, own ? F[1] : 0.0, own ? F[2] : 0.0};
         block_reduce3(tot, red);
@@ -709,12 +718,14 @@ k_springs(SpringsDev sp, const double* __restrict__ q,
 // part (deterministic sums) the block instead writes its kbar sum and, per
 // pair e = (a, b), the sum over its particles of
 // -k (Fbar_a - Fbar_b) . d/|d| (d = q_b - q_a), in particle order, to
-// part[block][1 + npairs]; k_sum_parts adds the blocks in order.
+// part[block][1 + npairs]; k_sum_parts adds the blocks in order.  fsum
+// (nullable): Fbar is added to it.
 __global__ void __launch_bounds__(BLK)
 k_springs_adjoint(SpringsDev sp, const double* __restrict__ q,
                   const double* __restrict__ Fbar, int64_t P,
                   double* __restrict__ qbar, double* __restrict__ kbar,
-                  double* __restrict__ r0bar, double* __restrict__ part) {
+                  double* __restrict__ r0bar, double* __restrict__ part,
+                  double* __restrict__ fsum) {
     extern __shared__ double smem[];
     __shared__ double red[16];
     double fe[3];
@@ -725,7 +736,10 @@ k_springs_adjoint(SpringsDev sp, const double* __restrict__ q,
                  (sp.nb + 1 + 2 * sp.npairs + 1) / 2;
     double* rb = fb + 3 * sp.ppb * sp.nb;
     const int nb = sp.nb;
-    for (int i = threadIdx.x; i < 3 * B.nblob; i += BLK) fb[i] = Fbar[3 * B.p0 * nb + i];
+    for (int i = threadIdx.x; i < 3 * B.nblob; i += BLK) {
+        fb[i] = Fbar[3 * B.p0 * nb + i];
+        if (fsum) fsum[3 * B.p0 * nb + i] += fb[i];
+    }
     for (int e = threadIdx.x; e < sp.npairs; e += BLK) rb[e] = 0.0;
     __syncthreads();
     double kb = 0.0;
@@ -926,7 +940,7 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
 // Spreading: one block per box tile (FX x FY x FZ binning tiles, btl), one
 // velocity component at a time, or, on a grid of three rows, one block per
 // box tile and component (spread_boxes); a box tile without records only
-// writes zeros, or nothing where the x pass masks such boxes (skip_empty).  The box tile's own records (those of its
+// writes zeros.  The box tile's own records (those of its
 // cells) add all 27 of their contributions to an LDS box of the nodes they
 // can reach, [lo-1, lo+T+1] per axis, so no record is read by more than one
 // block and no contribution is masked.  The box is written to the box
@@ -952,72 +966,46 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
 // Threads of a spreading block covering f binning tiles: up to 1024 for
 // float32 fields, 512 for float64 ones (whose ~80 registers per thread
 // would otherwise leave room for one block per CU, not two).
-// SMALL: boxes binned by box hold at most 256 records, one per thread of a
-// block of 256; float32 then needs the 32-bit sums alone (27 KB of LDS), so
-// that the many blocks of box tiles without records pass quickly.
-template <typename T, bool SMALL>
+template <typename T>
 constexpr int spread_threads(int f) {
-    if (SMALL) return BLK;
     const int cap = sizeof(T) == 4 ? 1024 : 512;
     return f * BLK < cap ? f * BLK : cap;
 }
 
-constexpr int SPREAD_RUN = 8;
-
-template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ, bool SMALL>
-__global__ void __launch_bounds__((spread_threads<T, SMALL>(FX * FY * FZ)))
+template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ>
+__global__ void __launch_bounds__(spread_threads<T>(FX * FY * FZ))
 k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
          const int* __restrict__ offs, int L, Tiles btl, Tiles tl, int det,
-         int skip_empty, T* __restrict__ E) {
-    constexpr int NT = spread_threads<T, SMALL>(FX * FY * FZ);
+         T* __restrict__ E) {
+    constexpr int NT = spread_threads<T>(FX * FY * FZ);
     const int comp = gridDim.y == 3 ? (int)blockIdx.y : -1;  // one component, or all
     constexpr int NR = FX * FY * FZ;  // binning tiles of this box tile
     constexpr int EX = TX + 3, EY = TY + 3, EZ = TZ + 3;
     constexpr int EV = EX * EY * EZ;
     constexpr bool F32 = std::is_same<T, float>::value;
-    constexpr bool ONLY32 = F32 && SMALL;
-    constexpr int AV = ONLY32 ? (EV + 1) / 2 : EV;  // 64-bit words
-    __shared__ unsigned long long acc[AV];
+    __shared__ unsigned long long acc[EV];
     __shared__ double red[16];
     unsigned int* acc32 = reinterpret_cast<unsigned int*>(acc);
     double* accd = reinterpret_cast<double*>(acc);
-    // skip_empty (SMALL): a block takes SPREAD_RUN box tiles in turn, most of
-    // them empty: the launch is bound by the number of blocks (32 boxes of
-    // 64^3, 26 blobs each: 6,144 blocks of one box tile and component, 21 us)
-    const int run = SMALL && skip_empty ? SPREAD_RUN : 1;
-    // the records of box tile bt: its binning tiles are numbered
+    const TileBox tb = tile_box(btl, L, blockIdx.x);
+    const int tile = tb.tile;
+    // the records of this box tile: its binning tiles are numbered
     // consecutively (box-tile major), so their records form one range
-    auto records = [&](const TileBox& b, int& first, int& total) {
-        const int tc[3] = {b.lo[0] / tl.tx, b.lo[1] / tl.ty, b.lo[2] / tl.tz};
-        const int g = b.box * tl.n + tile_index(tc, tl);  // its first binning tile
+    int first, total;
+    {
+        const int tc[3] = {tb.lo[0] / tl.tx, tb.lo[1] / tl.ty, tb.lo[2] / tl.tz};
+        const int g = tb.box * tl.n + tile_index(tc, tl);  // its first binning tile
         first = offs[g];
         total = offs[g + NR] - first;
-    };
-    unsigned todo = 1u;
-    if (SMALL && run > 1) {  // which of the run hold records, read at once
-        todo = 0u;
-#pragma unroll
-        for (int br = 0; br < SPREAD_RUN; ++br) {
-            const int bt = blockIdx.x * SPREAD_RUN + br, last = btl.n * btl.nbox - 1;
-            int f0, n0;
-            records(tile_box(btl, L, bt < last ? bt : last), f0, n0);
-            todo |= bt <= last && n0 > 0 ? 1u << br : 0u;
-        }
     }
-    for (; todo != 0; todo = SMALL ? todo & (todo - 1) : 0u) {
-    const int bt = blockIdx.x * run + (SMALL ? __ffs(todo) - 1 : 0);
-    const TileBox tb = tile_box(btl, L, bt);
-    const int tile = tb.tile;
-    int first, total;
-    records(tb, first, total);
     if (total == 0) {  // no records: an empty box
         for (int a = comp < 0 ? 0 : comp; a <= (comp < 0 ? 2 : comp); ++a) {
             T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
             for (int i = threadIdx.x; i < EV; i += NT) st32(Ea, (unsigned)i, T(0));
         }
-        continue;
+        return;
     }
-    for (int i = threadIdx.x; i < AV; i += NT) acc[i] = 0ull;
+    for (int i = threadIdx.x; i < EV; i += NT) acc[i] = 0ull;
     // The k-th record a thread takes is the sorted record q(k) of the box
     // tile.  For float32 fields q(k) = (k * P) mod total with P = 263 (269
     // where 263 divides total, 1 where 269 does too), a bijection since P is
@@ -1057,7 +1045,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     // mode 0: the fast fixed-point form (u32 for float, u64 for double)
     int mode, e;
     if (F32) {
-        mode = SMALL || total <= 2048 ? 0 : 1;
+        mode = total <= 2048 ? 0 : 1;
         e = fixed_exponent(fmx, total, mode == 0 ? 0x1p31 : 0x1p63, 0x1p30);
     } else {
         // up to 2^20 records one 64-bit fixed-point sum (mode 0); beyond,
@@ -1106,7 +1094,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         }                                                                    \
     }
             if (F32) {
-                if (ONLY32 || mode == 0) {
+                if (mode == 0) {
 #define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)__float2int_rn((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
@@ -1149,7 +1137,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
         for (int i = threadIdx.x; i < EV; i += NT) {
             T val;
-            if (ONLY32 || (F32 && mode == 0)) {
+            if (F32 && mode == 0) {
                 val = ldexpf((float)(int)acc32[i], -e);
                 acc32[i] = 0u;
             } else if (F32 || mode == 0 || (mode == 2 && pass == 0)) {
@@ -1166,7 +1154,6 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
         }
         __syncthreads();
       }
-    }
     }
 }
 
@@ -1633,12 +1620,13 @@ __device__ __forceinline__ void node_offsets(const RecG<T>& r, int a, int L, uns
 // gathers its 27 nodes straight from the field.  A tile of k_interp stages
 // three components of 19 x 11 x 11 nodes for the few records it holds, and
 // most tiles hold none: here the launch is as small as the blobs (208 blobs
-// in 64^3 float64: 6.7 us by tiles).  Arguments as k_interp.
+// in 64^3 float64: 6.7 us by tiles, 5.2 so).  Arguments as k_interp; act
+// (nullable): clears the marks of the z planes of the records.
 template <typename T>
 __global__ void __launch_bounds__(WAVE)
 k_interp_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, int L, int mbox,
                 int64_t M, const T* __restrict__ v, double* __restrict__ u_out, double uscale,
-                double* __restrict__ q, double dt) {
+                double* __restrict__ q, double dt, unsigned char* __restrict__ act) {
     const int64_t j = (int64_t)blockIdx.x * WAVE + threadIdx.x;
     if (j >= 3 * M) return;
     const int64_t pos = j / 3;
@@ -1667,6 +1655,11 @@ k_interp_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, i
     const double u = uscale * (double)acc;
     if (u_out) u_out[i] = u;
     if (q) q[i] = q0 + dt * u;
+    if (act && a == 0) {  // the planes k_bin_box marked for this record
+        unsigned char* ab = act + (size_t)(pos / mbox) * L;
+        const int cz = (int)((r.cell >> 18) & 511u);
+        for (int o = -1; o <= 2; ++o) ab[wrapL(cz + o, L)] = 0;
+    }
 }
 
 // Position derivative of the interpolation, contracted with blob weights:
@@ -1767,6 +1760,64 @@ k_interp_grad(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
             gout[3 * i + 1] += gr[1];
             gout[3 * i + 2] += gr[2];
         }
+    }
+}
+
+// The same for small boxes (small_boxes): thread (record, component) gathers
+// its 27 nodes and the three derivative sums straight from the field, and the
+// three components of a record, in neighbouring threads of one wave, are
+// added in order.  u_out (nullable): also the interpolation uscale J v itself
+// (the reverse step needs both of one field).
+constexpr int GRAD_LANES = WAVE / 3;  // records per wave
+template <typename T>
+__global__ void __launch_bounds__(WAVE)
+k_interp_grad_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, int L,
+                     int mbox, int64_t M, const T* __restrict__ v, const double* __restrict__ W,
+                     double wscale, double inv_h, double* __restrict__ gout,
+                     double* __restrict__ u_out, double uscale) {
+    const int lr = threadIdx.x / 3, a = threadIdx.x - 3 * lr;
+    const int64_t pos = (int64_t)blockIdx.x * GRAD_LANES + lr;
+    const bool on = lr < GRAD_LANES && pos < M;
+    const int64_t pc = on ? pos : 0;
+    const RecG<T> r = rec[pc];
+    const int64_t i = perm[pc];
+    const double wgt = W[3 * i + a];
+    const T* va = v + ((size_t)(pc / mbox) * 3 + a) * ((size_t)L * L * L);
+    unsigned o[3][3];
+    node_offsets(r, a, L, o);
+    T w[3][3], dw[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) kernel_weights_deriv<T>(rec_t(r, a, b), w[b], dw[b]);
+    T acc = T(0), dx = T(0), dy = T(0), dz = T(0);
+#pragma unroll
+    for (int oz = 0; oz < 3; ++oz) {
+#pragma unroll
+        for (int oy = 0; oy < 3; ++oy) {
+            const unsigned ro = o[2][oz] + o[1][oy];
+            const T r0 = ld32(va, ro + o[0][0]), r1 = ld32(va, ro + o[0][1]),
+                    r2 = ld32(va, ro + o[0][2]);
+            const T sxv = row_sum(w[0], r0, r1, r2);
+            const T dsx = row_sum(dw[0], r0, r1, r2);
+            acc = fma(w[2][oz] * w[1][oy], sxv, acc);
+            dx += (w[2][oz] * w[1][oy]) * dsx;
+            dy += (w[2][oz] * dw[1][oy]) * sxv;
+            dz += (dw[2][oz] * w[1][oy]) * sxv;
+        }
+    }
+    const double c = wscale * inv_h * wgt;
+    const double g[3] = {c * (double)dx, c * (double)dy, c * (double)dz};
+    // lane (record, a) adds component a of the three threads' sums
+    double s = 0.0;
+    const int l0 = 3 * lr;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double t0 = __shfl(g[0], l0 + k), t1 = __shfl(g[1], l0 + k),
+                     t2 = __shfl(g[2], l0 + k);
+        s += a == 0 ? t0 : (a == 1 ? t1 : t2);
+    }
+    if (on) {
+        gout[3 * i + a] += s;
+        if (u_out) u_out[3 * i + a] = uscale * (double)acc;
     }
 }
 
@@ -1980,17 +2031,6 @@ static inline unsigned blocks_for(int64_t n) {
     return (unsigned)((n + BLK - 1) / BLK);
 }
 
-// The two record arrays in the grid's record scratch: geometry, then forces.
-template <typename T>
-static RecG<T>* rec_geo(mb_grid* g) {
-    return (RecG<T>*)g->d_rec;
-}
-template <typename T>
-static T* rec_force(mb_grid* g) {
-    const size_t cap = (size_t)std::max<int64_t>(g->d.max_blobs, 1);
-    return (T*)((char*)g->d_rec + cap * sizeof(RecG<T>));
-}
-
 // Exclusive scan of the tile counts into offs (the counts reset to zero).
 static void scan_tiles(mb_grid* g, hipStream_t s) {
     const int nt = g->tiles.n * g->tiles.nbox;
@@ -2011,14 +2051,16 @@ bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp) {
 template <typename T, bool SPRINGS>
 static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M, const double* q,
                             const double* F, const double* F2, double f2scale, double* Fsum,
-                            double fscale, double* fpart, bool mark, hipStream_t s) {
+                            double fscale, double* fpart, bool sort, bool mark,
+                            hipStream_t s) {
     BoxBin bb{};
     bb.n = g->tiles.n;
     bb.mbox = (int)(M / g->tiles.nbox);
     bb.M = M;
-    bb.offs = g->d_offs;
+    bb.offs = sort ? g->d_offs : nullptr;
     bb.act = mark ? g->d_act : nullptr;
-    const size_t lds = (size_t)((bb.n + 1) / 2) * sizeof(double) + (SPRINGS ? springs_lds(sp) : 0);
+    const size_t lds =
+        (sort ? (size_t)((bb.n + 1) / 2) * sizeof(double) : 0) + (SPRINGS ? springs_lds(sp) : 0);
     MB_LAUNCH(g, kid, s, (k_bin_box<T, SPRINGS>), g->tiles.nbox, BLK, lds, sp, bb, g->tiles, q, F,
               F2, f2scale, Fsum, 1.0 / g->d.h, g->L, fscale, rec_geo<T>(g), rec_force<T>(g),
               g->d_perm, fpart, finite_flag(g));
@@ -2107,12 +2149,13 @@ hipError_t finish_call(mb_grid* g, int64_t P, int nb, bool reordered, double* q,
 
 template <typename T>
 hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, hipStream_t s,
-                       double fscale, const double* F2, double f2scale, double* Fsum) {
+                       bool tiles, double fscale, const double* F2, double f2scale,
+                       double* Fsum) {
     const double h = g->d.h;
     const double sc = fscale > 0.0 ? fscale : 1.0 / (h * h * h);
     if (small_boxes(g, M, nullptr))
         return bin_boxes<T, false>(g, K_BIN_SCATTER, SpringsDev{}, M, q, F, F2, f2scale, Fsum, sc,
-                                   nullptr, false, s);
+                                   nullptr, tiles, false, s);
     hipError_t e = hipSuccess;
     if (Fsum) {
         e = blob_axpy(3 * M, F2, f2scale, F, Fsum, s);
@@ -2130,10 +2173,10 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
 template <typename T>
 hipError_t bin_springs(mb_grid* g, const SpringsDev& sp, int64_t P, const double* q,
                        const double* Fext, hipStream_t s, const double* Gblob, bool force_sums,
-                       bool mark) {
+                       bool tiles, bool mark) {
     const double h = g->d.h;
     return bin_boxes<T, true>(g, K_SPRINGS_SCATTER, sp, P * sp.nb, q, Fext, Gblob, 0.0, nullptr,
-                              1.0 / (h * h * h), force_sums ? g->d_force_part : nullptr, mark, s);
+                              1.0 / (h * h * h), force_sums ? g->d_force_part : nullptr, tiles, mark, s);
 }
 
 template <typename T>
@@ -2188,12 +2231,13 @@ size_t springs_adjoint_lds(const SpringsDev& sp) {
 
 hipError_t springs_adjoint(const SpringsDev& sp, int64_t P, const double* q,
                            const double* Fbar, double* qbar, double* kbar,
-                           double* r0bar, hipStream_t s, mb_grid* tg, double* part) {
+                           double* r0bar, hipStream_t s, mb_grid* tg, double* part,
+                           double* fsum) {
     const int64_t M = P * sp.nb;
     if (M == 0) return hipSuccess;
     const int nblk = springs_blocks(sp, P);
     MB_LAUNCH(tg, K_SPRINGS_ADJ, s, k_springs_adjoint, nblk, BLK,
-              springs_adjoint_lds(sp), sp, q, Fbar, P, qbar, kbar, r0bar, part);
+              springs_adjoint_lds(sp), sp, q, Fbar, P, qbar, kbar, r0bar, part, fsum);
     if (part && (kbar || r0bar)) {
         const int nent = 1 + sp.npairs;
         hipLaunchKernelGGL(k_sum_parts, dim3(blocks_for(nent)), dim3(BLK), 0, s, part, nblk,
@@ -2297,7 +2341,7 @@ bool tile_shape_supported(int tx, int ty, int tz) {
     X(16, 16, 8, 1, 1, 1) X(16, 8, 16, 1, 1, 1) X(8, 16, 16, 1, 1, 1)
 
 template <typename T>
-hipError_t spread_boxes(mb_grid* g, hipStream_t s, bool skip_empty) {
+hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
     const Tiles& t = g->tiles;
     const Tiles& b = g->btiles;
     bool ok = false;
@@ -2312,27 +2356,17 @@ hipError_t spread_boxes(mb_grid* g, hipStream_t s, bool skip_empty) {
     // mixed, 32.5 -> 40.2 float64).
     constexpr int kSplitBoxTiles = 256;
     const int nbt = b.n * b.nbox;
-    // (skip_empty and small kernels: boxes binned by box; few box tiles keep
-    // the larger blocks, whose phases are shorter: 64 of 64^3 float64, 208
-    // blobs, 9.0 us against 10.3)
-    const bool small = g->binned_small && nbt > 64;
-    skip_empty = skip_empty && small;
-    const dim3 grid(skip_empty ? (nbt + SPREAD_RUN - 1) / SPREAD_RUN : nbt,
-                    small || nbt <= kSplitBoxTiles ? 3 : 1);
-#define MB_BOX_K(SX, SY, SZ, FX, FY, FZ, SM)                                             \
-    MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ, SM>), grid,           \
-              (spread_threads<T, SM>(FX * FY * FZ)), 0, rec_geo<T>(g), rec_force<T>(g),  \
-              g->d_offs, g->L, b, t, g->d.deterministic, skip_empty ? 1 : 0, (T*)g->d_box)
+    const dim3 grid(nbt, nbt <= kSplitBoxTiles ? 3 : 1);
 #define MB_BOX(SX, SY, SZ, FX, FY, FZ)                                                   \
     if (!ok && b.tx == SX && b.ty == SY && b.tz == SZ && SX == FX * t.tx &&              \
         SY == FY * t.ty && SZ == FZ * t.tz) {                                            \
-        if (small) MB_BOX_K(SX, SY, SZ, FX, FY, FZ, true);                               \
-        else MB_BOX_K(SX, SY, SZ, FX, FY, FZ, false);                                    \
+        MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ>), grid,           \
+                  spread_threads<T>(FX * FY * FZ), 0, rec_geo<T>(g), rec_force<T>(g),    \
+                  g->d_offs, g->L, b, t, g->d.deterministic, (T*)g->d_box);              \
         ok = true;                                                                       \
     }
     MB_BOX_SHAPES(MB_BOX)
 #undef MB_BOX
-#undef MB_BOX_K
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
@@ -2354,13 +2388,13 @@ hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s) {
 template <typename T>
 hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
                        double* q_update, int diag, hipStream_t s, double uscale,
-                       bool bin_next) {
+                       bool bin_next, bool clear_planes) {
     double* part = diag ? g->d_tile_part : nullptr;
     const int kid = q_update ? K_INTERP_STEP : K_INTERP;
     if (g->binned_small && !part) {
         MB_LAUNCH(g, kid, s, k_interp_direct<T>, (unsigned)((3 * M + WAVE - 1) / WAVE), WAVE, 0,
                   rec_geo<T>(g), g->d_perm, g->L, (int)(M / g->tiles.nbox), M, v, u_out, uscale,
-                  q_update, g->d.dt);
+                  q_update, g->d.dt, clear_planes ? g->d_act : nullptr);
         return hipGetLastError();
     }
     BinNext bn{nullptr, nullptr, nullptr};
@@ -2377,8 +2411,19 @@ hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
 }
 
 template <typename T>
-hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wscale,
-                            double* gout, hipStream_t s) {
+hipError_t interpolate_grad(mb_grid* g, int64_t M, const T* v, const double* W, double wscale,
+                            double* gout, hipStream_t s, double* u_out, double uscale) {
+    if (g->binned_small) {
+        MB_LAUNCH(g, K_INTERP_GRAD, s, k_interp_grad_direct<T>,
+                  (unsigned)((M + GRAD_LANES - 1) / GRAD_LANES), WAVE, 0, rec_geo<T>(g), g->d_perm,
+                  g->L, (int)(M / g->tiles.nbox), M, v, W, wscale, 1.0 / g->d.h, gout, u_out,
+                  uscale);
+        return hipGetLastError();
+    }
+    if (u_out) {
+        const hipError_t e = interpolate<T>(g, M, v, u_out, nullptr, 0, s, uscale);
+        if (e != hipSuccess) return e;
+    }
     const bool ok = with_tile_shape(g->tiles, [&](auto X, auto Y, auto Z) {
         MB_LAUNCH(g, K_INTERP_GRAD, s, (k_interp_grad<T, decltype(X)::value, decltype(Y)::value, decltype(Z)::value>),
                   g->tiles.n * g->tiles.nbox, BLK, 0, rec_geo<T>(g), g->d_perm,
@@ -2391,20 +2436,20 @@ hipError_t interpolate_grad(mb_grid* g, const T* v, const double* W, double wsca
 // Explicit instantiations.
 template hipError_t bin_blobs<float>(mb_grid*, int64_t, const double*, hipStream_t, bool, bool);
 template hipError_t bin_blobs<double>(mb_grid*, int64_t, const double*, hipStream_t, bool, bool);
-template hipError_t bin_records<float>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double, const double*, double, double*);
-template hipError_t bin_records<double>(mb_grid*, int64_t, const double*, const double*, hipStream_t, double, const double*, double, double*);
-template hipError_t bin_springs<float>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
-template hipError_t bin_springs<double>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
+template hipError_t bin_records<float>(mb_grid*, int64_t, const double*, const double*, hipStream_t, bool, double, const double*, double, double*);
+template hipError_t bin_records<double>(mb_grid*, int64_t, const double*, const double*, hipStream_t, bool, double, const double*, double, double*);
+template hipError_t bin_springs<float>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool, bool);
+template hipError_t bin_springs<double>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool, bool);
 template hipError_t scatter_springs<float>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
 template hipError_t scatter_springs<double>(mb_grid*, const SpringsDev&, int64_t, const double*, const double*, hipStream_t, const double*, bool, bool);
-template hipError_t spread_boxes<float>(mb_grid*, hipStream_t, bool);
-template hipError_t spread_boxes<double>(mb_grid*, hipStream_t, bool);
+template hipError_t spread_boxes<float>(mb_grid*, hipStream_t);
+template hipError_t spread_boxes<double>(mb_grid*, hipStream_t);
 template hipError_t fold_boxes<float>(mb_grid*, float*, hipStream_t);
 template hipError_t fold_boxes<double>(mb_grid*, double*, hipStream_t);
-template hipError_t interpolate<float>(mb_grid*, int64_t, const float*, double*, double*, int, hipStream_t, double, bool);
-template hipError_t interpolate<double>(mb_grid*, int64_t, const double*, double*, double*, int, hipStream_t, double, bool);
-template hipError_t interpolate_grad<float>(mb_grid*, const float*, const double*, double, double*, hipStream_t);
-template hipError_t interpolate_grad<double>(mb_grid*, const double*, const double*, double, double*, hipStream_t);
+template hipError_t interpolate<float>(mb_grid*, int64_t, const float*, double*, double*, int, hipStream_t, double, bool, bool);
+template hipError_t interpolate<double>(mb_grid*, int64_t, const double*, double*, double*, int, hipStream_t, double, bool, bool);
+template hipError_t interpolate_grad<float>(mb_grid*, int64_t, const float*, const double*, double, double*, hipStream_t, double*, double);
+template hipError_t interpolate_grad<double>(mb_grid*, int64_t, const double*, const double*, double, double*, hipStream_t, double*, double);
 
 size_t box_elems(const Tiles& t) {
     return (size_t)3 * t.nbox * t.n * (t.tx + 3) * (t.ty + 3) * (t.tz + 3);
