@@ -64,10 +64,14 @@ inline T* rec_force(const mb_grid* g) {
     return (T*)((char*)g->d_rec + cap * sizeof(RecG<T>));
 }
 
-// Kernel offset of a record for velocity component a along axis b.
+// Kernel offset of a record for velocity component a along axis b.  (One read
+// of s[b]: read in both arms, the compiler makes the first s[a], an indexed
+// array where a is not a constant, which it keeps in LDS at an address that
+// takes the launch packet's block size, a load from host memory of some 12 us.)
 template <typename T>
 __device__ __forceinline__ T rec_t(const RecG<T>& r, int a, int b) {
-    return a == b ? r.s[b] - T(0.5) : r.s[b] - T((r.cell >> (27 + b)) & 1u);
+    const T node = a == b ? T(0.5) : T((r.cell >> (27 + b)) & 1u);
+    return r.s[b] - node;
 }
 
 // 1/sqrt(x) for a normal float64 x > 0: the hardware estimate refined by
@@ -107,6 +111,14 @@ __device__ __forceinline__ void kernel_weights(T t, T w[3]) {
     w[1] = (T(1) + s) * (T(1) / T(3));
     w[2] = (T(2) + T(3) * t - s) * sixth;
     w[0] = (T(2) - T(3) * t - s) * sixth;
+}
+
+// Weight k (0, 1, 2: nodes i0-1, i0, i0+1) alone, without an indexed array.
+template <typename T>
+__device__ __forceinline__ T kernel_weight(T t, int k) {
+    const T s = weight_sqrt(T(1) - T(3) * t * t);
+    const T side = k == 0 ? T(2) - T(3) * t : T(2) + T(3) * t;
+    return k == 1 ? (T(1) + s) * (T(1) / T(3)) : (side - s) * (T(1) / T(6));
 }
 
 // The weights and their derivatives with respect to t: d/dt Phi(t) =

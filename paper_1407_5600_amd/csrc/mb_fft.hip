@@ -278,7 +278,6 @@ struct Geo {
     // against 34.5)
     static constexpr int TXY_RAW = ((L * H / 8 + WAVE - 1) / WAVE) * WAVE;
     static constexpr int TXY = TXY_RAW > 1024 ? 1024 : TXY_RAW;
-    static constexpr int TXYP = TXY > 512 ? 512 : TXY;  // some planes only: a loop, no spills
     static constexpr int NBXY = 3 * L;                         // blocks per box
 };
 
@@ -358,13 +357,10 @@ __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
             total += __popcll(m);
         }
         if (keep) {
-            T wx[3], wy[3], wz[3];
+            T wx[3], wy[3];
             kernel_weights<T>(rec_t(r, a, 0), wx);
             kernel_weights<T>(rec_t(r, a, 1), wy);
-            kernel_weights<T>(rec_t(r, a, 2), wz);
-            T f = wz[2];  // (selected, not indexed)
-            f = dz == 1 ? wz[1] : f;
-            f = (dz == 0 ? wz[0] : f) * F;
+            const T f = kernel_weight<T>(rec_t(r, a, 2), dz) * F;
             RecLine<T>* e = list + before + __popcll(m & ((1ull << (tid % WAVE)) - 1));
             e->wx[0] = wx[0];
             e->wx[1] = wx[1];
@@ -898,28 +894,32 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // produced (a block takes those of active_planes); else act
 // (nullable) is cleared.
 template <typename T, int L, bool PLANES>
-__global__ void __launch_bounds__((PLANES ? Geo<T, L>::TXYP : Geo<T, L>::TXY))
+__global__ void __launch_bounds__((Geo<T, L>::TXY))
 k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
          T* __restrict__ vout, unsigned char* __restrict__ act) {
     using G = Geo<T, L>;
-    constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = PLANES ? G::TXYP : G::TXY;
+    constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = G::TXY;
     __shared__ cplx<T> buf[L * PS];
     __shared__ cplx<T> tws[L];
     __shared__ cplx<T> twh[H];
-    const int tid = threadIdx.x;
-    for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
-    for (int i = tid; i < H; i += NTHR) twh[i] = tw[2 * i];
+    const int tid0 = threadIdx.x;
+    for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
+    for (int i = tid0; i < H; i += NTHR) twh[i] = tw[2 * i];
     constexpr int nz = PLANES ? 8 : L;
     const int bc = blockIdx.x / nz, z0 = blockIdx.x % nz;  // box * 3 + c
     unsigned long long todo = 1;
     if (PLANES) {
         todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0);
-    } else if (act && tid == 0 && bc % 3 == 0) {
+    } else if (act && tid0 == 0 && bc % 3 == 0) {
         act[(size_t)(bc / 3) * L + z0] = 0;  // for the next binning
     }
     for (; todo != 0; todo = PLANES ? todo & (todo - 1) : 0) {
     const int cz = PLANES ? bc * L + z0 + 8 * (__ffsll(todo) - 1)  // (box * 3 + c) * L + z
                           : (int)blockIdx.x;
+    // (opaque in the loop over planes: the indices formed from it are not kept
+    // across it, which spilled)
+    int tid = tid0;
+    if (PLANES) asm volatile("" : "+v"(tid));
     // stage the half spectrum: F[kx][ky] at row ky, column kx (0..H)
     const cplx<T>* in = A + (size_t)cz * NC * L;
     {
@@ -1054,8 +1054,8 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
 #undef MB_Z
     if constexpr (G::XY) {
         if (part)
-            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * 8 * nbox, G::TXYP,
-                      0, A, tw, v_out, act);
+            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * 8 * nbox, G::TXY, 0,
+                      A, tw, v_out, act);
         else
             MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, false>), G::NBXY * nbox, G::TXY, 0, A,
                       tw, v_out, act);

@@ -759,18 +759,19 @@ k_springs_adjoint(SpringsDev sp, const double* __restrict__ q,
             const int o = code & 0xff;
             const int e = code >> 8;
             const double dx = qp[3 * o] - qx, dy = qp[3 * o + 1] - qy, dz = qp[3 * o + 2] - qz;
-            const double len = sqrt(dx * dx + dy * dy + dz * dz);
+            const double inv = rsqrt_nr(dx * dx + dy * dy + dz * dz);
             const double r0 = B.r0s[e];
-            const double sc = sp.k * (1.0 - r0 / len);
-            const double tc = sp.k * r0 / (len * len * len);
+            const double st = fma(-r0, inv, 1.0);  // 1 - r0 / |d|
+            const double sc = sp.k * st;
+            const double tc = sp.k * r0 * (inv * inv * inv);
             const double lx = fp[3 * o] - fx, ly = fp[3 * o + 1] - fy, lz = fp[3 * o + 2] - fz;
             const double ld = lx * dx + ly * dy + lz * dz;
             gx += sc * lx + tc * dx * ld;
             gy += sc * ly + tc * dy * ld;
             gz += sc * lz + tc * dz * ld;
             const double fd = fx * dx + fy * dy + fz * dz;
-            kb += fd * (1.0 - r0 / len);
-            if (!part) atomicAdd(&rb[e], -sp.k * fd / len);
+            kb += fd * st;
+            if (!part) atomicAdd(&rb[e], -sp.k * fd * inv);
         }
         double* qo = qbar + 3 * (B.p0 * nb + j);
         qo[0] += gx;
