@@ -37,9 +37,11 @@ __device__ __forceinline__ AxisSrc axis_sources(int v, int T, int nt, int tstrid
     return s;
 }
 
-// Elements of one tile's box.
+// Elements between the boxes of two tiles: a box's, rounded up to a multiple
+// of four (the spreading stores four at a time).
+constexpr int box_stride(int nodes) { return (nodes + 3) & ~3; }
 __device__ __forceinline__ int box_volume(const Tiles& tl) {
-    return (tl.tx + 3) * (tl.ty + 3) * (tl.tz + 3);
+    return box_stride((tl.tx + 3) * (tl.ty + 3) * (tl.tz + 3));
 }
 
 // Sources of a node along x, y and z of the box array.

@@ -938,6 +938,24 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
     return e_sum < e_one ? e_sum : e_one;
 }
 
+// The nearest integer of x (ties up) in one instruction; rint and a conversion
+// are two.
+__device__ __forceinline__ int round_int(float x) {
+    int r;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// Elements 2 i, 2 i + 1, and 4 i .. 4 i + 3, of a box.
+template <typename T>
+__device__ __forceinline__ void store2(T* Ea, int i, T a, T b) {
+    if constexpr (sizeof(T) == 4) reinterpret_cast<float2*>(Ea)[i] = make_float2(a, b);
+    else reinterpret_cast<double2*>(Ea)[i] = make_double2(a, b);
+}
+__device__ __forceinline__ void store4(float* Ea, int i, float4 x) {
+    reinterpret_cast<float4*>(Ea)[i] = x;
+}
+
 // Spreading: one block per box tile (FX x FY x FZ binning tiles, btl), one
 // velocity component at a time, or, on a grid of three rows, one block per
 // box tile and component (spread_boxes); a box tile without records only
@@ -983,11 +1001,14 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     constexpr int NR = FX * FY * FZ;  // binning tiles of this box tile
     constexpr int EX = TX + 3, EY = TY + 3, EZ = TZ + 3;
     constexpr int EV = EX * EY * EZ;
+    constexpr int EVP = box_stride(EV);  // elements of a box in E
     constexpr bool F32 = std::is_same<T, float>::value;
-    __shared__ unsigned long long acc[EV];
-    __shared__ double red[16];
+    __shared__ __align__(16) unsigned long long acc[EVP];
+    __shared__ unsigned long long fmax_bits;
+    __shared__ int e_shared;
     unsigned int* acc32 = reinterpret_cast<unsigned int*>(acc);
     double* accd = reinterpret_cast<double*>(acc);
+    if (threadIdx.x == 0) fmax_bits = 0ull;
     const TileBox tb = tile_box(btl, L, blockIdx.x);
     const int tile = tb.tile;
     // the records of this box tile: its binning tiles are numbered
@@ -1001,12 +1022,25 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     }
     if (total == 0) {  // no records: an empty box
         for (int a = comp < 0 ? 0 : comp; a <= (comp < 0 ? 2 : comp); ++a) {
-            T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
-            for (int i = threadIdx.x; i < EV; i += NT) st32(Ea, (unsigned)i, T(0));
+            T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EVP;
+            for (int i = threadIdx.x; i < EVP / 2; i += NT) store2<T>(Ea, i, T(0), T(0));
         }
         return;
     }
-    for (int i = threadIdx.x; i < EV; i += NT) acc[i] = 0ull;
+    // mode 0: the fast fixed-point form (u32 for float, u64 for double); float64:
+    // up to 2^20 records one 64-bit fixed-point sum (mode 0); beyond, float64
+    // LDS atomics (mode 1, whose last bits depend on the order) or, with det,
+    // two 64-bit fixed-point sums (mode 2): the contributions rounded to the
+    // quantum 2^-e, then their rounding remainders to 2^-(e+38), which cannot
+    // overflow up to 2^25 records (each remainder at most 2^37 quanta)
+    const int mode = F32 ? (total <= 2048 ? 0 : 1)
+                         : (total <= (1 << 20) ? 0 : ((det && total <= (1 << 25)) ? 2 : 1));
+    {
+        // clear the sums, 16 bytes a store (32-bit sums: the first half)
+        uint4* z = reinterpret_cast<uint4*>(acc);
+        const int nz = F32 && mode == 0 ? EVP / 4 : EVP / 2;
+        for (int i = threadIdx.x; i < nz; i += NT) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     // The k-th record a thread takes is the sorted record q(k) of the box
     // tile.  For float32 fields q(k) = (k * P) mod total with P = 263 (269
     // where 263 divides total, 1 where 269 does too), a bijection since P is
@@ -1034,30 +1068,40 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
 #pragma unroll
         for (int b = 0; b < 3; ++b) F0[b] = recf[3 * (size_t)p + b];
     }
-    double fm = 0.0;
+    // the largest |F h^-3| of the box tile: one LDS maximum per wave of the
+    // bits of a nonnegative number (NaN left out, as fmax does), the exponent
+    // by one wave (its float64 divisions cost every wave some 150
+    // instructions otherwise)
+    T fm = T(0);
+    auto larger = [&fm](T x) {
+        x = x < T(0) ? -x : x;
+        fm = x > fm ? x : fm;
+    };
 #pragma unroll
-    for (int b = 0; b < 3; ++b) fm = fmax(fm, fabs((double)F0[b]));
+    for (int b = 0; b < 3; ++b) larger(F0[b]);
     for (int k = threadIdx.x + NT, q = adv(q0); k < total; k += NT, q = adv(q)) {
         const size_t p = (size_t)(first + q);
 #pragma unroll
-        for (int b = 0; b < 3; ++b) fm = fmax(fm, fabs((double)recf[3 * p + b]));
+        for (int b = 0; b < 3; ++b) larger(recf[3 * p + b]);
     }
-    const double fmx = block_reduce<true>(fm, red);
-    // mode 0: the fast fixed-point form (u32 for float, u64 for double)
-    int mode, e;
-    if (F32) {
-        mode = total <= 2048 ? 0 : 1;
-        e = fixed_exponent(fmx, total, mode == 0 ? 0x1p31 : 0x1p63, 0x1p30);
-    } else {
-        // up to 2^20 records one 64-bit fixed-point sum (mode 0); beyond,
-        // float64 LDS atomics (mode 1, whose last bits depend on the order)
-        // or, with det, two 64-bit fixed-point sums (mode 2): the
-        // contributions rounded to the quantum 2^-e, then their rounding
-        // remainders to 2^-(e+38), which cannot overflow up to 2^25 records
-        // (each remainder at most 2^37 quanta)
-        mode = total <= (1 << 20) ? 0 : ((det && total <= (1 << 25)) ? 2 : 1);
-        e = mode != 1 ? fixed_exponent(fmx, total, 0x1p63, 0x1p50) : 0;
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const T y = __shfl_xor(fm, o, WAVE);
+        fm = y > fm ? y : fm;
     }
+    __syncthreads();  // fmax_bits and the sums are cleared
+    if (threadIdx.x % WAVE == 0)
+        atomicMax(&fmax_bits, (unsigned long long)__double_as_longlong((double)fm));
+    __syncthreads();
+    if (threadIdx.x < WAVE) {
+        const double fmx = __longlong_as_double((long long)fmax_bits);
+        int ex = 0;
+        if (F32) ex = fixed_exponent(fmx, total, mode == 0 ? 0x1p31 : 0x1p63, 0x1p30);
+        else if (mode != 1) ex = fixed_exponent(fmx, total, 0x1p63, 0x1p50);
+        if (threadIdx.x == 0) e_shared = ex;
+    }
+    __syncthreads();
+    const int e = e_shared;
     const int npass = mode == 2 ? 2 : 1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -1096,12 +1140,12 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     }
             if (F32) {
                 if (mode == 0) {
-#define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)__float2int_rn((float)(v)))
+#define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)round_int((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
                 } else {
 #define MB_ADD(i, v) \
-    atomicAdd(&acc[i], (unsigned long long)(long long)__float2int_rn((float)(v)))
+    atomicAdd(&acc[i], (unsigned long long)(long long)round_int((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
                 }
@@ -1134,24 +1178,42 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
 #undef MB_SPREAD_27
         }
         __syncthreads();
-        // write the box and clear it for the next component
-        T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EV;
-        for (int i = threadIdx.x; i < EV; i += NT) {
-            T val;
-            if (F32 && mode == 0) {
-                val = ldexpf((float)(int)acc32[i], -e);
-                acc32[i] = 0u;
-            } else if (F32 || mode == 0 || (mode == 2 && pass == 0)) {
-                val = (T)ldexp((double)(long long)acc[i], -e);
-                acc[i] = 0ull;
-            } else if (mode == 2) {  // the remainders, added to the first sum
-                val = Ea[i] + (T)ldexp((double)(long long)acc[i], -(e + 38));
-                acc[i] = 0ull;
-            } else {
-                val = (T)accd[i];
-                acc[i] = 0ull;
+        // write the box, four nodes a store, and clear it for the next
+        // component
+        T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EVP;
+        if (F32 && mode == 0) {
+            const float sc = ldexpf(1.0f, -e);  // (exact: a power of two)
+            const bool fine = e <= 126 && e >= -126;
+            for (int i = threadIdx.x; i < EVP / 4; i += NT) {
+                int4* p = reinterpret_cast<int4*>(acc) + i;
+                const int4 s = *p;
+                *p = make_int4(0, 0, 0, 0);
+                const float x[4] = {(float)s.x, (float)s.y, (float)s.z, (float)s.w};
+                float val[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) val[c] = fine ? x[c] * sc : ldexpf(x[c], -e);
+                store4(reinterpret_cast<float*>(Ea), i,
+                       make_float4(val[0], val[1], val[2], val[3]));
             }
-            st32(Ea, (unsigned)i, val);
+        } else {
+            // (16 bytes of sums a thread: with four each, 32 bytes apart, the
+            // LDS reads of a wave collide)
+            for (int i = threadIdx.x; i < EVP / 2; i += NT) {
+                T val[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int j = 2 * i + c;
+                    const long long s = (long long)acc[j];
+                    if (F32 || mode == 0 || (mode == 2 && pass == 0))
+                        val[c] = (T)ldexp((double)s, -e);
+                    else if (mode == 2)  // the remainders, added to the first sum
+                        val[c] = Ea[j] + (T)ldexp((double)s, -(e + 38));
+                    else
+                        val[c] = (T)accd[j];
+                }
+                reinterpret_cast<uint4*>(acc)[i] = make_uint4(0u, 0u, 0u, 0u);
+                store2<T>(Ea, i, val[0], val[1]);
+            }
         }
         __syncthreads();
       }
@@ -2453,7 +2515,7 @@ template hipError_t interpolate_grad<float>(mb_grid*, int64_t, const float*, con
 template hipError_t interpolate_grad<double>(mb_grid*, int64_t, const double*, const double*, double, double*, hipStream_t, double*, double);
 
 size_t box_elems(const Tiles& t) {
-    return (size_t)3 * t.nbox * t.n * (t.tx + 3) * (t.ty + 3) * (t.tz + 3);
+    return (size_t)3 * t.nbox * t.n * box_stride((t.tx + 3) * (t.ty + 3) * (t.tz + 3));
 }
 
 size_t record_size(int precision) {
