@@ -34,8 +34,8 @@ constexpr int EPT = 8;  // elements per thread in a line transform
 // elements, so that the radix-16 stage's stores (stride 16) and the
 // following stage's loads spread over the banks.
 __device__ __forceinline__ constexpr int lpad(int e) { return e + (e >> 4); }
-// line stride: room for the padded line, odd
-constexpr int line_stride(int L) { return (L + (L - 1) / 16 + 1) | 1; }
+// line stride: room for the padded line (lpad(L - 1) + 1 slots), odd
+constexpr int line_stride(int L) { return (L + (L - 1) / 16) | 1; }
 
 // Radix plan: 16s, then 8, 4, 2, then 3s.
 constexpr int nstages(int n) {
@@ -198,18 +198,21 @@ constexpr int rows_x(int L) { return largest_even_divisor(L, 4096 / L > 2 ? 4096
 // -> 20.5, float64 38.2 -> 34.6).  Fewer rows store shorter runs of ky (a
 // batch of 32 64^3 boxes: 69.7 us with 16 rows, 76 with 8).  Above, float32
 // takes as few elements as 512 threads allow (144^3, 16 rows: 40.9 -> 35.9
-// us; 192^3 96.5 -> 92.1; 256^3 211.7 -> 204.6), float64 stays at eight,
-// bound by its registers (256^3 339 us with eight, 344 with four).
+// us; 192^3 96.5 -> 92.1; 256^3 211.7 -> 204.6), float64 four of eight rows
+// from L = 192 on (192^3 with boxes 198.5 -> 196 us, without 165 -> 152, 256^3
+// with boxes 435 -> 426; four of sixteen rows 566: three waves of 512 threads
+// do not fit its registers) and eight of 24 at 144 (75 us, 80 with eight rows).
 template <typename T>
 constexpr int rows_xf(int L) {
     if (L <= 128 || (sizeof(T) == 4 && L == 144)) return largest_even_divisor(L, 16);
+    if (sizeof(T) == 8 && L >= 192) return 8;
     return rows_x(L);
 }
 template <typename T>
 constexpr int elems_xf(int L) {
     const int n = rows_xf<T>(L) / 2 * L;
     if (L <= 128) return L <= 24 ? 1 : (L <= 72 ? 2 : 4);
-    if (sizeof(T) == 8) return EPT;
+    if (sizeof(T) == 8) return L >= 192 ? 4 : EPT;
     int e = 3;
     while (n % e != 0 || n / e > 512) ++e;
     return e;
@@ -481,10 +484,12 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     }
     // KG iterations (2 KG nodes) per round: all loads of a round, the box
     // entries included (box_entries: loads only, in uniform branches), are
-    // issued before its arithmetic.  One iteration: two took 96 registers in
-    // float32 (five waves per SIMD, 1.2 rounds of blocks at 128^3); one fits
-    // six waves and one round (25.4 against 26.7 us).
-    constexpr int KG = 1;
+    // issued before its arithmetic.  Two where a float32 wave keeps to one row
+    // pair and has them (128^3: 21.4 against 20.7 us, 256^3: 209 against 202);
+    // one elsewhere (float64 128^3: 34.5 against 37.5 with two, whose registers
+    // cost a wave; 96^3: 14.0 against 15.5).
+    constexpr bool UNI_ROWS = L % WAVE == 0 && NTHR % L == 0;
+    constexpr int KG = sizeof(T) == 4 && UNI_ROWS && BOX && !STEADY && G::EX % 2 == 0 ? 2 : 1;
     static_assert(G::EX % KG == 0, "rounds of the x pass");
     // a wave's lanes share y when L is a multiple of the wave
     constexpr bool UNI = L % WAVE == 0 && NTHR % L == 0;
@@ -503,38 +508,41 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     for (int k0 = 0; k0 < G::EX; k0 += KG) {
         T vc[KG][2], vn[KG][2][6], fv[KG][2];
         T eb[KG][2][4][2];
-        if constexpr (UNI && KG == 1) {
-            const int line = line0 + k0 * (NTHR / L);
+        if constexpr (UNI) {
             const char* vb = reinterpret_cast<const char*>(v);
             const char* fb = reinterpret_cast<const char*>(f);
             auto at = [](const char* base, int row, unsigned o) {
                 return *reinterpret_cast<const T*>(base + (size_t)row * sizeof(T) + o);
             };
 #pragma unroll
+            for (int g = 0; g < KG; ++g) {
+            const int line = line0 + (k0 + g) * (NTHR / L);
+#pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
                 const int y = y0 + 2 * line + hh;
                 const int row = cbase + (z * L + y) * L;
-                if (SRC == SRC_FIELD) fv[0][hh] = at(fb, row, ox);
-                if constexpr (ADD) fv[0][hh] = at(reinterpret_cast<const char*>(add), row, ox);
+                if (SRC == SRC_FIELD) fv[g][hh] = at(fb, row, ox);
+                if constexpr (ADD) fv[g][hh] = at(reinterpret_cast<const char*>(add), row, ox);
                 if constexpr (REC)
-                    fv[0][hh] = add ? at(reinterpret_cast<const char*>(add), row, ox) : T(0);
+                    fv[g][hh] = add ? at(reinterpret_cast<const char*>(add), row, ox) : T(0);
                 if (!STEADY) {
                     const int ym = y == 0 ? L - 1 : y - 1, yp = y == L - 1 ? 0 : y + 1;
-                    vc[0][hh] = at(vb, row, ox);
-                    vn[0][hh][0] = at(vb, row, oxm);
-                    vn[0][hh][1] = at(vb, row, oxp);
-                    vn[0][hh][2] = at(vb, cbase + (z * L + ym) * L, ox);
-                    vn[0][hh][3] = at(vb, cbase + (z * L + yp) * L, ox);
-                    vn[0][hh][4] = at(vb, cbase + (zm * L + y) * L, ox);
-                    vn[0][hh][5] = at(vb, cbase + (zp * L + y) * L, ox);
+                    vc[g][hh] = at(vb, row, ox);
+                    vn[g][hh][0] = at(vb, row, oxm);
+                    vn[g][hh][1] = at(vb, row, oxp);
+                    vn[g][hh][2] = at(vb, cbase + (z * L + ym) * L, ox);
+                    vn[g][hh][3] = at(vb, cbase + (z * L + yp) * L, ox);
+                    vn[g][hh][4] = at(vb, cbase + (zm * L + y) * L, ox);
+                    vn[g][hh][5] = at(vb, cbase + (zp * L + y) * L, ox);
                 }
             }
             if constexpr (BOX) {
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) {
                     const AxisSrc by = box_src_y(tl, y0 + 2 * line + hh);
-                    box_entries(Ec, bxu, by, bz, eb[0][hh]);
+                    box_entries(Ec, bxu, by, bz, eb[g][hh]);
                 }
+            }
             }
         } else {
 #pragma unroll
@@ -647,7 +655,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
 
 // y pass: block = (component, z plane, WY consecutive kx); the kx rows of
 // length L (along ky) are contiguous in A.
-template <typename T, int L, bool INV>
+template <typename T, int L, bool INV, bool ACT>
 __global__ void __launch_bounds__((Geo<T, L>::TY))
 k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     const unsigned char* __restrict__ act) {
@@ -658,16 +666,13 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     const int tid = threadIdx.x;
     const int ch = blockIdx.x % G::NCHY;
     for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
-    // act (nullable): planes without force are neither read nor written; a
-    // block then takes the planes of active_planes
-    const int nz = act ? 8 : L;
-    const int bc = blockIdx.x / G::NCHY / nz;  // box * 3 + c
-    const int z0 = blockIdx.x / G::NCHY % nz;
+    // ACT: planes without a mark in act are neither read nor written; a block
+    // then takes the planes of active_planes
+    const int bcz = blockIdx.x / G::NCHY;  // (box * 3 + c) * L + z, or ... * 8 + zi
     unsigned long long todo = 1;
-    if (act) todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0);
-    for (; todo != 0; todo &= todo - 1) {
-    const int z = z0 + 8 * (__ffsll(todo) - 1);
-    const int cz = bc * L + z;
+    if constexpr (ACT) todo = active_planes<L>(act + (size_t)(bcz / 24) * L, bcz % 8);
+    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
+    const int cz = ACT ? bcz / 8 * L + bcz % 8 + 8 * (__ffsll(todo) - 1) : bcz;
     const int kx0 = ch * W;
     const int wc = NC - kx0 < W ? NC - kx0 : W;
     cplx<T>* base = A + ((size_t)cz * NC + kx0) * L;
@@ -1037,9 +1042,11 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         else MB_XF(SRC_BOX, false);
     }
 #undef MB_XF
-    MB_LAUNCH(g, K_FFT_Y_FWD, s, (k_y<T, L, false>), 3 * (act ? 8 : L) * G::NCHY * nbox,
-              G::TY, 0, A,
-              tw, (const unsigned char*)act);
+#define MB_Y(ID, INV, AC)                                                                 \
+    MB_LAUNCH(g, ID, s, (k_y<T, L, INV, AC>), 3 * (AC ? 8 : L) * G::NCHY * nbox, G::TY, 0, A, \
+              tw, (const unsigned char*)act)
+    if (act) MB_Y(K_FFT_Y_FWD, false, true);
+    else MB_Y(K_FFT_Y_FWD, false, false);
     const T c0 = steady ? T(0) : (T)(g->d.rho / g->d.dt * N);
     const T c1 = steady ? (T)(g->d.eta * N) : (T)(0.5 * g->d.eta * N);
     const double mv = rhs ? 0.0 : 1.0 / N;
@@ -1060,11 +1067,12 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
             MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, false>), G::NBXY * nbox, G::TXY, 0, A,
                       tw, v_out, act);
     } else {
-        MB_LAUNCH(g, K_FFT_Y_INV, s, (k_y<T, L, true>), 3 * (part ? 8 : L) * G::NCHY * nbox,
-                  G::TY, 0, A, tw, (const unsigned char*)(part ? act : nullptr));
+        if (part) MB_Y(K_FFT_Y_INV, true, true);
+        else MB_Y(K_FFT_Y_INV, true, false);
         MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A,
                   tw, v_out, act, part);
     }
+#undef MB_Y
     return hipGetLastError();
 }
 

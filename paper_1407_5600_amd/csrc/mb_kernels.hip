@@ -938,14 +938,6 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
     return e_sum < e_one ? e_sum : e_one;
 }
 
-// The nearest integer of x (ties up) in one instruction; rint and a conversion
-// are two.
-__device__ __forceinline__ int round_int(float x) {
-    int r;
-    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
 // Elements 2 i, 2 i + 1, and 4 i .. 4 i + 3, of a box.
 template <typename T>
 __device__ __forceinline__ void store2(T* Ea, int i, T a, T b) {
@@ -1140,12 +1132,12 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     }
             if (F32) {
                 if (mode == 0) {
-#define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)round_int((float)(v)))
+#define MB_ADD(i, v) atomicAdd(&acc32[i], (unsigned int)__float2int_rn((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
                 } else {
 #define MB_ADD(i, v) \
-    atomicAdd(&acc[i], (unsigned long long)(long long)round_int((float)(v)))
+    atomicAdd(&acc[i], (unsigned long long)(long long)__float2int_rn((float)(v)))
                     MB_SPREAD_27(MB_ADD)
 #undef MB_ADD
                 }
