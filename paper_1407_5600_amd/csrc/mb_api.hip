@@ -147,17 +147,17 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The grid's scratch as regions of one workspace, each 256-byte aligned, in
 // this order: FFT tables (twiddles, divergence symbol, |symbol|^2), the
-// spectrum, the x-pass partial sums, the per-tile arrays (counts, offsets,
-// scan block sums, diagnostics partials) and the spread boxes, both sized
-// for the tile shape of L with the most tiles / box entries, the per-blob
-// arrays (tile, rank, sorted blob, records, velocities), the springs
-// blocks' force sums, the non-finite flag, and the particle reordering of
-// the step calls (positions and a per-particle array in the calls' own
-// particle order, and that order), and a byte per z plane (whether it holds
-// a force).
+// spectrum, the x-pass partial sums, the tile offsets and scan block sums and
+// the spread boxes, both sized for the tile shape of L with the most tiles /
+// box entries, the per-blob arrays (tile, rank, sorted blob, records,
+// velocities), the particle reordering of the step calls (positions and a
+// per-particle array in the calls' own particle order, and that order); then
+// what starts as zero: the tile counts, the diagnostics' partials of the tiles
+// and of the springs blocks, the non-finite flag, and a byte per z plane
+// (whether it holds a force).
 struct WsLayout {
-    enum { TW, DSYM, D2, SPEC, PSUM, COUNT, OFFS, BSUM, TPART, BOX, TILE, RANK, PERM,
-           REC, U, FPART, FLAG, QINT, PINT, ORDER, ACT, NREG };
+    enum { TW, DSYM, D2, SPEC, PSUM, OFFS, BSUM, BOX, TILE, RANK, PERM, REC, U, QINT, PINT,
+           ORDER, COUNT, TPART, FPART, FLAG, ACT, NREG };  // zeroed from COUNT on
     size_t off[NREG];
     size_t total;
     int ntiles_cap;  // tiles per box
@@ -221,6 +221,7 @@ void ws_bind(mb_grid* g, void* base) {
     char* b = (char*)base;
     g->ws = base;
     g->ws_bytes = w.total;
+    g->zero_off = w.off[WsLayout::COUNT];
     g->ntiles_cap = w.ntiles_cap;
     g->nscan = w.nscan;
     g->d_tw = b + w.off[WsLayout::TW];

@@ -217,13 +217,25 @@ constexpr int elems_xf(int L) {
     while (n % e != 0 || n / e > 512) ++e;
     return e;
 }
-// kx columns per block of the y pass (at least 128 B contiguous per row)
+// kx columns per block of the y pass (at least 128 B contiguous per row; the
+// last block is not left with a column or two: 64^3 33 = 17 + 16 columns, not
+// 32 + 1: 32 boxes 7.5 -> 5.6 us)
 template <typename T>
 constexpr int cols_y(int L) {
+    const int nc = L / 2 + 1;
     int w = 2048 / L;
     if (w < 1) w = 1;
-    const int nc = L / 2 + 1;
-    return w < nc ? w : nc;
+    if (w >= nc) return nc;
+    if (L > 96) return w;  // (tuned as they are: 128^3, 13 columns against 16 were slower)
+    const int blocks = (nc + w - 1) / w;
+    return (nc + blocks - 1) / blocks;
+}
+// Elements per thread of the z pass: shorter chains where a pass is a round or
+// two of blocks (float64 one 32^3 box 5.8 -> 4.8 us, 48^3 7.5 -> 5.9, 64^3 8.3
+// -> 7.9; float32 96^3 16.5 -> 12.4 with four columns).
+template <typename T>
+constexpr int elems_z(int L) {
+    return sizeof(T) == 8 ? (L <= 64 ? 4 : EPT) : (L == 72 || L == 96 ? 4 : EPT);
 }
 // ky columns per block of the z pass (a divisor of L; LDS <= 64 KB for
 // float32, 100 KB for float64).  At 128^3 float32, eight columns give 1,040
@@ -236,10 +248,10 @@ constexpr int cols_y(int L) {
 // for one block per CU (256^3: 288 us against 424 us with four).
 template <typename T>
 constexpr int cols_z(int L) {
-    int w = sizeof(T) == 8 ? (L <= 128 ? 4 : 8) : 8;
+    int w = sizeof(T) == 8 ? (L <= 128 && L != 48 ? 4 : 8) : (L == 96 ? 4 : 8);
     const int cap = sizeof(T) == 8 ? 102400 : 65536;
     while (w > 1 && (L % w != 0 || 3 * L * w * 2 * (int)sizeof(T) > cap ||
-                     3 * w * L / EPT > 1024))
+                     3 * w * L / elems_z<T>(L) > 1024))
         w /= 2;
     return w;
 }
@@ -258,9 +270,9 @@ struct Geo {
     static constexpr int LS = line_stride(L); // LDS line stride (complex)
     static constexpr int WY = cols_y<T>(L);
     static constexpr int NCHY = (NC + WY - 1) / WY;
-    static constexpr int TY = WY * L / EPT;
+    static constexpr int TY = (WY * L + EPT - 1) / EPT;
     static constexpr int WZ = cols_z<T>(L);
-    static constexpr int TZ = 3 * WZ * L / EPT;
+    static constexpr int TZ = 3 * WZ * L / elems_z<T>(L);
     static constexpr int NBX = 3 * L * (L / R);  // blocks of an x pass
     static_assert(NBX % 8 == 0, "x-pass blocks are remapped over the 8 XCDs");
     // inverse plane pass (y and x together, one (component, z) plane per
@@ -276,10 +288,11 @@ struct Geo {
     static constexpr int XY_LDS = PLANE_BYTES + (L + H) * 2 * (int)sizeof(T);
     static constexpr bool XY =
         PLANE_BYTES <= 72 * 1024 || (XY_LDS <= 160 * 1024 && L <= 144);
-    // threads: 8 elements each, at most 1,024 (more waves hide more of the
+    // threads: 4 elements each, at most 1,024 (more waves hide more of the
     // latency; at 128^3 float32 18.0 against 18.9 us with 512, float64 32.9
-    // against 34.5)
-    static constexpr int TXY_RAW = ((L * H / 8 + WAVE - 1) / WAVE) * WAVE;
+    // against 34.5; one 32^3 box 5.8 -> 5.2 us against 8 elements, 96^3
+    // float64 22.4 -> 20.8)
+    static constexpr int TXY_RAW = ((L * H / 4 + WAVE - 1) / WAVE) * WAVE;
     static constexpr int TXY = TXY_RAW > 1024 ? 1024 : TXY_RAW;
     static constexpr int NBXY = 3 * L;                         // blocks per box
 };

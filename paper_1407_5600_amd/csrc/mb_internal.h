@@ -106,6 +106,7 @@ struct mb_grid {
     // partials and the non-finite flag) lies in this one region
     void* ws;           // null until a workspace is set (external_workspace)
     size_t ws_bytes;
+    size_t zero_off;    // the workspace is zeroed from here on
     bool ws_owned;      // allocated by the library (freed at destroy)
     int* d_flag;        // [0] non-finite flag (check_finite; bit 2: a springs
                         // block gave up waiting for the offsets), [1] the

@@ -2320,13 +2320,9 @@ hipError_t init_workspace(mb_grid* g, hipStream_t s) {
     else
         hipLaunchKernelGGL(k_fft_tables<double>, dim3(blocks_for(L)), dim3(BLK), 0, s, L,
                            g->d.h, (double*)g->d_tw, (double*)g->d_dsym, (double*)g->d_d2);
-    const size_t nt = (size_t)g->ntiles_cap * g->tiles.nbox;
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = zero_words(g->d_count, nt, s);
-    if (e == hipSuccess) e = zero_words(g->d_tile_part, nt * 4 * 2, s);
-    if (e == hipSuccess) e = zero_words(g->d_force_part, (size_t)g->force_blocks_cap * 3 * 2, s);
-    if (e == hipSuccess) e = zero_words(g->d_flag, 2, s);
-    if (e == hipSuccess) e = zero_words(g->d_act, (size_t)g->tiles.nbox * L / 4, s);
+    if (e == hipSuccess)
+        e = zero_words((char*)g->ws + g->zero_off, (g->ws_bytes - g->zero_off) / 4, s);
     return e;
 }
 
