@@ -314,25 +314,71 @@ __device__ __forceinline__ void write_record(RecG<T>* __restrict__ rec, T* __res
     perm[pos] = (int)i;
 }
 
+// Scan of the tile counts inside the kernel that places records (n > 0:
+// there is then no scan kernel ahead of it).  Block 0 scans the counts into
+// offs and publishes them by setting *flag = epoch after a device-scope fence;
+// every block reads its offsets only after seeing that (block 0 is dispatched
+// first, so the others' bounded wait ends).
+struct FusedScan {
+    int* count;
+    int* flag;
+    int* err;
+    int n, epoch;
+};
+__device__ __forceinline__ void publish_scan(const FusedScan& sc, int* __restrict__ offs,
+                                             int* wsum) {
+    if (sc.n > 0 && blockIdx.x == 0) {
+        block_scan_counts(sc.count, sc.n, offs, wsum);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // offsets out of this XCD's L2
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(sc.flag, sc.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+// False (and the error bit set) when the offsets did not come; ok: an int of
+// LDS.  Called by the whole block, after which offsets are read with
+// scanned_offset.
+__device__ __forceinline__ bool await_scan(const FusedScan& sc, int* ok) {
+    if (sc.n == 0) return true;
+    if (threadIdx.x == 0) *ok = wait_flag(sc.flag, sc.epoch);
+    __syncthreads();
+    if (!*ok && threadIdx.x == 0) atomicOr(sc.err, 2);
+    return *ok != 0;
+}
+// The offset as block 0 left it in memory (past any stale copy in this XCD's
+// L2).
+__device__ __forceinline__ int scanned_offset(const FusedScan& sc, const int* offs, int tile) {
+    return sc.n == 0 ? offs[tile]
+                     : __hip_atomic_load(&offs[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Records in tile order for given forces (F may be null: interpolation).
 template <typename T>
 __global__ void __launch_bounds__(BLK)
 k_bin_scatter(const double* __restrict__ q, const double* __restrict__ F,
               int64_t M, double inv_h, int L, double inv_vol,
-              const int* __restrict__ offs, const int* __restrict__ tile_of,
+              int* __restrict__ offs, const int* __restrict__ tile_of,
               const int* __restrict__ rank, RecG<T>* __restrict__ rec,
-              T* __restrict__ recf, int* __restrict__ perm, int* __restrict__ flag) {
-    const int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    if (i >= M) return;
+              T* __restrict__ recf, int* __restrict__ perm, int* __restrict__ flag,
+              FusedScan sc) {
+    __shared__ int wsum[BLK / WAVE];
+    __shared__ int scan_ok;
+    publish_scan(sc, offs, wsum);
+    const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
+    const bool own = j < M;
+    const int64_t i = own ? j : 0;
     const Geom g = blob_geom(q, i, inv_h, L);
+    const int t = tile_of[i], rk = rank[i];
     double f[3] = {0.0, 0.0, 0.0};
     if (F) {
         f[0] = F[3 * i];
         f[1] = F[3 * i + 1];
         f[2] = F[3 * i + 2];
     }
-    if (flag && (nonfinite(q + 3 * i, 3) | nonfinite(f, 3))) atomicOr(flag, 1);
-    const int64_t pos = (int64_t)offs[tile_of[i]] + rank[i];
+    if (flag && own && (nonfinite(q + 3 * i, 3) | nonfinite(f, 3))) atomicOr(flag, 1);
+    if (!await_scan(sc, &scan_ok)) return;
+    if (!own) return;
+    const int64_t pos = (int64_t)scanned_offset(sc, offs, t) + rk;
     write_record<T>(rec, F ? recf : nullptr, perm, pos, i, g, f, inv_vol);
 }
 
@@ -492,23 +538,12 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
                   double inv_vol, int* __restrict__ offs,
                   const int* __restrict__ tile_of, const int* __restrict__ rank,
                   RecG<T>* __restrict__ rec, T* __restrict__ recf, int* __restrict__ perm,
-                  double* __restrict__ fpart, int* __restrict__ flag, int* __restrict__ count,
-                  int scan_n, int* __restrict__ sflag, int epoch, int* __restrict__ err) {
+                  double* __restrict__ fpart, int* __restrict__ flag, FusedScan sc) {
     extern __shared__ double smem[];
     __shared__ double red[16 * 3];
     __shared__ int scan_ok;
     const int64_t p0 = (int64_t)blockIdx.x * sp.ppb;
-    // scan_n > 0: block 0 first scans the tile counts into offs (there is
-    // then no scan kernel ahead of this one) and publishes them by setting
-    // *sflag = epoch after a device-scope fence; every block reads its
-    // offsets only after seeing that (block 0 is dispatched first, so the
-    // others' bounded wait ends)
-    if (scan_n > 0 && blockIdx.x == 0) {
-        block_scan_counts(count, scan_n, offs, reinterpret_cast<int*>(red));
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // offsets out of this XCD's L2
-        __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_store(sflag, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    publish_scan(sc, offs, reinterpret_cast<int*>(red));
     const int nblob = (int)((P - p0 < sp.ppb ? P - p0 : sp.ppb) * sp.nb);
     const bool own = (int)threadIdx.x < nblob;
     const int64_t ib = p0 * sp.nb + threadIdx.x;
@@ -520,20 +555,13 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
     // the block's positions are requested before the tile's offset, which
     // waits for the tile; both arrive while the block stages its positions
     const SpringsBlk B = springs_stage(sp, q, Fext, Gblob, p0, springs_npart(sp, P), smem, fe, sp.k,
-                                       [&] { if (scan_n == 0) off = offs[tl]; });
+                                       [&] { if (sc.n == 0) off = offs[tl]; });
     double F[3];
     int64_t i;
     springs_forces<sizeof(T) == 4 ? 1 : 2>(sp, B, fe, F, &i);
-    if (scan_n > 0) {
-        // the offsets as block 0 left them in memory (past any stale copy
-        // in this XCD's L2)
-        if (threadIdx.x == 0) scan_ok = wait_flag(sflag, epoch);
-        __syncthreads();
-        if (!scan_ok) {
-            if (threadIdx.x == 0) atomicOr(err, 2);
-            i = -1;  // no offsets: no records written (the error bit is set)
-        }
-        off = __hip_atomic_load(&offs[tl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (sc.n > 0) {
+        if (!await_scan(sc, &scan_ok)) i = -1;  // no offsets: no records written
+        off = scanned_offset(sc, offs, tl);
     }
     if (i >= 0) {
         const Geom g = blob_geom(B.qs, threadIdx.x, inv_h, L);
@@ -1212,21 +1240,30 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     }
 }
 
-// The field from the boxes (the spreading call of the library).
+// The field from the boxes (the spreading call of the library).  A block takes
+// FOLD_PER BLK nodes of one plane of a component, each thread's loads in flight
+// together; indices in 32 bits (divisions of 64-bit node numbers by L took
+// longer than the loads: 72^3 float64 8.9 -> 6.1 us).
+constexpr int FOLD_PER = 2;
 template <typename T>
 __global__ void __launch_bounds__(BLK)
-k_fold(const T* __restrict__ E, int L, Tiles tl, T* __restrict__ f) {
-    const int64_t N = (int64_t)L * L * L;
-    const int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x;
-    if (i >= 3 * N * tl.nbox) return;
-    const int64_t bc = i / N;  // box * 3 + component
-    const int box = (int)(bc / 3);
-    const int a = (int)(bc - 3 * box);
-    const int64_t rem = i - bc * N;
-    const int x = (int)(rem % L);
-    const int y = (int)((rem / L) % L);
-    const int z = (int)(rem / ((int64_t)L * L));
-    f[i] = box_sum(E + (size_t)box * 3 * tl.n * box_volume(tl), tl, a, x, y, z);
+k_fold(const T* __restrict__ E, int L, int chunks, Tiles tl, T* __restrict__ f) {
+    const int plane = blockIdx.x / chunks;  // (box * 3 + component) * L + z
+    const int z = plane % L, bc = plane / L;
+    const T* Ea = E + (size_t)bc * tl.n * box_volume(tl);
+    T* fp = f + (size_t)plane * L * L;
+    const AxisSrc sz = box_src_z(tl, z);
+    const int i0 = (blockIdx.x - plane * chunks) * (FOLD_PER * BLK) + (int)threadIdx.x;
+    T e[FOLD_PER][4][2];
+#pragma unroll
+    for (int k = 0; k < FOLD_PER; ++k) {
+        const int i = i0 + k * BLK < L * L ? i0 + k * BLK : 0;
+        const int y = i / L, x = i - y * L;
+        box_entries(Ea, box_src_x(tl, x), box_src_y(tl, y), sz, e[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < FOLD_PER; ++k)
+        if (i0 + k * BLK < L * L) fp[i0 + k * BLK] = box_entries_sum(e[k]);
 }
 
 // Sum of the three nodes of a row with their weights; the multiply-adds of
@@ -2124,6 +2161,20 @@ static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M
     return hipGetLastError();
 }
 
+// The scan of the tile counts for a kernel that places records, with its
+// launch number (none: n = 0).
+static FusedScan fused_scan(mb_grid* g, bool scan) {
+    FusedScan sc{};
+    if (!scan) return sc;
+    sc.count = g->d_count;
+    sc.flag = g->d_flag + 1;
+    sc.err = g->d_flag;
+    sc.n = g->tiles.n * g->tiles.nbox;
+    sc.epoch = (int)(++g->scan_epoch & 0x7fffffff);
+    if (sc.epoch == 0) sc.epoch = (int)(++g->scan_epoch & 0x7fffffff);
+    return sc;
+}
+
 template <typename T>
 hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s, bool counted,
                      bool scan) {
@@ -2216,11 +2267,13 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
         e = blob_axpy(3 * M, F2, f2scale, F, Fsum, s);
         F = Fsum;
     }
-    if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s);
+    const bool fuse = M > 0 && fused_scan_ok(g, s);  // the scan in the scattering kernel
+    if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s, false, !fuse);
     if (e != hipSuccess || M == 0) return e;
+    const FusedScan scan = fused_scan(g, fuse);
     MB_LAUNCH(g, K_BIN_SCATTER, s, k_bin_scatter<T>, blocks_for(M), BLK, 0, q, F,
               M, 1.0 / h, g->L, sc, g->d_offs, g->d_tile, g->d_rank,
-              rec_geo<T>(g), rec_force<T>(g), g->d_perm, finite_flag(g));
+              rec_geo<T>(g), rec_force<T>(g), g->d_perm, finite_flag(g), scan);
     g->perm_m = M;
     return hipGetLastError();
 }
@@ -2244,17 +2297,11 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
         return hipGetLastError();
     }
     const double h = g->d.h;
-    int scan_n = 0, epoch = 0;
-    if (scan) {
-        scan_n = g->tiles.n * g->tiles.nbox;
-        epoch = (int)(++g->scan_epoch & 0x7fffffff);
-        if (epoch == 0) epoch = (int)(++g->scan_epoch & 0x7fffffff);
-    }
+    const FusedScan sc = fused_scan(g, scan);
     MB_LAUNCH(g, K_SPRINGS_SCATTER, s, k_springs_scatter<T>, springs_blocks(sp, P), BLK,
               springs_lds(sp), sp, q, Fext, Gblob, P, 1.0 / h, g->L, 1.0 / (h * h * h), g->d_offs,
               g->d_tile, g->d_rank, rec_geo<T>(g), rec_force<T>(g), g->d_perm,
-              force_sums ? g->d_force_part : nullptr, finite_flag(g), g->d_count, scan_n,
-              g->d_flag + 1, epoch, g->d_flag);
+              force_sums ? g->d_force_part : nullptr, finite_flag(g), sc);
     g->perm_m = M;
     return hipGetLastError();
 }
@@ -2431,8 +2478,9 @@ bool box_shape_supported(int sx, int sy, int sz, int tx, int ty, int tz) {
 
 template <typename T>
 hipError_t fold_boxes(mb_grid* g, T* f, hipStream_t s) {
-    MB_LAUNCH(g, K_FOLD, s, k_fold<T>, blocks_for(3 * g->N * g->tiles.nbox), BLK, 0,
-              (const T*)g->d_box, g->L, g->btiles, f);
+    const int chunks = (g->L * g->L + FOLD_PER * BLK - 1) / (FOLD_PER * BLK);
+    MB_LAUNCH(g, K_FOLD, s, k_fold<T>, 3 * g->tiles.nbox * g->L * chunks, BLK, 0,
+              (const T*)g->d_box, g->L, chunks, g->btiles, f);
     return hipGetLastError();
 }
 
