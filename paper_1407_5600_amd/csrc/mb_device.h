@@ -359,6 +359,21 @@ __device__ __forceinline__ void st32(T* __restrict__ base, unsigned i, const T& 
     *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T)) = x;
 }
 
+// The same past the caches' ordinary replacement, for data that is used once
+// or only after more than the L2s hold has passed.
+template <typename T>
+__device__ __forceinline__ cplx<T> ld32_once(const cplx<T>* __restrict__ base, unsigned i) {
+    typedef T V __attribute__((ext_vector_type(2)));
+    const V x = __builtin_nontemporal_load(reinterpret_cast<const V*>(
+        reinterpret_cast<const char*>(base) + i * (unsigned)sizeof(cplx<T>)));
+    return cplx<T>{x.x, x.y};
+}
+template <typename T>
+__device__ __forceinline__ void st32_once(T* __restrict__ base, unsigned i, T x) {
+    __builtin_nontemporal_store(
+        x, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T)));
+}
+
 // A hook that does nothing (default of the "after the loads are issued"
 // callbacks).
 struct NoOp {

@@ -833,6 +833,14 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
         T* __restrict__ vout, unsigned char* __restrict__ act, int part_out) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::RI, NL = G::NLI, NTHR = G::TXI, LS = G::LS;
+    // The spectrum is not read again, and before the field is, more than the
+    // L2s hold passes through them (this pass runs from 192^3 on: 85 MB): both
+    // go past the caches' replacement where rows are whole lines.  256^3
+    // float32: this pass 78 -> 66 us, the interpolation after it, whose boxes of
+    // nodes overlap in the caches, 234 -> 213; a 192^3 float64 solve's forward
+    // x pass, of inputs that stay, 150 -> 142.  Rows that split lines lose
+    // (216^3 float64: this pass 106 -> 115, a dense step +0.7%).
+    constexpr bool ONCE = L * sizeof(T) % 128 == 0;
     constexpr int SS = NC + 1;  // staging row stride
     __shared__ cplx<T> stg[R * SS];
     __shared__ cplx<T> buf[NL * LS];
@@ -860,7 +868,8 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
             const int e = tid + k * NTHR;
             const int kx = e / R;
             const int rl = e - kx * R;
-            ld[k] = ld32(in, (unsigned)(e < NC * R ? kx * L + rl : 0));
+            const unsigned i = (unsigned)(e < NC * R ? kx * L + rl : 0);
+            ld[k] = ONCE ? ld32_once(in, i) : ld32(in, i);
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -892,8 +901,14 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     };
     T* out = vout + ((size_t)cz * L + y0) * L;
     auto st = [out](int line, int x, cplx<T> zz) {
-        st32(out, (unsigned)((2 * line) * L + x), zz.x);
-        st32(out, (unsigned)((2 * line + 1) * L + x), zz.y);
+        const unsigned i = (unsigned)((2 * line) * L + x);
+        if (ONCE) {
+            st32_once(out, i, zz.x);
+            st32_once(out, i + L, zz.y);
+        } else {
+            st32(out, i, zz.x);
+            st32(out, i + L, zz.y);
+        }
     };
     line_fft_io<T, L, true, NL, LS, NTHR, false, false, false>(buf, tws, tid, ld, st);
 }

@@ -966,14 +966,22 @@ __device__ __forceinline__ int fixed_exponent(double fmax, int n, double lim_sum
     return e_sum < e_one ? e_sum : e_one;
 }
 
-// Elements 2 i, 2 i + 1, and 4 i .. 4 i + 3, of a box.
-template <typename T>
-__device__ __forceinline__ void store2(T* Ea, int i, T a, T b) {
-    if constexpr (sizeof(T) == 4) reinterpret_cast<float2*>(Ea)[i] = make_float2(a, b);
-    else reinterpret_cast<double2*>(Ea)[i] = make_double2(a, b);
+// Elements 2 i, 2 i + 1, and 4 i .. 4 i + 3, of a box; ONCE: past the caches'
+// replacement (spread_boxes).
+template <bool ONCE, typename V>
+__device__ __forceinline__ void store_box(V* p, V x) {
+    if (ONCE) __builtin_nontemporal_store(x, p);
+    else *p = x;
 }
-__device__ __forceinline__ void store4(float* Ea, int i, float4 x) {
-    reinterpret_cast<float4*>(Ea)[i] = x;
+template <bool ONCE, typename T>
+__device__ __forceinline__ void store2(T* Ea, int i, T a, T b) {
+    typedef T V __attribute__((ext_vector_type(2)));
+    store_box<ONCE>(reinterpret_cast<V*>(Ea) + i, V{a, b});
+}
+template <bool ONCE>
+__device__ __forceinline__ void store4(float* Ea, int i, const float (&v)[4]) {
+    typedef float V __attribute__((ext_vector_type(4)));
+    store_box<ONCE>(reinterpret_cast<V*>(Ea) + i, V{v[0], v[1], v[2], v[3]});
 }
 
 // Spreading: one block per box tile (FX x FY x FZ binning tiles, btl), one
@@ -1011,7 +1019,7 @@ constexpr int spread_threads(int f) {
     return f * BLK < cap ? f * BLK : cap;
 }
 
-template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ>
+template <typename T, int TX, int TY, int TZ, int FX, int FY, int FZ, bool ONCE>
 __global__ void __launch_bounds__(spread_threads<T>(FX * FY * FZ))
 k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
          const int* __restrict__ offs, int L, Tiles btl, Tiles tl, int det,
@@ -1043,7 +1051,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
     if (total == 0) {  // no records: an empty box
         for (int a = comp < 0 ? 0 : comp; a <= (comp < 0 ? 2 : comp); ++a) {
             T* Ea = E + ((size_t)(tb.box * 3 + a) * btl.n + tile) * EVP;
-            for (int i = threadIdx.x; i < EVP / 2; i += NT) store2<T>(Ea, i, T(0), T(0));
+            for (int i = threadIdx.x; i < EVP / 2; i += NT) store2<false>(Ea, i, T(0), T(0));
         }
         return;
     }
@@ -1212,8 +1220,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
                 float val[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) val[c] = fine ? x[c] * sc : ldexpf(x[c], -e);
-                store4(reinterpret_cast<float*>(Ea), i,
-                       make_float4(val[0], val[1], val[2], val[3]));
+                store4<ONCE>(reinterpret_cast<float*>(Ea), i, val);
             }
         } else {
             // (16 bytes of sums a thread: with four each, 32 bytes apart, the
@@ -1232,7 +1239,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
                         val[c] = (T)accd[j];
                 }
                 reinterpret_cast<uint4*>(acc)[i] = make_uint4(0u, 0u, 0u, 0u);
-                store2<T>(Ea, i, val[0], val[1]);
+                store2<ONCE>(Ea, i, val[0], val[1]);
             }
         }
         __syncthreads();
@@ -2455,16 +2462,29 @@ hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
     constexpr int kSplitBoxTiles = 256;
     const int nbt = b.n * b.nbox;
     const dim3 grid(nbt, nbt <= kSplitBoxTiles ? 3 : 1);
+    // Boxes of more than half the 256 MB last-level cache would push the field
+    // out of it and be pushed out themselves before the x pass reads them:
+    // those of tiles with records go past its replacement (256^3 float32, 355
+    // MB, phi = 0.2: spreading 153 -> 151 us, the x pass after it 201 -> 188;
+    // 192^3 float64, 299 MB, 122 -> 107 and 193 -> 176; 192^3 float32, 150 MB,
+    // 61 -> 58 and 91 -> 84).  Smaller ones are found there (128^3 float64, 89
+    // MB: the x pass 34.7 -> 50.5 if not), and empty boxes cost more so
+    // (192^3, 100 particles: spreading 23 -> 37).
+    const bool once = box_elems(b) * sizeof(T) > (size_t)128 << 20;
+#define MB_SPREAD(SX, SY, SZ, FX, FY, FZ, ONCE)                                          \
+    MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ, ONCE>), grid,         \
+              spread_threads<T>(FX * FY * FZ), 0, rec_geo<T>(g), rec_force<T>(g),        \
+              g->d_offs, g->L, b, t, g->d.deterministic, (T*)g->d_box)
 #define MB_BOX(SX, SY, SZ, FX, FY, FZ)                                                   \
     if (!ok && b.tx == SX && b.ty == SY && b.tz == SZ && SX == FX * t.tx &&              \
         SY == FY * t.ty && SZ == FZ * t.tz) {                                            \
-        MB_LAUNCH(g, K_SPREAD, s, (k_spread<T, SX, SY, SZ, FX, FY, FZ>), grid,           \
-                  spread_threads<T>(FX * FY * FZ), 0, rec_geo<T>(g), rec_force<T>(g),    \
-                  g->d_offs, g->L, b, t, g->d.deterministic, (T*)g->d_box);              \
+        if (once) MB_SPREAD(SX, SY, SZ, FX, FY, FZ, true);                               \
+        else MB_SPREAD(SX, SY, SZ, FX, FY, FZ, false);                                   \
         ok = true;                                                                       \
     }
     MB_BOX_SHAPES(MB_BOX)
 #undef MB_BOX
+#undef MB_SPREAD
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
