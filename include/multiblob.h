@@ -305,7 +305,9 @@ mb_status mb_spring_forces_ext(const mb_springs* springs, int64_t nparticles,
 /* nsteps steps of each of ngrids grids (as mb_step_ext, no per-step
  * outputs), with one step of every grid captured once into a HIP graph and
  * the graph launched nsteps times on a private stream ordered after
- * `stream`; returns when the steps are done.  Launch-bound workloads (many
+ * `stream`; returns when the steps are done.  (With a steady grid of at most
+ * 256 blobs per box the last step is launched by itself: the ones before it
+ * form the field only where its blobs are.)  Launch-bound workloads (many
  * small boxes, several size classes) then pay one graph launch per step.
  * Arrays per grid as in mb_step_ext (Fext and F_blob entries may be NULL).
  * Grids with no blobs are allowed; timing hooks are off during the capture. */

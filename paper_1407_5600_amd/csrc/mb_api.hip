@@ -902,7 +902,8 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
             e = hipGraphLaunch(exec, cs);
     }
     if (tail && e == hipSuccess && st == MB_OK) st = one_step(cs, true);
-    if (e == hipSuccess && st == MB_OK) e = hipStreamSynchronize(cs);
+    // (also after a step that failed: the replays before it still use the graph)
+    if (e == hipSuccess) e = hipStreamSynchronize(cs);
     for (int i = 0; i < ngrids; ++i) grids[i]->timing = timing[i];
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
