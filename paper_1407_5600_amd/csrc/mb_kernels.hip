@@ -1250,7 +1250,7 @@ k_spread(const RecG<T>* __restrict__ rec, const T* __restrict__ recf,
 // The field from the boxes (the spreading call of the library).  A block takes
 // FOLD_PER BLK nodes of one plane of a component, each thread's loads in flight
 // together; indices in 32 bits (divisions of 64-bit node numbers by L took
-// longer than the loads: 72^3 float64 8.9 -> 6.1 us).
+// longer than the loads: 72^3 float64 9.5 -> 7.5 us).
 constexpr int FOLD_PER = 2;
 template <typename T>
 __global__ void __launch_bounds__(BLK)
@@ -2464,10 +2464,10 @@ hipError_t spread_boxes(mb_grid* g, hipStream_t s) {
     const dim3 grid(nbt, nbt <= kSplitBoxTiles ? 3 : 1);
     // Boxes of more than half the 256 MB last-level cache would push the field
     // out of it and be pushed out themselves before the x pass reads them:
-    // those of tiles with records go past its replacement (256^3 float32, 355
-    // MB, phi = 0.2: spreading 153 -> 151 us, the x pass after it 201 -> 188;
-    // 192^3 float64, 299 MB, 122 -> 107 and 193 -> 176; 192^3 float32, 150 MB,
-    // 61 -> 58 and 91 -> 84).  Smaller ones are found there (128^3 float64, 89
+    // those of tiles with records go past its replacement (256^3 float32, 337
+    // MB, phi = 0.4: spreading 153 -> 151 us, the x pass after it 201 -> 188;
+    // 192^3 float64, 284 MB, 122 -> 107 and 193 -> 176; 192^3 float32, 142 MB,
+    // 61 -> 58 and 91 -> 84).  Smaller ones are found there (128^3 float64, 84
     // MB: the x pass 34.7 -> 50.5 if not), and empty boxes cost more so
     // (192^3, 100 particles: spreading 23 -> 37).
     const bool once = box_elems(b) * sizeof(T) > (size_t)128 << 20;
