@@ -371,7 +371,8 @@ mb_status mb_step_adjoint(mb_grid* grid, const mb_springs* springs,
  * mb_springs_create).  Each call rebuilds the FFT tables and clears the
  * counters in the array on `stream`, by kernels, then steps; results equal
  * mb_step's on a grid of the same description.  MB_ERR_UNSUPPORTED when
- * mb_workspace_size(desc, 1) exceeds MB_NOALLOC_SCRATCH_BYTES (for example
+ * mb_workspace_size(desc, 1) exceeds MB_NOALLOC_SCRATCH_BYTES by more than the
+ * 32 KiB of padding that the array has beside them (for example
  * L <= 64 with ~10^5 blobs fits; 128^3 does not).  All calls on one GPU
  * share its array: calls that overlap on one GPU (different streams or
  * threads) race and give undefined results. */

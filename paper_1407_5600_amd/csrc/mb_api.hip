@@ -1228,8 +1228,13 @@ mb_status mb_grid_kernel_times(mb_grid* g, void* stream, double* ms_out,
 
 // The scratch of mb_step_noalloc: one array per device (each GPU the library
 // runs on holds it until the process ends).  Host code never uses its name
-// as an address: the device address comes from hipGetSymbolAddress.
-static __device__ __align__(256) unsigned char scratch[MB_NOALLOC_SCRATCH_BYTES];
+// as an address: the device address comes from hipGetSymbolAddress.  The
+// spare bytes hold what the layout takes for the 16-byte stores of the boxes,
+// the x pass's partial sums of its smaller blocks and the marks of the planes
+// (at most 31,488 bytes in a grid of up to the documented size: 72^3 float64),
+// so that these refuse no grid that fits without them.
+constexpr size_t kScratchSpare = 32 << 10;
+static __device__ __align__(256) unsigned char scratch[MB_NOALLOC_SCRATCH_BYTES + kScratchSpare];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -1265,7 +1270,7 @@ mb_status mb_step_noalloc(const mb_grid_desc* desc, const mb_springs* sp, int64_
     if (ds != MB_OK) return ds;
     if (P < 0 || P * sp->nb > d.max_blobs) return MB_ERR_INVALID;
     const WsLayout w = ws_layout(d, 1);
-    if (w.total > MB_NOALLOC_SCRATCH_BYTES) return MB_ERR_UNSUPPORTED;
+    if (w.total > MB_NOALLOC_SCRATCH_BYTES + kScratchSpare) return MB_ERR_UNSUPPORTED;
     int dev = 0;
     if (!device_ok(&dev)) return MB_ERR_DEVICE;
     void* base = nullptr;

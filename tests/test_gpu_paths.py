@@ -291,3 +291,26 @@ def test_steady_steps_of_few_blobs_leave_the_whole_field(torch_cuda, nb, L, P, p
         for other in out[1:]:
             for a, b in zip(out[0], other):
                 assert np.array_equal(a, b)
+
+
+def test_step_noalloc_at_the_scratch_size(torch_cuda):
+    """72^3 float64 with 5,915 blobs fills the static scratch but for the
+    padding; its step equals a grid's bit for bit."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    from paper_1407_5600_amd.binding import step_noalloc
+    say("noalloc at the scratch size")
+    L, P = 72, 455
+    w = inputs.random_suspension(L, P, 3)
+    sp = Springs(w.nb, w.pa, w.pb, w.r0, w.k)
+    g = Grid(L, max_blobs=w.M)
+    out = []
+    for noalloc in (False, True):
+        q, v, F = dev(torch, w.q), g.field(), dev(torch, w.Fext)
+        if noalloc:
+            step_noalloc(sp, q, v, F, L=L)
+        else:
+            g.step(sp, q, v, F)
+        out.append([q.cpu().numpy(), v.cpu().numpy()])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
