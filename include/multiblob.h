@@ -115,7 +115,8 @@ typedef enum {
  *
  * deterministic = 1: every result is the same bit for bit from run to run.
  * Spreading always sums in fixed point (independent of the order of the
- * blobs and of the atomic additions); the one order-dependent path, float64
+ * blobs and of the atomic additions; so do the steps of boxes with few blobs,
+ * whose solve forms the force from the blobs itself); the one order-dependent path, float64
  * LDS atomics for a float64 spreading box tile (16^3 cells) of more than
  * 2^20 blobs, is then replaced by two 64-bit fixed-point sums (the
  * contributions, then their rounding remainders; up to 2^25 blobs in one

@@ -273,6 +273,26 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
+// Maximum of a non-negative 32-bit value over the wave, in its last lane: six
+// register moves between lanes (an LDS maximum of 256 threads at one address
+// took 2 us of the 4.4 of a kernel).
+__device__ __forceinline__ unsigned wave_max_last(unsigned v) {
+#define MB_DPP(ctrl)                                                                      \
+    do {                                                                                  \
+        const unsigned o_ =                                                               \
+            (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, (ctrl), 0xf, 0xf, false);    \
+        v = o_ > v ? o_ : v;                                                              \
+    } while (0)
+    MB_DPP(0x111);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+    MB_DPP(0x112);
+    MB_DPP(0x114);
+    MB_DPP(0x118);
+    MB_DPP(0x142);  // row_bcast 15, 31: lane 63
+    MB_DPP(0x143);
+#undef MB_DPP
+    return v;
+}
+
 // Sum (or max) of one value per thread; the result is valid in every
 // thread.  `scratch` holds at least 16 doubles.  Contains barriers.
 template <bool MAX>

@@ -311,7 +311,8 @@ enum : int { SRC_FIELD, SRC_BOX, SRC_BOX_ADD, SRC_REC };
 // the force is all there is): whether each z plane of each box holds any
 // force, as the binning marked it; the x and y passes pass over planes without
 // one and the z pass takes them as zero (two particles in 64^3 lie in about 7
-// of the 64 planes).
+// of the 64 planes).  fexp: per box, the exponent of the fixed-point sums its
+// force is formed in (FixedSum), as the binning left it.
 template <typename T>
 struct ForceSrc {
     const T* add;
@@ -319,11 +320,47 @@ struct ForceSrc {
     const T* recf;
     int mbox;
     const unsigned char* act;
+    const int* fexp;
+};
+
+// Sum of the contributions w s of records to a node in fixed point, so that it
+// does not depend on their order, as in the spreading.  s is scaled by 2^e, e
+// the box's exponent (box_exponent): |w s| < 2^51.  Adding 1.5 2^52 then leaves
+// the contribution rounded to an integer in the low bits (one fused
+// multiply-add), and the bits are summed as 64-bit integers (at most kSmallBlobs
+// of them).  float64: the rounding remainder, exact by a second fused
+// multiply-add, is summed the same way at 2^-40 of the first quantum, so that
+// the sum is at least as close as one in float64 (the first sum alone is held
+// to 2^-52 of the box's largest force).
+template <typename T>
+struct FixedSum {
+    static constexpr double MAGIC = 0x1.8p52;
+    static constexpr int LOW = 40;
+    unsigned long long hi = 0, lo = 0;  // (modulo 2^64)
+    unsigned n = 0;
+    __device__ __forceinline__ void add(T w, T s) {
+        const double y = fma((double)w, (double)s, MAGIC);
+        hi += (unsigned long long)__double_as_longlong(y);
+        if constexpr (sizeof(T) == 8) {
+            const double r = fma(w, s, MAGIC - y);
+            lo += (unsigned long long)__double_as_longlong(fma(r, (double)(1ll << LOW), MAGIC));
+        }
+        ++n;
+    }
+    __device__ __forceinline__ T value(int e) const {
+        // (a force that is not finite: every node of the box)
+        if (e == kExpNonfinite) return (T)__builtin_nan("");
+        const unsigned long long m = n * 0x4338000000000000ull;  // n times MAGIC's bits
+        double x = (double)(long long)(hi - m);
+        if constexpr (sizeof(T) == 8)
+            x = fma((double)(long long)(lo - m), 1.0 / (double)(1ll << LOW), x);
+        return (T)ldexp(x, -e);
+    }
 };
 
 // A record as the rows of one plane see it: its first nodes along x and y
 // (wrapped), the x weights, and the y weights times the z weight of the plane
-// times the force.
+// times the force, scaled by 2^e.
 template <typename T>
 struct RecLine {
     T wx[3], wyf[3];
@@ -331,13 +368,13 @@ struct RecLine {
 };
 
 // The records of a box (forces recf) with nodes of component a in plane z and
-// in any of the R rows from y0, in record order, into list; returns their
-// number.  Each thread looks at one record a round (a round takes NTHR); cnt:
+// in any of the R rows from y0, in record order, into list, the forces times
+// 2^e2; returns their number.  Each thread looks at one record a round (a round takes NTHR); cnt:
 // an int per wave.  Called by the whole block; ends with a barrier.
 template <typename T, int L, int R, int NTHR>
 __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
                                              const T* __restrict__ recf, int mbox, int a, int z,
-                                             int y0, RecLine<T>* list, int* cnt) {
+                                             int y0, int e2, RecLine<T>* list, int* cnt) {
     constexpr int NW = (NTHR + WAVE - 1) / WAVE;
     const int tid = threadIdx.x, wave = tid / WAVE;
     int n = 0;
@@ -381,9 +418,8 @@ __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
             e->wx[0] = wx[0];
             e->wx[1] = wx[1];
             e->wx[2] = wx[2];
-            e->wyf[0] = wy[0] * f;
-            e->wyf[1] = wy[1] * f;
-            e->wyf[2] = wy[2] * f;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) e->wyf[k] = ldexp(wy[k] * f, e2);
             e->xs = xs;
             e->ys = ys;
         }
@@ -399,8 +435,8 @@ __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
 // the other rows of the block cost next to nothing.
 template <typename T, int L, int NTHR>
 __device__ __forceinline__ void list_force(const RecLine<T>* list, int n, int x, int y, int y0,
-                                           int rlo, int rhi, T out[2]) {
-    T f0 = T(0), f1 = T(0);
+                                           int rlo, int rhi, int e2, T out[2]) {
+    FixedSum<T> f0, f1;
     const int left = NTHR - (int)(threadIdx.x - threadIdx.x % WAVE);
     const int cw = NTHR % WAVE == 0 || left >= WAVE ? WAVE : left;  // the wave's lanes
     for (int k0 = 0; k0 < n; k0 += cw) {
@@ -417,13 +453,13 @@ __device__ __forceinline__ void list_force(const RecLine<T>* list, int n, int x,
             const int dy1 = dy == L - 1 ? 0 : dy + 1;
             if (dx < 3) {
                 const T w = e->wx[dx];
-                if (dy < 3) f0 = fma(w, e->wyf[dy], f0);
-                if (dy1 < 3) f1 = fma(w, e->wyf[dy1], f1);
+                if (dy < 3) f0.add(w, e->wyf[dy]);
+                if (dy1 < 3) f1.add(w, e->wyf[dy1]);
             }
         }
     }
-    out[0] = f0;
-    out[1] = f1;
+    out[0] = f0.value(e2);
+    out[1] = f1.value(e2);
 }
 
 // Planes of a box with marks act, dealt out to blocks eight apart (zi + 8 k:
@@ -489,11 +525,12 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     [[maybe_unused]] const T* add =
         (ADD || REC) && mk.add ? mk.add + (size_t)box * 3 * L * L * L : nullptr;
     __shared__ RecLine<T> list[REC ? kSmallBlobs : 1];
-    int nlist = 0;
+    int nlist = 0, e2 = 0;
     if constexpr (REC) {
+        e2 = mk.fexp[box];
         const size_t b0 = (size_t)box * mk.mbox;
         nlist = plane_records<T, L, R, NTHR>(mk.rec + b0, mk.recf + 3 * b0, mk.mbox, comp, z, y0,
-                                             list, reinterpret_cast<int*>(red));
+                                             e2, list, reinterpret_cast<int*>(red));
     }
     // KG iterations (2 KG nodes) per round: all loads of a round, the box
     // entries included (box_entries: loads only, in uniform branches), are
@@ -604,7 +641,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
                 const int w0 = __builtin_amdgcn_readfirstlane(e);  // the wave's first element
                 const int w1 = w0 + WAVE - 1 < NL * L - 1 ? w0 + WAVE - 1 : NL * L - 1;
                 list_force<T, L, NTHR>(list, nlist, x, y0 + 2 * line, y0, 2 * (w0 / L),
-                                       2 * (w1 / L) + 1, lf);
+                                       2 * (w1 / L) + 1, e2, lf);
             }
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
@@ -1048,6 +1085,7 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         mk.rec = rec_geo<T>(g);
         mk.recf = rec_force<T>(g);
         mk.mbox = F.mbox;
+        mk.fexp = g->d_rank;
         if (F.planes) mk.act = g->d_act;
     }
     unsigned char* act = mk.act ? g->d_act : nullptr;

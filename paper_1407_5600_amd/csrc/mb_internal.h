@@ -134,7 +134,8 @@ struct mb_grid {
     int* d_bsum;        // scan block sums
     int nscan;          // scan blocks
     int* d_tile;        // [max_blobs] tile of each blob
-    int* d_rank;        // [max_blobs] place among its tile's blobs
+    int* d_rank;        // [max_blobs] place among its tile's blobs; small boxes: [nbox] exponent
+                        // of each box's fixed-point force sums
     int* d_perm;        // [max_blobs] blob of each sorted record
     int64_t perm_m;     // d_perm is a permutation of [0, perm_m) (-1: none)
     bool binned_small;  // the last binning was by box (small_boxes)
@@ -213,6 +214,7 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
 // number of boxes, so that a batch steps as its boxes would alone.
 constexpr int kSmallBlobs = 256;
 constexpr int kSmallTiles = 4096;  // 16 KB of LDS counts
+constexpr int kExpNonfinite = 1 << 20;  // box exponent: a force of the box is not finite
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp);
 // Springs and records of small boxes, with tiles by tile (for the spreading and
 // the interpolation that forms sums over the tiles); mark: also the z planes

@@ -590,14 +590,24 @@ k_springs_scatter(SpringsDev sp, const double* __restrict__ q,
 // particles: 4.4 + 7.7 + 4.3 + 5.1 us).  SPRINGS: the forces are the springs
 // and external forces, as k_springs_scatter; else F (nullable: no forces; with
 // Fsum the force is F2 + f2scale F, also stored there).  act (nullable): marks
-// the z planes of the box that hold nodes of its blobs.
+// the z planes of the box that hold nodes of its blobs.  fexp[box]: the
+// exponent in which the x pass sums the box's forces (box_exponent).
 struct BoxBin {
     int n;       // tiles per box
     int mbox;    // blobs per box
     int64_t M;
     int* offs;
     unsigned char* act;
+    int* fexp;
 };
+
+// The e with |w F h^-3| 2^e < 2^51 for every product w of kernel weights (at
+// most (2/3)^3 < 2^-1.7) and every force of a box, from the high word of its
+// largest |F h^-3| in float64; kExpNonfinite for an infinity or NaN.
+__device__ __forceinline__ int box_exponent(unsigned hi) {
+    const int b = (int)(hi >> 20);  // biased exponent: |F h^-3| < 2^(b - 1022)
+    return b == 2047 ? kExpNonfinite : 51 - ((b > 0 ? b : 1) - 1023);
+}
 
 template <typename T, bool SPRINGS>
 __global__ void __launch_bounds__(BLK)
@@ -608,6 +618,7 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
           double* __restrict__ fpart, int* __restrict__ flag) {
     extern __shared__ double smem[];
     __shared__ double red[16 * 3];
+    __shared__ unsigned fmax_hi[BLK / WAVE];
     int* wsum = reinterpret_cast<int*>(red);
     int* hist = reinterpret_cast<int*>(smem);  // [n], before the springs' staging
     double* rest = smem + (bb.offs ? (bb.n + 1) / 2 : 0);
@@ -658,10 +669,26 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
         }
         if (flag && (nonfinite(x, 3) | nonfinite(F, 3))) atomicOr(flag, 1);
     }
+    if (SPRINGS || Fext) {
+        unsigned m = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const unsigned h =
+                (unsigned)__double2hiint((double)(T)(F[b] * inv_vol)) & 0x7fffffffu;
+            m = own && h > m ? h : m;
+        }
+        m = wave_max_last(m);
+        if (tid % WAVE == WAVE - 1) fmax_hi[tid / WAVE] = m;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int w = 0; w < BLK / WAVE; ++w) m = fmax_hi[w] > m ? fmax_hi[w] : m;
+            bb.fexp[box] = box_exponent(m);
+        }
+    }
     int64_t pos = i0 + tid;
     if (sort) {  // (uniform over the grid)
-        // rank: the blobs before this one in its tile, so that the order of
-        // the records depends on the positions alone (the x pass sums in it)
+        // rank: the blobs before this one in its tile
         __shared__ __align__(16) int tiles_of[BLK];
         tiles_of[tid] = own ? t : -1;
         if (own) atomicAdd(&hist[t], 1);
@@ -2158,6 +2185,7 @@ static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M
     bb.M = M;
     bb.offs = sort ? g->d_offs : nullptr;
     bb.act = mark ? g->d_act : nullptr;
+    bb.fexp = g->d_rank;
     const size_t lds =
         (sort ? (size_t)((bb.n + 1) / 2) * sizeof(double) : 0) + (SPRINGS ? springs_lds(sp) : 0);
     MB_LAUNCH(g, kid, s, (k_bin_box<T, SPRINGS>), g->tiles.nbox, BLK, lds, sp, bb, g->tiles, q, F,

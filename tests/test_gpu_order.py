@@ -1,0 +1,102 @@
+"""Results that do not depend on the order of the blobs, on whether diagnostics
+are asked for, or on how steps are grouped into calls; and the scale of the
+fixed-point sums that make it so."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+NB = 13
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1407_5600_amd  # noqa: F401  (loads the library, fails loudly)
+    return torch
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def chains(rng, P, L):
+    """P chains of NB blobs in a corner of the box, so that many of them share
+    nodes."""
+    body = rng.uniform(-1.0, 1.0, size=(NB, 3))
+    q = rng.uniform(0.0, min(L, 8), size=(P, 1, 3)) + body
+    pa = np.arange(NB - 1, dtype=np.int32)
+    r0 = np.linalg.norm(body[1:] - body[:-1], axis=1)
+    return q + rng.uniform(-0.05, 0.05, size=q.shape), (NB, pa, pa + 1, r0, 10.0)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("mode", ["unsteady", "steady"])
+@pytest.mark.parametrize("L,P", [(16, 3), (32, 19), (48, 19), (32, 20), (96, 19)])
+def test_step_independent_of_order_diagnostics_and_calls(torch_cuda, L, P, mode, prec):
+    """Three steps of 39 to 260 blobs (both sides of the 256 whose forces are
+    formed in the solve) in one call, in three, with diagnostics and without,
+    with the particles in another order: the same bit for bit."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    rng = np.random.default_rng(100 * L + P)
+    q0, spr = chains(rng, P, L)
+    F0 = rng.standard_normal((P, 3))
+    v0 = rng.standard_normal((3, L, L, L))
+    for scheme in ("euler", "midpoint"):
+        out = []
+        for name, order, calls, diag in (("plain", 1, 1, False), ("diagnostics", 1, 1, True),
+                                         ("calls", 1, 3, False), ("calls, diagnostics", 1, 3, True),
+                                         ("order", -1, 1, False), ("order, diagnostics", -1, 1, True)):
+            say("order", L, P, mode, prec, scheme, name)
+            g = Grid(L, precision=prec, mode=mode, scheme=scheme, max_blobs=P * NB)
+            q, F = dev(torch, q0[::order].reshape(-1, 3)), dev(torch, F0[::order])
+            v = dev(torch, v0).to(g.field_dtype)
+            u = torch.zeros_like(q)
+            d = torch.zeros(7, dtype=torch.float64, device="cuda") if diag else None
+            for _ in range(calls):
+                g.step(Springs(*spr), q, v, F, 3 // calls, u_out=u, diag_out=d)
+            out.append([v.cpu().numpy()] + [x.cpu().numpy().reshape(P, NB, 3)[::order]
+                                            for x in (q, u)])
+        for other in out[1:]:
+            for a, b in zip(out[0], other):
+                assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec,ks", [("fp64", (-900, -300, 300, 900)), ("mixed", (-60, -20, 20, 60))])
+def test_force_scale_of_few_blobs(torch_cuda, prec, ks):
+    """Steady flow is linear, and every operation on the way scales exactly by a
+    power of two: forces 2^k F give 2^k v bit for bit, whatever exponent the
+    fixed-point sums take; no force gives no flow, and one that is not finite
+    does not pass for one that is."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    L, P = 32, 5
+    rng = np.random.default_rng(7)
+    q0, spr = chains(rng, P, L)
+    F0 = rng.standard_normal((P * NB, 3))
+    sp = Springs(*spr[:4], 0.0)
+
+    def flow(F):
+        g = Grid(L, precision=prec, mode="steady", max_blobs=P * NB)
+        v = g.field()
+        g.step_ext(sp, dev(torch, q0.reshape(-1, 3)), v, None, dev(torch, F))
+        return v.cpu().numpy()
+
+    ref = flow(F0)
+    assert np.isfinite(ref).all() and ref.any()
+    for k in ks:
+        say("force scale", prec, k)
+        assert np.array_equal(np.ldexp(ref, k), flow(np.ldexp(F0, k)))
+    assert not flow(0.0 * F0).any()
+    say("force scale", prec, "bad forces")
+    for bad in (np.inf, np.nan):
+        F = F0.copy()
+        F[3, 1] = bad
+        assert np.isnan(flow(F)).all()
