@@ -320,6 +320,7 @@ struct ForceSrc {
     const T* recf;
     int mbox;
     const unsigned char* act;
+    int ng;  // with act: blocks that share a box's planes (active_planes)
     const int* fexp;
 };
 
@@ -462,12 +463,15 @@ __device__ __forceinline__ void list_force(const RecLine<T>* list, int n, int x,
     out[1] = f1.value(e2);
 }
 
-// Planes of a box with marks act, dealt out to blocks eight apart (zi + 8 k:
-// the planes of a few particles, neighbours, fall to different blocks, and few
-// blocks find nothing to do): bit k of plane zi + 8 k, read at once.
+// Planes with marks act of block zi of the ng that share a box's planes (and
+// one component, rows or columns): bit k of plane zi + 8 k.  ng = L (plane_blocks):
+// its plane alone.  Else ng = 8: the planes eight apart, read at once (those of
+// a few particles, neighbours, fall to different blocks, and few blocks find
+// nothing to do).
 template <int L>
 __device__ __forceinline__ unsigned long long active_planes(const unsigned char* __restrict__ act,
-                                                            int zi) {
+                                                            int zi, int ng) {
+    if (ng == L) return act[zi] ? 1ull : 0ull;
     unsigned long long m = 0;
 #pragma unroll
     for (int k = 0; k < L / 8; ++k) m |= act[zi + 8 * k] ? 1ull << k : 0ull;
@@ -487,7 +491,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     __shared__ cplx<T> buf[NL * LS];
     __shared__ cplx<T> tws[L];
     __shared__ double red[16];
-    const int tid = threadIdx.x;
+    const int tid0 = threadIdx.x;
     // blocks of a box are consecutive (G::NBX per box, a multiple of 8);
     // within a box each XCD takes a contiguous range of (c, z, y) rows, so
     // the rows of the Laplacian's z and y neighbours, read by adjacent
@@ -495,22 +499,29 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     // with act a block takes the planes of active_planes
     constexpr bool ACT = REC && STEADY;
     const bool planes = ACT && mk.act;
-    const int per_box = planes ? G::NBX / (L / 8) : G::NBX;
+    const int per_box = planes ? G::NBX / L * mk.ng : G::NBX;
     const int box = blockIdx.x / per_box;
     const int lb = planes ? blockIdx.x - box * per_box : xcd_remap(blockIdx.x - box * per_box, G::NBX);
     const int yb = lb % (L / R);
-    const int nz = planes ? 8 : L;
+    const int nz = planes ? mk.ng : L;
     const int comp = lb / (L / R) / nz;
     const int z_first = lb / (L / R) % nz;
     const int cbase = comp * L * L * L;   // component offset (elements)
     const int y0 = yb * R;
     v += (size_t)box * 3 * L * L * L;
     A += (size_t)box * 3 * L * NC * L;
-    for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     if (SRC == SRC_FIELD) f += (size_t)box * 3 * L * L * L;
     unsigned long long todo = 1;
-    if (planes) todo = active_planes<L>(mk.act + (size_t)box * L, z_first);
+    if (planes) {
+        todo = active_planes<L>(mk.act + (size_t)box * L, z_first, mk.ng);
+        if (todo == 0) return;
+    }
+    for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
     for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
+    // (opaque in the loop over planes: the indices formed from it are not kept
+    // across it, which took up to 264 registers)
+    int tid = tid0;
+    if (ACT) asm volatile("" : "+v"(tid));
     const int z = z_first + (ACT ? 8 * (__ffsll(todo) - 1) : 0);
     const int cz = comp * L + z;
     double sv = 0.0, sf = 0.0;
@@ -708,21 +719,24 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
 template <typename T, int L, bool INV, bool ACT>
 __global__ void __launch_bounds__((Geo<T, L>::TY))
 k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
-    const unsigned char* __restrict__ act) {
+    const unsigned char* __restrict__ act, int ng) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, W = G::WY, NTHR = G::TY, LS = G::LS;
     __shared__ cplx<T> buf[W * LS];
     __shared__ cplx<T> tws[L];
-    const int tid = threadIdx.x;
+    const int tid0 = threadIdx.x;
     const int ch = blockIdx.x % G::NCHY;
-    for (int i = tid; i < L; i += NTHR) tws[i] = tw[i];
     // ACT: planes without a mark in act are neither read nor written; a block
     // then takes the planes of active_planes
-    const int bcz = blockIdx.x / G::NCHY;  // (box * 3 + c) * L + z, or ... * 8 + zi
+    const int bcz = blockIdx.x / G::NCHY;  // (box * 3 + c) * L + z, or ... * ng + zi
     unsigned long long todo = 1;
-    if constexpr (ACT) todo = active_planes<L>(act + (size_t)(bcz / 24) * L, bcz % 8);
+    if constexpr (ACT) todo = active_planes<L>(act + (size_t)(bcz / ng / 3) * L, bcz % ng, ng);
+    if (ACT && todo == 0) return;
+    for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
     for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
-    const int cz = ACT ? bcz / 8 * L + bcz % 8 + 8 * (__ffsll(todo) - 1) : bcz;
+    int tid = tid0;
+    if (ACT) asm volatile("" : "+v"(tid));  // (as in k_x_fwd)
+    const int cz = ACT ? bcz / ng * L + bcz % ng + 8 * (__ffsll(todo) - 1) : bcz;
     const int kx0 = ch * W;
     const int wc = NC - kx0 < W ? NC - kx0 : W;
     cplx<T>* base = A + ((size_t)cz * NC + kx0) * L;
@@ -966,23 +980,24 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 template <typename T, int L, bool PLANES>
 __global__ void __launch_bounds__((Geo<T, L>::TXY))
 k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
-         T* __restrict__ vout, unsigned char* __restrict__ act) {
+         T* __restrict__ vout, unsigned char* __restrict__ act, int ng) {
     using G = Geo<T, L>;
     constexpr int H = G::H, PS = G::PS, NC = G::NC, NTHR = G::TXY;
     __shared__ cplx<T> buf[L * PS];
     __shared__ cplx<T> tws[L];
     __shared__ cplx<T> twh[H];
     const int tid0 = threadIdx.x;
-    for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
-    for (int i = tid0; i < H; i += NTHR) twh[i] = tw[2 * i];
-    constexpr int nz = PLANES ? 8 : L;
+    const int nz = PLANES ? ng : L;
     const int bc = blockIdx.x / nz, z0 = blockIdx.x % nz;  // box * 3 + c
     unsigned long long todo = 1;
     if (PLANES) {
-        todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0);
+        todo = active_planes<L>(act + (size_t)(bc / 3) * L, z0, ng);
+        if (todo == 0) return;
     } else if (act && tid0 == 0 && bc % 3 == 0) {
         act[(size_t)(bc / 3) * L + z0] = 0;  // for the next binning
     }
+    for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
+    for (int i = tid0; i < H; i += NTHR) twh[i] = tw[2 * i];
     for (; todo != 0; todo = PLANES ? todo & (todo - 1) : 0) {
     const int cz = PLANES ? bc * L + z0 + 8 * (__ffsll(todo) - 1)  // (box * 3 + c) * L + z
                           : (int)blockIdx.x;
@@ -1062,6 +1077,19 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     }
 }
 
+// Blocks that share the marked planes of a box (active_planes) in a pass whose
+// whole launch would be n blocks for the batch, for mbox blobs a box.  One plane
+// a block while the launch fills the chip a few times at most: blocks of planes
+// without a mark end at once, and a block that takes up to L / 8 planes runs
+// them one after another (19 particles in one 96^3 box, float32: x pass 17 us
+// against 63, y 6.3 and 25, inverse plane 12 and 54; 4 boxes 34 and 66).  Above,
+// the empty blocks cost more than the chain (32 64^3 boxes of two particles: x
+// pass of 24,576 blocks 33 against 27; 32 48^3, 13,824: 21 and 19), at half
+// the number in the inverse plane pass, whose blocks take more LDS (32 64^3, 6,144:
+// 19 and 16).  So few blobs that at most half the planes can be marked are
+// dealt out too (one particle in 128^3: inverse plane pass 9.4 against 13.3).
+inline int plane_blocks(int64_t n, int mbox, int L) { return n <= 8192 && 8 * mbox > L ? L : 8; }
+
 template <typename T, int L>
 hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_out,
                        hipStream_t s) {
@@ -1087,12 +1115,13 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         mk.mbox = F.mbox;
         mk.fexp = g->d_rank;
         if (F.planes) mk.act = g->d_act;
+        mk.ng = plane_blocks((int64_t)G::NBX * nbox, F.mbox, L);
     }
     unsigned char* act = mk.act ? g->d_act : nullptr;
     const int part = F.planes && F.planes_out ? 1 : 0;
 #define MB_XF(SR, ST)                                                                     \
     MB_LAUNCH(g, K_FFT_X_FWD, s, (k_x_fwd<T, L, SR, ST>),                             \
-              (act ? G::NBX / (L / 8) : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
+              (act ? G::NBX / L * mk.ng : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
               g->btiles, mk, tw, a, b, A, g->d_psum)
     if (F.src == SolveForce<T>::FIELD) {
         if (rhs) MB_XF(SRC_FIELD, true);
@@ -1108,9 +1137,10 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         else MB_XF(SRC_BOX, false);
     }
 #undef MB_XF
+    const int ngy = plane_blocks((int64_t)3 * L * G::NCHY * nbox, F.mbox, L);
 #define MB_Y(ID, INV, AC)                                                                 \
-    MB_LAUNCH(g, ID, s, (k_y<T, L, INV, AC>), 3 * (AC ? 8 : L) * G::NCHY * nbox, G::TY, 0, A, \
-              tw, (const unsigned char*)act)
+    MB_LAUNCH(g, ID, s, (k_y<T, L, INV, AC>), 3 * (AC ? ngy : L) * G::NCHY * nbox, G::TY, 0, \
+              A, tw, (const unsigned char*)act, ngy)
     if (act) MB_Y(K_FFT_Y_FWD, false, true);
     else MB_Y(K_FFT_Y_FWD, false, false);
     const T c0 = steady ? T(0) : (T)(g->d.rho / g->d.dt * N);
@@ -1126,12 +1156,13 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     else MB_Z(false);
 #undef MB_Z
     if constexpr (G::XY) {
+        const int ngx = plane_blocks((int64_t)2 * G::NBXY * nbox, F.mbox, L);
         if (part)
-            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * 8 * nbox, G::TXY, 0,
-                      A, tw, v_out, act);
+            MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * ngx * nbox, G::TXY, 0,
+                      A, tw, v_out, act, ngx);
         else
             MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, false>), G::NBXY * nbox, G::TXY, 0, A,
-                      tw, v_out, act);
+                      tw, v_out, act, L);
     } else {
         if (part) MB_Y(K_FFT_Y_INV, true, true);
         else MB_Y(K_FFT_Y_INV, true, false);

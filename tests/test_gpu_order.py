@@ -100,3 +100,32 @@ def test_force_scale_of_few_blobs(torch_cuda, prec, ks):
         F = F0.copy()
         F[3, 1] = bad
         assert np.isnan(flow(F)).all()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("L,P,nbox", [(8, 1, 3), (24, 3, 9), (24, 1, 64), (64, 2, 32), (96, 19, 1),
+                                      (128, 1, 1), (144, 1, 1), (192, 2, 1)])
+def test_marked_planes_by_block(torch_cuda, L, P, nbox, prec):
+    """Steady calls form only the z planes that hold blobs until their last
+    step, a block taking one plane or every eighth by the launch's blocks and
+    the blobs: one call of three steps equals three calls bit for bit, with
+    blobs on both sides of the seam."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    say("planes by block", L, P, nbox, prec)
+    rng = np.random.default_rng(L + P)
+    q0, spr = chains(rng, P * nbox, L)
+    q0[::2, :, 2] -= 4.0
+    F0 = rng.standard_normal((P * nbox, 3))
+    out = []
+    for calls in (1, 3):
+        g = Grid(L, precision=prec, mode="steady", dt=0.05, max_blobs=P * nbox * NB, nbox=nbox)
+        if L == 192:
+            g.set_tiles(32, 8, 8)
+        q, F = dev(torch, q0.reshape(-1, 3)), dev(torch, F0)
+        v = torch.full(g.field_shape, 3.0, dtype=g.field_dtype, device="cuda")
+        for _ in range(calls):
+            g.step(Springs(*spr), q, v, F, 3 // calls)
+        out.append([x.cpu().numpy() for x in (q, v)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
