@@ -188,31 +188,40 @@ constexpr int largest_even_divisor(int L, int cap) {
 }
 // rows per block of the inverse x pass (about 256 threads per block)
 constexpr int rows_x(int L) { return largest_even_divisor(L, 4096 / L > 2 ? 4096 / L : 2); }
-// Rows per block of the forward x pass and elements per thread.  A block is
-// a chain (a load round per element of a thread, the transform, the store),
-// so short chains and many blocks matter most: up to L = 128, 16 rows and
-// one element per thread (L <= 24), two (<= 72) or four against eight
-// elements of 4096 / L rows before (one 32^3 box, 48 blocks of 256 threads
-// against 96 of 64: 10.0 -> 5.4 us; 64^3 float32 12.2 -> 8.0, float64 14.7
-// -> 12.7; 72^3 14.6 -> 9.1; 96^3 float64 25.0 -> 21.9; 128^3 float32 21.7
-// -> 20.5, float64 38.2 -> 34.6).  Fewer rows store shorter runs of ky (a
-// batch of 32 64^3 boxes: 69.7 us with 16 rows, 76 with 8).  Above, float32
-// takes as few elements as 512 threads allow (144^3, 16 rows: 40.9 -> 35.9
-// us; 192^3 96.5 -> 92.1; 256^3 211.7 -> 204.6), float64 four of eight rows
-// from L = 192 on (192^3 with boxes 198.5 -> 196 us, without 165 -> 152, 256^3
-// with boxes 435 -> 426; four of sixteen rows 566: three waves of 512 threads
-// do not fit its registers) and eight of 24 at 144 (75 us, 80 with eight rows).
+// Rows per block of the forward x pass and elements per thread (by the size, and
+// by whether the force is a field and whether it is all that is transformed).  A
+// block is a chain (a load round per element of a thread, the transform, the
+// store), so short chains and many blocks matter most: up to L = 128, 16 rows and
+// one element per thread (L <= 24), two (<= 72) or four against eight elements of
+// 4096 / L rows (one 32^3 box, 48 blocks of 256 threads against 96 of 64: 10.0 ->
+// 5.4 us; 64^3 float32 12.2 -> 8.0, float64 14.7 -> 12.7; 72^3 14.6 -> 9.1; 96^3
+// float64 25.0 -> 21.9; 128^3 float32 21.7 -> 20.5, float64 38.2 -> 34.6).  Fewer
+// rows store shorter runs of ky (a batch of 32 64^3 boxes: 69.7 us with 16 rows,
+// 76 with 8).
+// Above, what the loads find in the caches decides, and every size was measured
+// both ways.  float32, as few elements as 512 threads allow against eight, in us:
+// with boxes 192^3 85 and 88, 216^3 206 and 228, 256^3 198 and 202, 288^3 366 and
+// 381, 384^3 722 and 775, 512^3 1695 and 1788, but 432^3 1195 and 1129; a field
+// with a velocity 55 and 58, 107 and 116, 133 and 131, 279 and 290, 490 and 530, 1168
+// and 1262, 432^3 922 and 810; a field alone 36 and 33 at 192^3, 60 and 53, 71
+// and 62, 173 and 133, 307 and 253, 580 and 438, 632 and 640; boxes alone as with
+// a velocity, but 288^3 290 and 250.  float64, four elements of eight rows against
+// eight of 4096 / L: 192^3 with boxes 173 and 177, a field 132 and 133, 216^3 336
+// and 355, 251 and 246, 256^3 404 and 413, 314 and 318; 288^3 872 and 699, 710 and
+// 548, 384^3 1614 and 1455, 1299 and 1176, 432^3 a field 1922 and 1875, 512^3 2705
+// and 2849; 144^3 80 and 75 (24 rows).
 template <typename T>
 constexpr int rows_xf(int L) {
     if (L <= 128 || (sizeof(T) == 4 && L == 144)) return largest_even_divisor(L, 16);
-    if (sizeof(T) == 8 && L >= 192) return 8;
+    if (sizeof(T) == 8 && L >= 192 && L <= 256) return 8;
     return rows_x(L);
 }
 template <typename T>
-constexpr int elems_xf(int L) {
+constexpr int elems_xf(int L, bool field, bool steady) {
     const int n = rows_xf<T>(L) / 2 * L;
     if (L <= 128) return L <= 24 ? 1 : (L <= 72 ? 2 : 4);
-    if (sizeof(T) == 8) return L >= 192 ? 4 : EPT;
+    if (sizeof(T) == 8) return L >= 192 && L <= 256 ? 4 : EPT;
+    if (L == 432 || (steady && (field ? L >= 192 : L == 288))) return EPT;
     int e = 3;
     while (n % e != 0 || n / e > 512) ++e;
     return e;
@@ -261,12 +270,9 @@ struct Geo {
     static constexpr int NC = L / 2 + 1;
     static constexpr int R = rows_xf<T>(L);  // forward x pass: rows per block
     static constexpr int NL = R / 2;
-    static constexpr int EX = elems_xf<T>(L); // elements per thread
-    static constexpr int TX = NL * L / EX;   // threads
     static constexpr int RI = rows_x(L);     // inverse x pass
     static constexpr int NLI = RI / 2;
     static constexpr int TXI = NLI * L / EPT;
-    static_assert(NL * L % EX == 0 && TX <= 512, "x pass");
     static constexpr int LS = line_stride(L); // LDS line stride (complex)
     static constexpr int WY = cols_y<T>(L);
     static constexpr int NCHY = (NC + WY - 1) / WY;
@@ -478,8 +484,16 @@ __device__ __forceinline__ unsigned long long active_planes(const unsigned char*
     return m;
 }
 
+// Threads of the forward x pass.
 template <typename T, int L, int SRC, bool STEADY>
-__global__ void __launch_bounds__((Geo<T, L>::TX))
+constexpr int threads_xf() {
+    constexpr int n = Geo<T, L>::NL * L, e = elems_xf<T>(L, SRC == SRC_FIELD, STEADY);
+    static_assert(n % e == 0 && n / e <= 512, "x pass");
+    return n / e;
+}
+
+template <typename T, int L, int SRC, bool STEADY>
+__global__ void __launch_bounds__((threads_xf<T, L, SRC, STEADY>()))
 k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> mk,
         const cplx<T>* __restrict__ tw, T a, T b,
         cplx<T>* __restrict__ A, double* __restrict__ psum) {
@@ -487,7 +501,8 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     constexpr bool REC = SRC == SRC_REC;
     constexpr bool ADD = SRC == SRC_BOX_ADD;
     using G = Geo<T, L>;
-    constexpr int NC = G::NC, R = G::R, NL = G::NL, NTHR = G::TX, LS = G::LS;
+    constexpr int NC = G::NC, R = G::R, NL = G::NL, LS = G::LS;
+    constexpr int NTHR = threads_xf<T, L, SRC, STEADY>(), EX = NL * L / NTHR;
     __shared__ cplx<T> buf[NL * LS];
     __shared__ cplx<T> tws[L];
     __shared__ double red[16];
@@ -517,7 +532,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
         if (todo == 0) return;
     }
     for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
-    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
+    do {  // (a loop only with ACT: as one of a single round, it took 10 to 20 registers more)
     // (opaque in the loop over planes: the indices formed from it are not kept
     // across it, which took up to 264 registers)
     int tid = tid0;
@@ -550,8 +565,8 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     // one elsewhere (float64 128^3: 34.5 against 37.5 with two, whose registers
     // cost a wave; 96^3: 14.0 against 15.5).
     constexpr bool UNI_ROWS = L % WAVE == 0 && NTHR % L == 0;
-    constexpr int KG = sizeof(T) == 4 && UNI_ROWS && BOX && !STEADY && G::EX % 2 == 0 ? 2 : 1;
-    static_assert(G::EX % KG == 0, "rounds of the x pass");
+    constexpr int KG = sizeof(T) == 4 && UNI_ROWS && BOX && !STEADY && EX % 2 == 0 ? 2 : 1;
+    static_assert(EX % KG == 0, "rounds of the x pass");
     // a wave's lanes share y when L is a multiple of the wave
     constexpr bool UNI = L % WAVE == 0 && NTHR % L == 0;
     // with UNI, a thread's x (and its neighbours and x box sources) is the
@@ -566,7 +581,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     [[maybe_unused]] AxisSrc bxu{};
     if constexpr (UNI && BOX) bxu = box_src_x(tl, xu);
 #pragma unroll
-    for (int k0 = 0; k0 < G::EX; k0 += KG) {
+    for (int k0 = 0; k0 < EX; k0 += KG) {
         T vc[KG][2], vn[KG][2][6], fv[KG][2];
         T eb[KG][2][4][2];
         if constexpr (UNI) {
@@ -711,7 +726,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
             psum[2 * pb + 1] = tf;
         }
     }
-    }
+    } while (ACT && (todo &= todo - 1) != 0);
 }
 
 // y pass: block = (component, z plane, WY consecutive kx); the kx rows of
@@ -733,7 +748,7 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     if constexpr (ACT) todo = active_planes<L>(act + (size_t)(bcz / ng / 3) * L, bcz % ng, ng);
     if (ACT && todo == 0) return;
     for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
-    for (; todo != 0; todo = ACT ? todo & (todo - 1) : 0) {
+    do {
     int tid = tid0;
     if (ACT) asm volatile("" : "+v"(tid));  // (as in k_x_fwd)
     const int cz = ACT ? bcz / ng * L + bcz % ng + 8 * (__ffsll(todo) - 1) : bcz;
@@ -750,7 +765,7 @@ k_y(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     };
     __syncthreads();  // twiddles; the plane before has left buf
     line_fft_io<T, L, INV, W, LS, NTHR, false, false, false>(buf, tws, tid, gload, gstore);
-    }
+    } while (ACT && (todo &= todo - 1) != 0);
 }
 
 // z pass fused with the solve: block = (kx, WZ consecutive ky), all three
@@ -998,7 +1013,7 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     }
     for (int i = tid0; i < L; i += NTHR) tws[i] = tw[i];
     for (int i = tid0; i < H; i += NTHR) twh[i] = tw[2 * i];
-    for (; todo != 0; todo = PLANES ? todo & (todo - 1) : 0) {
+    do {
     const int cz = PLANES ? bc * L + z0 + 8 * (__ffsll(todo) - 1)  // (box * 3 + c) * L + z
                           : (int)blockIdx.x;
     // (opaque in the loop over planes: the indices formed from it are not kept
@@ -1074,7 +1089,7 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     auto gst = [out](int line, int e, cplx<T> x) { st32(out, (unsigned)(line * H + e), x); };
     line_fft_io<T, H, true, L, PS, NTHR, false, true, false>(buf, twh, tid, ldl, gst);
     if (PLANES) __syncthreads();  // (another plane in buf)
-    }
+    } while (PLANES && (todo &= todo - 1) != 0);
 }
 
 // Blocks that share the marked planes of a box (active_planes) in a pass whose
@@ -1121,8 +1136,8 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     const int part = F.planes && F.planes_out ? 1 : 0;
 #define MB_XF(SR, ST)                                                                     \
     MB_LAUNCH(g, K_FFT_X_FWD, s, (k_x_fwd<T, L, SR, ST>),                             \
-              (act ? G::NBX / L * mk.ng : G::NBX) * nbox, G::TX, 0, v_in, fin,                     \
-              g->btiles, mk, tw, a, b, A, g->d_psum)
+              (act ? G::NBX / L * mk.ng : G::NBX) * nbox, (threads_xf<T, L, SR, ST>()), 0, \
+              v_in, fin, g->btiles, mk, tw, a, b, A, g->d_psum)
     if (F.src == SolveForce<T>::FIELD) {
         if (rhs) MB_XF(SRC_FIELD, true);
         else MB_XF(SRC_FIELD, false);
