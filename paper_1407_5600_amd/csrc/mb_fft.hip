@@ -893,20 +893,26 @@ k_z_solve(cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // one complex line Z = X_even + i X_odd (Hermitian extension for kx > L/2,
 // imaginary parts of kx = 0 and L/2 dropped), transformed, and the real and
 // imaginary parts stored as the two velocity rows.
-template <typename T, int L>
+template <typename T, int L, bool KEEP>
 __global__ void __launch_bounds__((Geo<T, L>::TXI))
 k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
         T* __restrict__ vout, unsigned char* __restrict__ act, int part_out) {
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::RI, NL = G::NLI, NTHR = G::TXI, LS = G::LS;
     // The spectrum is not read again, and before the field is, more than the
-    // L2s hold passes through them (this pass runs from 192^3 on: 85 MB): both
-    // go past the caches' replacement where rows are whole lines.  256^3
-    // float32: this pass 78 -> 66 us, the interpolation after it, whose boxes of
-    // nodes overlap in the caches, 234 -> 213; a 192^3 float64 solve's forward
-    // x pass, of inputs that stay, 150 -> 142.  Rows that split lines lose
-    // (216^3 float64: this pass 106 -> 115, a dense step +0.7%).
-    constexpr bool ONCE = L * sizeof(T) % 128 == 0;
+    // L2s hold passes through them: both go past the caches' replacement where
+    // what a block takes of them are whole 128-byte lines (its runs of R values of
+    // the spectrum, its rows of the field).  Stores: the interpolation, whose boxes
+    // of nodes overlap in the caches, 206 -> 186 us at 256^3 float32, 272 -> 260 at
+    // 288^3, 885 -> 874 at 512^3, float64 112 -> 103 at 192^3, 247 -> 233 at 256^3; a
+    // 192^3 float64 solve's forward x pass 147 -> 133.  Loads, with the stores: this
+    // pass 178 -> 153 us at 256^3 float64, 1323 -> 1294 at 512^3; of split lines 135
+    // -> 155 at 288^3 float32, 755 -> 930 at 512^3.  KEEP: neither, for a solve in
+    // place whose velocity, force and spectrum the last-level cache holds together,
+    // so that the next one finds its input there (144^3 float64: a solve 172 us, 186
+    // with the hints; into another field 193 and 171, a dense step 365 and 358).
+    constexpr bool LD_ONCE = !KEEP && R * 2 * sizeof(T) % 128 == 0;
+    constexpr bool ST_ONCE = !KEEP && L * sizeof(T) % 128 == 0;
     constexpr int SS = NC + 1;  // staging row stride
     __shared__ cplx<T> stg[R * SS];
     __shared__ cplx<T> buf[NL * LS];
@@ -935,7 +941,7 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
             const int kx = e / R;
             const int rl = e - kx * R;
             const unsigned i = (unsigned)(e < NC * R ? kx * L + rl : 0);
-            ld[k] = ONCE ? ld32_once(in, i) : ld32(in, i);
+            ld[k] = LD_ONCE ? ld32_once(in, i) : ld32(in, i);
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -968,7 +974,7 @@ k_x_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     T* out = vout + ((size_t)cz * L + y0) * L;
     auto st = [out](int line, int x, cplx<T> zz) {
         const unsigned i = (unsigned)((2 * line) * L + x);
-        if (ONCE) {
+        if (ST_ONCE) {
             st32_once(out, i, zz.x);
             st32_once(out, i + L, zz.y);
         } else {
@@ -1181,8 +1187,19 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     } else {
         if (part) MB_Y(K_FFT_Y_INV, true, true);
         else MB_Y(K_FFT_Y_INV, true, false);
-        MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A,
-                  tw, v_out, act, part);
+#define MB_XI(KEEP)                                                                       \
+    MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L, KEEP>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A, \
+              tw, v_out, act, part)
+        // v, f and the spectrum of all boxes against the 256 MB last-level cache
+        constexpr int64_t three = (int64_t)9 * L * L * L * sizeof(T), room = (int64_t)224 << 20;
+        const bool in_place = F.src == SolveForce<T>::FIELD && (v_out == v_in || v_out == F.f);
+        if constexpr (three <= room) {
+            if (in_place && three * nbox <= room) MB_XI(true);
+            else MB_XI(false);
+        } else {
+            MB_XI(false);
+        }
+#undef MB_XI
     }
 #undef MB_Y
     return hipGetLastError();
