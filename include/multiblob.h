@@ -133,12 +133,17 @@ typedef enum {
  * after its last replay.  check_finite = 0 (the default): no check and no
  * synchronisation; non-finite inputs give non-finite or meaningless
  * outputs, never an access outside the library's buffers.
- * The same check reports a stalled scan: in a step the first workgroup of
- * the spring-force kernel sums the tile counts and the others wait for it,
- * for at most one to two seconds (only a device that does not run that
- * workgroup makes them give up); a workgroup that gives up writes no
- * records, and with check_finite = 1 the call returns MB_ERR_DEVICE, with
- * check_finite = 0 its outputs are undefined.
+ * The same check reports a stalled scan: in the kernel that sorts the blobs by
+ * tile (in a step that of the spring forces, and in mb_spread, mb_interpolate,
+ * mb_interpolate_grad, mb_step_adjoint and the midpoint scheme's interpolations
+ * that of the records; neither for few blobs per box nor in a captured call) the
+ * first workgroup sums the tile counts and the others wait for it, for at most
+ * one to two seconds (only a device that does not run that workgroup makes them
+ * give up).  A workgroup that gives up writes no records: the outputs of the
+ * call, and those of later calls made from them, are then undefined.  With
+ * check_finite = 1 the call returns MB_ERR_DEVICE; with check_finite = 0 the next
+ * call on the grid that waits for the device does (mb_step_graph,
+ * mb_grid_autotune, mb_grid_kernel_times).
  *
  * external_workspace = 1: mb_grid_create allocates no scratch; every call
  * on the grid returns MB_ERR_INVALID until a workspace of at least

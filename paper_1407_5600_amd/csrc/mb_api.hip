@@ -283,11 +283,14 @@ mb_status enter(mb_grid* g) {
 
 // Result of a call whose launches gave e: with check_finite, waits for the
 // stream and reports (then clears) the flag its kernels set: bit 1 a
-// non-finite input, bit 2 a springs block that gave up waiting for the
-// tile offsets (a device failure).
-mb_status finish(mb_grid* g, hipError_t e, hipStream_t s) {
+// non-finite input, bit 2 a block that gave up waiting for the tile offsets
+// (a device failure).  waits: the call waits for the stream in any case; it
+// then reports bit 2 of the calls before it too, which without check_finite did
+// not wait.
+mb_status finish(mb_grid* g, hipError_t e, hipStream_t s, bool waits = false) {
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? MB_ERR_NOMEM : MB_ERR_DEVICE;
-    if (!g->d.check_finite) return MB_OK;
+    if (!g->d.check_finite && !(waits && g->scan_unchecked)) return MB_OK;
+    g->scan_unchecked = false;
     int flag = 0;
     e = hipMemcpyAsync(&flag, g->d_flag, sizeof(int), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -650,7 +653,7 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
         if (small) {
             e = bin_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, sums, mark);
         } else {
-            const bool fuse = fused_scan_ok(g, s);  // the scan in the springs kernel
+            const bool fuse = fused_scan_ok(g, s, kFusedTiles);
             e = bin_blobs<T>(g, M, x, s, counted, !fuse);
             if (e == hipSuccess) e = scatter_springs<T>(g, sd, P, x, Fext, s, Gblob, sums, fuse);
             if (e == hipSuccess) e = spread_boxes<T>(g, s);
@@ -849,7 +852,7 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     auto check_all = [&](hipError_t e) -> mb_status {
         mb_status r = MB_OK;
         for (int i = 0; i < ngrids; ++i) {
-            const mb_status ri = finish(grids[i], e, (hipStream_t)stream);
+            const mb_status ri = finish(grids[i], e, (hipStream_t)stream, true);
             if (r == MB_OK) r = ri;
         }
         return r;
@@ -1179,6 +1182,8 @@ mb_status mb_grid_autotune(mb_grid* g, const mb_springs* sp, int64_t P, const do
     if (vc) (void)hipFree(vc);
     if (st != MB_OK) return st;
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? MB_ERR_NOMEM : from_hip(e);
+    st = finish(g, e, s, true);
+    if (st != MB_OK) return st;
     if (shape_out) {
         shape_out[0] = best[0];
         shape_out[1] = best[1];
@@ -1220,7 +1225,7 @@ mb_status mb_grid_kernel_times(mb_grid* g, void* stream, double* ms_out,
         launches_out[i] = g->acc_n[i];
     }
     if (n_out) *n_out = K_NUM;
-    return MB_OK;
+    return finish(g, hipSuccess, (hipStream_t)stream, true);
 }
 
 // ---- Allocation-free step: the grid's workspace in a static device array.

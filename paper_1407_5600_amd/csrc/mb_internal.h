@@ -111,7 +111,8 @@ struct mb_grid {
     int* d_flag;        // [0] non-finite flag (check_finite; bit 2: a springs
                         // block gave up waiting for the offsets), [1] the
                         // fused scan's published launch number
-    uint32_t scan_epoch;  // launches of the springs kernel with the fused scan
+    uint32_t scan_epoch;  // launches of kernels with the fused scan
+    bool scan_unchecked;  // one since the flag was last read
     double* d_qint;     // [max_blobs][3] positions in the step calls' particle order
     double* d_pint;     // [max_blobs][3] per-particle forces, same order
     int* d_order;       // [max_blobs] caller's particle of each internal particle
@@ -235,11 +236,17 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
                            const double* q, const double* Fext, hipStream_t s,
                            const double* Gblob = nullptr, bool force_sums = true,
                            bool scan = false);
-// The scan can ride in the springs kernel: a single scan block's worth of
-// tiles and a stream not being captured (a captured launch would replay its
+// The scan can ride in the kernel that places the records: at most `tiles`
+// tiles (kFusedTiles, a single scan block's worth, in the springs kernel, whose
+// blocks have forces to form meanwhile; kFusedScatterTiles in the scattering
+// kernel, where the others wait for all of it: 1,300 blobs in each of 48 32^3
+// boxes, 1,536 tiles, an interpolation 32.3 -> 31.4 us, 64 boxes 38.9 -> 40.1;
+// 128^3, 2,048 tiles, 79,000 blobs 28.2 -> 30.6) and a stream not being captured (a captured launch would replay its
 // launch number; d_flag[1] is zeroed with the workspace, launch numbers
 // start at 1).
-bool fused_scan_ok(mb_grid* g, hipStream_t s);
+constexpr int kFusedTiles = 4096;
+constexpr int kFusedScatterTiles = 1536;
+bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles);
 hipError_t spring_forces(const SpringsDev& sp, int64_t P, const double* q,
                          const double* Fext, double* F, hipStream_t s,
                          mb_grid* timing_grid, const double* Gblob = nullptr);

@@ -2217,6 +2217,7 @@ static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M
 static FusedScan fused_scan(mb_grid* g, bool scan) {
     FusedScan sc{};
     if (!scan) return sc;
+    g->scan_unchecked = true;
     sc.count = g->d_count;
     sc.flag = g->d_flag + 1;
     sc.err = g->d_flag;
@@ -2318,7 +2319,7 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
         e = blob_axpy(3 * M, F2, f2scale, F, Fsum, s);
         F = Fsum;
     }
-    const bool fuse = M > 0 && fused_scan_ok(g, s);  // the scan in the scattering kernel
+    const bool fuse = M > 0 && fused_scan_ok(g, s, kFusedScatterTiles);
     if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s, false, !fuse);
     if (e != hipSuccess || M == 0) return e;
     const FusedScan scan = fused_scan(g, fuse);
@@ -2357,8 +2358,8 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
     return hipGetLastError();
 }
 
-bool fused_scan_ok(mb_grid* g, hipStream_t s) {
-    if (g->nscan != 1) return false;
+bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles) {
+    if ((int64_t)g->tiles.n * g->tiles.nbox > tiles) return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();

@@ -129,3 +129,43 @@ def test_marked_planes_by_block(torch_cuda, L, P, nbox, prec):
         out.append([x.cpu().numpy() for x in (q, v)])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("waits", ["kernel_times", "step_graph", "autotune"])
+def test_stalled_scan_is_reported_by_the_next_call_that_waits(torch_cuda, waits):
+    """Without the finite check a call does not wait, and so cannot report that
+    its blocks gave up waiting for the tile offsets.  The bit they set (here set by
+    the host, in the words before the plane marks that end the workspace) is
+    reported once by the next call that waits for the device, after which the
+    grid is usable."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    from paper_1407_5600_amd.binding import step_graph
+    say("stalled scan", waits)
+    L, P = 32, 30
+    rng = np.random.default_rng(3)
+    q0, spr = chains(rng, P, L)
+    g = Grid(L, max_blobs=P * NB, workspace="torch")
+    sp = Springs(*spr)
+    at = g.workspace_size() - 256 * ((L + 255) // 256) - 256
+    flag = g.workspace[at:at + 4].view(torch.int32)
+
+    def call():
+        if waits == "kernel_times":
+            g.kernel_times()
+        elif waits == "step_graph":
+            step_graph([g], [sp], [q.clone()], [g.field()], [F], None, 2)
+        else:
+            g.autotune(sp, q, g.field(), F, 2)
+
+    q, F = dev(torch, q0.reshape(-1, 3)), dev(torch, np.ones((P, 3)))
+    v = torch.randn(g.field_shape, dtype=torch.float64, device="cuda")
+    call()
+    assert int(flag) == 0
+    ref = g.interpolate(q, v).clone()
+    flag.fill_(2)
+    with pytest.raises(Exception, match="device"):
+        call()
+    assert int(flag) == 0
+    call()
+    assert torch.equal(g.interpolate(q, v), ref)
