@@ -1804,6 +1804,17 @@ k_interp_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, i
     }
 }
 
+// Waves per SIMD that the derivative kernel's registers leave room for: in float64
+// the five that its boxes of nodes leave in 160 KB of LDS, else four (102 registers
+// and four waves without the bound: 256^3, 636,000 blobs, 186 us, 170 with it; 192^3,
+// 268,000, 60 and 54); float32 seven (79 at most otherwise: 78 and 74).
+template <typename T, int TX, int TY, int TZ>
+constexpr int grad_min_waves() {
+    constexpr int rows = (TY + 3) * (TZ + 3);
+    constexpr int lds = rows * ((TX + 3) * (int)sizeof(T) + (int)sizeof(int));
+    return sizeof(T) == 4 ? 7 : (5 * lds <= 160 << 10 ? 5 : 4);
+}
+
 // Position derivative of the interpolation, contracted with blob weights:
 // g_i += wscale sum_a W_{i,a} grad_{q_i} (J_i v)_a.  One block per tile as in
 // k_interp (same staged field, one component at a time); per record and
@@ -1812,7 +1823,7 @@ k_interp_direct(const RecG<T>* __restrict__ rec, const int* __restrict__ perm, i
 // indexed by blob; each blob belongs to one record, so g is updated without
 // atomics.
 template <typename T, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(BLK)
+__global__ void __launch_bounds__(BLK, (grad_min_waves<T, TX, TY, TZ>()))
 k_interp_grad(const RecG<T>* __restrict__ rec, const int* __restrict__ perm,
               const int* __restrict__ offs, int L, Tiles tl, const T* __restrict__ v,
               const double* __restrict__ W, double wscale, double inv_h,
