@@ -318,7 +318,7 @@ enum : int { SRC_FIELD, SRC_BOX, SRC_BOX_ADD, SRC_REC };
 // force, as the binning marked it; the x and y passes pass over planes without
 // one and the z pass takes them as zero (two particles in 64^3 lie in about 7
 // of the 64 planes).  fexp: per box, the exponent of the fixed-point sums its
-// force is formed in (FixedSum), as the binning left it.
+// force is formed in (add_records), as the binning left it.
 template <typename T>
 struct ForceSrc {
     const T* add;
@@ -328,41 +328,6 @@ struct ForceSrc {
     const unsigned char* act;
     int ng;  // with act: blocks that share a box's planes (active_planes)
     const int* fexp;
-};
-
-// Sum of the contributions w s of records to a node in fixed point, so that it
-// does not depend on their order, as in the spreading.  s is scaled by 2^e, e
-// the box's exponent (box_exponent): |w s| < 2^51.  Adding 1.5 2^52 then leaves
-// the contribution rounded to an integer in the low bits (one fused
-// multiply-add), and the bits are summed as 64-bit integers (at most kSmallBlobs
-// of them).  float64: the rounding remainder, exact by a second fused
-// multiply-add, is summed the same way at 2^-40 of the first quantum, so that
-// the sum is at least as close as one in float64 (the first sum alone is held
-// to 2^-52 of the box's largest force).
-template <typename T>
-struct FixedSum {
-    static constexpr double MAGIC = 0x1.8p52;
-    static constexpr int LOW = 40;
-    unsigned long long hi = 0, lo = 0;  // (modulo 2^64)
-    unsigned n = 0;
-    __device__ __forceinline__ void add(T w, T s) {
-        const double y = fma((double)w, (double)s, MAGIC);
-        hi += (unsigned long long)__double_as_longlong(y);
-        if constexpr (sizeof(T) == 8) {
-            const double r = fma(w, s, MAGIC - y);
-            lo += (unsigned long long)__double_as_longlong(fma(r, (double)(1ll << LOW), MAGIC));
-        }
-        ++n;
-    }
-    __device__ __forceinline__ T value(int e) const {
-        // (a force that is not finite: every node of the box)
-        if (e == kExpNonfinite) return (T)__builtin_nan("");
-        const unsigned long long m = n * 0x4338000000000000ull;  // n times MAGIC's bits
-        double x = (double)(long long)(hi - m);
-        if constexpr (sizeof(T) == 8)
-            x = fma((double)(long long)(lo - m), 1.0 / (double)(1ll << LOW), x);
-        return (T)ldexp(x, -e);
-    }
 };
 
 // A record as the rows of one plane see it: its first nodes along x and y
@@ -375,9 +340,9 @@ struct RecLine {
 };
 
 // The records of a box (forces recf) with nodes of component a in plane z and
-// in any of the R rows from y0, in record order, into list, the forces times
-// 2^e2; returns their number.  Each thread looks at one record a round (a round takes NTHR); cnt:
-// an int per wave.  Called by the whole block; ends with a barrier.
+// in any of the R rows from y0 into list, the forces times 2^e2; returns their
+// number.  Each thread looks at one record a round (a round takes NTHR); cnt: an
+// int per wave.  Called by the whole block; ends with a barrier.
 template <typename T, int L, int R, int NTHR>
 __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
                                              const T* __restrict__ recf, int mbox, int a, int z,
@@ -417,56 +382,84 @@ __device__ __forceinline__ int plane_records(const RecG<T>* __restrict__ rec,
             total += __popcll(m);
         }
         if (keep) {
-            T wx[3], wy[3];
-            kernel_weights<T>(rec_t(r, a, 0), wx);
-            kernel_weights<T>(rec_t(r, a, 1), wy);
-            const T f = kernel_weight<T>(rec_t(r, a, 2), dz) * F;
             RecLine<T>* e = list + before + __popcll(m & ((1ull << (tid % WAVE)) - 1));
-            e->wx[0] = wx[0];
-            e->wx[1] = wx[1];
-            e->wx[2] = wx[2];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) e->wyf[k] = ldexp(wy[k] * f, e2);
-            e->xs = xs;
+            for (int b = 0; b < 3; ++b) e->wx[b] = rec_t(r, a, b);
+            e->wyf[0] = F;
+            e->xs = xs | dz << 16;
             e->ys = ys;
         }
         n = total;
         __syncthreads();
     }
+    if (n > 0) {
+        // the weights, by as few waves as the list takes
+        for (int k = tid; k < n; k += NTHR) {
+            RecLine<T>* e = list + k;
+            const int dz = e->xs >> 16;
+            T wx[3], wy[3];
+            const T f = kernel_weight<T>(e->wx[2], dz) * e->wyf[0];
+            kernel_weights<T>(e->wx[0], wx);
+            kernel_weights<T>(e->wx[1], wy);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                e->wx[b] = wx[b];
+                e->wyf[b] = ldexp(wy[b] * f, e2);
+            }
+            e->xs &= 0xffff;
+        }
+        __syncthreads();
+    }
     return n;
 }
 
-// Force of the nodes (x, y) and (x, y + 1) from the n records of a list; y0
-// the first row of the block, [rlo, rhi] the rows from y0 that the wave's lanes
-// ask for.  A wave picks the records with nodes in its rows by ballot, so that
-// the other rows of the block cost next to nothing.
-template <typename T, int L, int NTHR>
-__device__ __forceinline__ void list_force(const RecLine<T>* list, int n, int x, int y, int y0,
-                                           int rlo, int rhi, int e2, T out[2]) {
-    FixedSum<T> f0, f1;
-    const int left = NTHR - (int)(threadIdx.x - threadIdx.x % WAVE);
-    const int cw = NTHR % WAVE == 0 || left >= WAVE ? WAVE : left;  // the wave's lanes
-    for (int k0 = 0; k0 < n; k0 += cw) {
-        const int i = k0 + (int)(threadIdx.x % WAVE);
-        int d = list[i < n ? i : 0].ys - y0;  // its first row from y0, in [0, L)
-        d += d < 0 ? L : 0;
-        unsigned long long m =
-            __ballot(i < n && ((d <= rhi && d + 2 >= rlo) || d - L + 2 >= rlo));
-        for (; m != 0; m &= m - 1) {
-            const RecLine<T>* e = list + k0 + (__ffsll(m) - 1);
-            int dx = x - e->xs, dy = y - e->ys;
-            dx += dx < 0 ? L : 0;
-            dy += dy < 0 ? L : 0;
-            const int dy1 = dy == L - 1 ? 0 : dy + 1;
-            if (dx < 3) {
-                const T w = e->wx[dx];
-                if (dy < 3) f0.add(w, e->wyf[dy]);
-                if (dy1 < 3) f1.add(w, e->wyf[dy1]);
-            }
+// Where the x pass of a small box sums the force of node (x, y0 + y) of its rows:
+// in float64 in the slot of the transform's buffer that takes the node's row pair
+// (two sums are as large as two values, and the thread that reads them writes the
+// slot), in float32 in an array of their own.
+template <typename T, int L>
+__device__ __forceinline__ int sum_slot(int y, int x) {
+    constexpr int LS = line_stride(L);
+    return sizeof(T) == 8 ? 2 * ((y >> 1) * LS + lpad(x)) + (y & 1) : y * L + x;
+}
+
+// The n records of a list, added to the sums acc (nacc of them, cleared here) of the
+// R rows from y0 of the plane: a thread takes one of a record's nine nodes in the
+// plane.  The sums are 64-bit integers, as in the spreading, so that they do not
+// depend on the order; |w F| 2^e2 < 2^55 (box_exponent) for each of at most
+// kSmallBlobs, so that none overflows and the quantum is below 2^-55 of the box's
+// largest force.  (Sums in registers, in a loop of every wave over the records of
+// its rows, took 17 us of the x pass for 247 blobs in one 16^3 box, which takes 7 so;
+// 512 such boxes in steady flow 186 and 78.)  Called by the whole block, n > 0; ends
+// with a barrier.
+template <typename T, int L, int R, int NTHR>
+__device__ __forceinline__ void add_records(const RecLine<T>* list, int n, int y0,
+                                            unsigned long long* acc, int nacc) {
+    for (int i = threadIdx.x; i < nacc / 2; i += NTHR)
+        reinterpret_cast<ulonglong2*>(acc)[i] = ulonglong2{0ull, 0ull};
+    __syncthreads();
+    for (int i = threadIdx.x; i < 9 * n; i += NTHR) {
+        const int k = i / 9, j = i - 9 * k;
+        const int ky = j / 3, kx = j - 3 * ky;
+        const RecLine<T>* e = list + k;
+        int y = e->ys + ky - y0, x = e->xs + kx;  // ys - y0 in (-L, L)
+        y += y < 0 ? L : 0;
+        y -= y >= L ? L : 0;
+        x -= x >= L ? L : 0;
+        if (y < R) {
+            const double c = (double)e->wx[kx] * (double)e->wyf[ky];
+            atomicAdd(acc + sum_slot<T, L>(y, x), (unsigned long long)(long long)rint(c));
         }
     }
-    out[0] = f0.value(e2);
-    out[1] = f1.value(e2);
+    __syncthreads();
+}
+
+// The force of a node from its sum (e2: kExpNonfinite where a force of the box is
+// not finite).
+template <typename T>
+__device__ __forceinline__ T sum_value(unsigned long long s, int e2) {
+    if (e2 == kExpNonfinite) return (T)__builtin_nan("");
+    return (T)ldexp((double)(long long)s, -e2);
 }
 
 // Planes with marks act of block zi of the ng that share a box's planes (and
@@ -503,8 +496,16 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     using G = Geo<T, L>;
     constexpr int NC = G::NC, R = G::R, NL = G::NL, LS = G::LS;
     constexpr int NTHR = threads_xf<T, L, SRC, STEADY>(), EX = NL * L / NTHR;
-    __shared__ cplx<T> buf[NL * LS];
+    // SRC_REC: the records of a block's rows and the sums of their forces.  The sums
+    // share the buffer in float64, the records (done with before it) in float32.
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr int LIST = (int)(kSmallBlobs * sizeof(RecLine<T>) / sizeof(cplx<T>));
+    __shared__ __align__(16) cplx<T> buf[REC && !F64 && LIST > NL * LS ? LIST : NL * LS];
     __shared__ cplx<T> tws[L];
+    __shared__ RecLine<T> list64[REC && F64 ? kSmallBlobs : 1];
+    __shared__ __align__(16) unsigned long long acc32[REC && !F64 ? R * L : 2];
+    unsigned long long* acc = F64 ? reinterpret_cast<unsigned long long*>(buf) : acc32;
+    constexpr int NACC = F64 ? 2 * NL * LS : R * L;
     __shared__ double red[16];
     const int tid0 = threadIdx.x;
     // blocks of a box are consecutive (G::NBX per box, a multiple of 8);
@@ -550,13 +551,14 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     }
     [[maybe_unused]] const T* add =
         (ADD || REC) && mk.add ? mk.add + (size_t)box * 3 * L * L * L : nullptr;
-    __shared__ RecLine<T> list[REC ? kSmallBlobs : 1];
-    int nlist = 0, e2 = 0;
+    [[maybe_unused]] int nlist = 0, e2 = 0;
     if constexpr (REC) {
         e2 = mk.fexp[box];
         const size_t b0 = (size_t)box * mk.mbox;
+        RecLine<T>* list = F64 ? list64 : reinterpret_cast<RecLine<T>*>(buf);
         nlist = plane_records<T, L, R, NTHR>(mk.rec + b0, mk.recf + 3 * b0, mk.mbox, comp, z, y0,
                                              e2, list, reinterpret_cast<int*>(red));
+        if (nlist > 0) add_records<T, L, R, NTHR>(list, nlist, y0, acc, NACC);
     }
     // KG iterations (2 KG nodes) per round: all loads of a round, the box
     // entries included (box_entries: loads only, in uniform branches), are
@@ -662,16 +664,10 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
             const int line = e / L;
             const int x = e - line * L;
             T val[2];
-            [[maybe_unused]] T lf[2];
-            if constexpr (REC) {
-                const int w0 = __builtin_amdgcn_readfirstlane(e);  // the wave's first element
-                const int w1 = w0 + WAVE - 1 < NL * L - 1 ? w0 + WAVE - 1 : NL * L - 1;
-                list_force<T, L, NTHR>(list, nlist, x, y0 + 2 * line, y0, 2 * (w0 / L),
-                                       2 * (w1 / L) + 1, e2, lf);
-            }
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
-                if (REC) fv[g][hh] = lf[hh] + fv[g][hh];
+                if (REC && (nlist > 0 || e2 == kExpNonfinite))
+                    fv[g][hh] = sum_value<T>(acc[sum_slot<T, L>(2 * line + hh, x)], e2) + fv[g][hh];
                 if (ADD) fv[g][hh] = box_entries_sum(eb[g][hh]) + fv[g][hh];
                 else if (BOX) fv[g][hh] = box_entries_sum(eb[g][hh]);
                 sf += (double)fv[g][hh];
@@ -1102,13 +1098,13 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // whole launch would be n blocks for the batch, for mbox blobs a box.  One plane
 // a block while the launch fills the chip a few times at most: blocks of planes
 // without a mark end at once, and a block that takes up to L / 8 planes runs
-// them one after another (19 particles in one 96^3 box, float32: x pass 17 us
-// against 63, y 6.3 and 25, inverse plane 12 and 54; 4 boxes 34 and 66).  Above,
+// them one after another (19 particles in one 96^3 box, float32: x pass 15 us
+// against 47, y 6.3 and 25, inverse plane 12 and 54; 4 boxes 32 and 53).  Above,
 // the empty blocks cost more than the chain (32 64^3 boxes of two particles: x
-// pass of 24,576 blocks 33 against 27; 32 48^3, 13,824: 21 and 19), at half
+// pass of 24,576 blocks 32 against 25; 32 48^3, 13,824: 18.6 and 16.5), at half
 // the number in the inverse plane pass, whose blocks take more LDS (32 64^3, 6,144:
 // 19 and 16).  So few blobs that at most half the planes can be marked are
-// dealt out too (one particle in 128^3: inverse plane pass 9.4 against 13.3).
+// dealt out too (one particle in 128^3: inverse plane pass 9.4 against 13.4).
 inline int plane_blocks(int64_t n, int mbox, int L) { return n <= 8192 && 8 * mbox > L ? L : 8; }
 
 template <typename T, int L>

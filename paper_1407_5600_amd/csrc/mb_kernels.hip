@@ -617,12 +617,12 @@ struct BoxBin {
     int* fexp;
 };
 
-// The e with |w F h^-3| 2^e < 2^51 for every product w of kernel weights (at
+// The e with |w F h^-3| 2^e < 2^55 for every product w of kernel weights (at
 // most (2/3)^3 < 2^-1.7) and every force of a box, from the high word of its
 // largest |F h^-3| in float64; kExpNonfinite for an infinity or NaN.
 __device__ __forceinline__ int box_exponent(unsigned hi) {
     const int b = (int)(hi >> 20);  // biased exponent: |F h^-3| < 2^(b - 1022)
-    return b == 2047 ? kExpNonfinite : 51 - ((b > 0 ? b : 1) - 1023);
+    return b == 2047 ? kExpNonfinite : 55 - ((b > 0 ? b : 1) - 1023);
 }
 
 template <typename T, bool SPRINGS>
@@ -2196,7 +2196,7 @@ static void scan_tiles(mb_grid* g, hipStream_t s) {
 
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp) {
     const int64_t mbox = M / g->tiles.nbox;
-    return M > 0 && mbox <= kSmallBlobs && g->tiles.n <= kSmallTiles &&
+    return M > 0 && mbox <= kSmallBlobs && 4 * mbox <= g->N && g->tiles.n <= kSmallTiles &&
            (!sp || mbox <= (int64_t)sp->ppb * sp->nb);
 }
 

@@ -103,7 +103,7 @@ def test_force_scale_of_few_blobs(torch_cuda, prec, ks):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
-@pytest.mark.parametrize("L,P,nbox", [(8, 1, 3), (24, 3, 9), (24, 1, 64), (64, 2, 32), (96, 19, 1),
+@pytest.mark.parametrize("L,P,nbox", [(8, 1, 3), (8, 9, 2), (8, 10, 2), (24, 3, 9), (24, 1, 64), (64, 2, 32), (96, 19, 1),
                                       (128, 1, 1), (144, 1, 1), (192, 2, 1)])
 def test_marked_planes_by_block(torch_cuda, L, P, nbox, prec):
     """Steady calls form only the z planes that hold blobs until their last
