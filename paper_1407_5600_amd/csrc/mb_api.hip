@@ -383,8 +383,6 @@ mb_status mb_grid_create_batch(const mb_grid_desc* desc, int32_t nbox, mb_grid**
     g->btiles = make_box_tiles(d.L, g->tiles);
     link_box_tiles(g->tiles, g->btiles);
     g->rec_size = record_size(d.precision);
-    // springs blocks hold at least one particle of at least one blob
-    g->force_blocks_cap = (int)std::max<int64_t>(d.max_blobs, 1);
     g->perm_m = -1;
     if (d.external_workspace) {
         *out = g;  // no scratch until mb_grid_set_workspace
@@ -1295,7 +1293,6 @@ mb_status mb_step_noalloc(const mb_grid_desc* desc, const mb_springs* sp, int64_
     g.btiles = make_box_tiles(d.L, g.tiles);
     link_box_tiles(g.tiles, g.btiles);
     g.rec_size = record_size(d.precision);
-    g.force_blocks_cap = (int)std::max<int64_t>(d.max_blobs, 1);
     g.ws_owned = false;
     ws_bind(&g, base);
     set_scan_blocks(&g);

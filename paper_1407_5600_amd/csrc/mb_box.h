@@ -56,29 +56,6 @@ __device__ __forceinline__ AxisSrc box_src_z(const Tiles& tl, int z) {
                         (tl.tx + 3) * (tl.ty + 3));
 }
 
-// Sum of the entries of component array Ea (E + a * tiles * box volume)
-// holding the node with the given sources, formed so that the loads of a
-// node are issued together: an absent x, y or z source reads the node's own
-// entry again and is multiplied by zero.
-template <typename T>
-__device__ __forceinline__ T box_sum(const T* __restrict__ Ea, const AxisSrc& sx,
-                                     const AxisSrc& sy, const AxisSrc& sz) {
-    const int x0 = sx.off[0];
-    const int x1 = sx.n > 1 ? sx.off[1] : x0;
-    const T mx = sx.n > 1 ? T(1) : T(0);
-    const int y1 = sy.n > 1 ? sy.off[1] : sy.off[0];
-    const int z1 = sz.n > 1 ? sz.off[1] : sz.off[0];
-    const T my = sy.n > 1 ? T(1) : T(0);
-    const T mz = sz.n > 1 ? T(1) : T(0);
-#define MB_ROW(o) (Ea[(o) + x0] + mx * Ea[(o) + x1])
-    const T r0 = MB_ROW(sz.off[0] + sy.off[0]);
-    const T r1 = MB_ROW(sz.off[0] + y1);
-    const T r2 = MB_ROW(z1 + sy.off[0]);
-    const T r3 = MB_ROW(z1 + y1);
-#undef MB_ROW
-    return (r0 + my * r1) + mz * (r2 + my * r3);
-}
-
 // The entries of component array Ea holding a node, loaded without
 // arithmetic: e[s][0] (first x source) and e[s][1] (second x source, lane
 // masked) for the (z, y) source pairs s = 0 (z0, y0), 1 (z0, y1), 2 (z1, y0),
@@ -86,7 +63,7 @@ __device__ __forceinline__ T box_sum(const T* __restrict__ Ea, const AxisSrc& sx
 // y and z counts are uniform over the wave when the lanes share y and z, so
 // the branches do not diverge, and since nothing is added inside them the
 // loads of several nodes stay in flight together; box_entries_sum then adds
-// them in the order of box_sum.
+// them: the x sources of each pair, then the y pairs, then z.
 template <typename T>
 __device__ __forceinline__ void box_entries(const T* __restrict__ Ea, const AxisSrc& sx,
                                             const AxisSrc& sy, const AxisSrc& sz,
@@ -118,14 +95,5 @@ __device__ __forceinline__ T box_entries_sum(const T e[4][2]) {
     return ((e[0][0] + e[0][1]) + (e[1][0] + e[1][1])) +
            ((e[2][0] + e[2][1]) + (e[3][0] + e[3][1]));
 }
-
-// Node (x, y, z) of component a.
-template <typename T>
-__device__ __forceinline__ T box_sum(const T* __restrict__ E, const Tiles& tl,
-                                     int a, int x, int y, int z) {
-    const T* Ea = E + (size_t)a * tl.n * box_volume(tl);
-    return box_sum(Ea, box_src_x(tl, x), box_src_y(tl, y), box_src_z(tl, z));
-}
-
 
 }  // namespace mb

@@ -566,11 +566,10 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
     // pair and has them (128^3: 21.4 against 20.7 us, 256^3: 209 against 202);
     // one elsewhere (float64 128^3: 34.5 against 37.5 with two, whose registers
     // cost a wave; 96^3: 14.0 against 15.5).
-    constexpr bool UNI_ROWS = L % WAVE == 0 && NTHR % L == 0;
-    constexpr int KG = sizeof(T) == 4 && UNI_ROWS && BOX && !STEADY && EX % 2 == 0 ? 2 : 1;
-    static_assert(EX % KG == 0, "rounds of the x pass");
-    // a wave's lanes share y when L is a multiple of the wave
+    // UNI: a wave's lanes share y.
     constexpr bool UNI = L % WAVE == 0 && NTHR % L == 0;
+    constexpr int KG = sizeof(T) == 4 && UNI && BOX && !STEADY && EX % 2 == 0 ? 2 : 1;
+    static_assert(EX % KG == 0, "rounds of the x pass");
     // with UNI, a thread's x (and its neighbours and x box sources) is the
     // same in every round and its line differs by a constant per round, the
     // wave's rows are uniform: each load is a uniform row base plus the
@@ -652,8 +651,7 @@ k_x_fwd(const T* __restrict__ v, const T* __restrict__ f, Tiles tl, ForceSrc<T> 
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) {
                     const int y = y0 + 2 * line + hh;
-                    const int yu = UNI ? __builtin_amdgcn_readfirstlane(y) : y;
-                    box_entries(Ec, bx, box_src_y(tl, yu), bz, eb[g][hh]);
+                    box_entries(Ec, bx, box_src_y(tl, y), bz, eb[g][hh]);
                 }
             }
         }
@@ -1025,7 +1023,7 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
     // stage the half spectrum: F[kx][ky] at row ky, column kx (0..H)
     const cplx<T>* in = A + (size_t)cz * NC * L;
     {
-        // every load of the thread issued before the LDS stores (at most 17
+        // every load of the thread issued before the LDS stores (at most 11
         // complex values per thread: K <= (L/2 + 1) L / NTHR)
         constexpr int K = (NC * L + NTHR - 1) / NTHR;
         cplx<T> ld[K];
@@ -1134,6 +1132,7 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         if (F.planes) mk.act = g->d_act;
         mk.ng = plane_blocks((int64_t)G::NBX * nbox, F.mbox, L);
     }
+    if (!small_edge(L) && F.src == SolveForce<T>::RECORDS) return hipErrorInvalidValue;
     unsigned char* act = mk.act ? g->d_act : nullptr;
     const int part = F.planes && F.planes_out ? 1 : 0;
 #define MB_XF(SR, ST)                                                                     \
@@ -1144,8 +1143,10 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         if (rhs) MB_XF(SRC_FIELD, true);
         else MB_XF(SRC_FIELD, false);
     } else if (F.src == SolveForce<T>::RECORDS) {
-        if (rhs) MB_XF(SRC_REC, true);
-        else MB_XF(SRC_REC, false);
+        if constexpr (small_edge(L)) {
+            if (rhs) MB_XF(SRC_REC, true);
+            else MB_XF(SRC_REC, false);
+        }
     } else if (mk.add) {
         if (rhs) MB_XF(SRC_BOX_ADD, true);
         else MB_XF(SRC_BOX_ADD, false);
@@ -1158,8 +1159,11 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
 #define MB_Y(ID, INV, AC)                                                                 \
     MB_LAUNCH(g, ID, s, (k_y<T, L, INV, AC>), 3 * (AC ? ngy : L) * G::NCHY * nbox, G::TY, 0, \
               A, tw, (const unsigned char*)act, ngy)
-    if (act) MB_Y(K_FFT_Y_FWD, false, true);
-    else MB_Y(K_FFT_Y_FWD, false, false);
+    if (act) {
+        if constexpr (small_edge(L)) MB_Y(K_FFT_Y_FWD, false, true);
+    } else {
+        MB_Y(K_FFT_Y_FWD, false, false);
+    }
     const T c0 = steady ? T(0) : (T)(g->d.rho / g->d.dt * N);
     const T c1 = steady ? (T)(g->d.eta * N) : (T)(0.5 * g->d.eta * N);
     const double mv = rhs ? 0.0 : 1.0 / N;
@@ -1169,8 +1173,11 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     MB_LAUNCH(g, K_FFT_Z_SPECTRAL, s, (k_z_solve<T, L, AC>), G::NC * (L / G::WZ) * nbox,   \
               G::TZ, 0, A, tw, (const cplx<T>*)g->d_dsym, (const T*)g->d_d2, c0, c1, zm,   \
               g->d_psum, G::NBX / 3, mv, mf, (const unsigned char*)act, part)
-    if (act) MB_Z(true);
-    else MB_Z(false);
+    if (act) {
+        if constexpr (small_edge(L)) MB_Z(true);
+    } else {
+        MB_Z(false);
+    }
 #undef MB_Z
     if constexpr (G::XY) {
         const int ngx = plane_blocks((int64_t)2 * G::NBXY * nbox, F.mbox, L);
@@ -1181,8 +1188,11 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
             MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, false>), G::NBXY * nbox, G::TXY, 0, A,
                       tw, v_out, act, L);
     } else {
-        if (part) MB_Y(K_FFT_Y_INV, true, true);
-        else MB_Y(K_FFT_Y_INV, true, false);
+        if (part) {
+            if constexpr (small_edge(L)) MB_Y(K_FFT_Y_INV, true, true);
+        } else {
+            MB_Y(K_FFT_Y_INV, true, false);
+        }
 #define MB_XI(KEEP)                                                                       \
     MB_LAUNCH(g, K_FFT_X_INV, s, (k_x_inv<T, L, KEEP>), 3 * L * (L / G::RI) * nbox, G::TXI, 0, A, \
               tw, v_out, act, part)

@@ -153,7 +153,6 @@ struct mb_grid {
     int scheme;            // mb_scheme of the steps
     double* d_tile_part;   // [tiles][4]  (sum v_a, max |Dv|)
     double* d_force_part;  // [force blocks][3]
-    int force_blocks_cap;
     // timing
     uint32_t timing;    // bit mask of timed kernel ids
     std::vector<mb::TimerPair> pending;
@@ -217,6 +216,9 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
 // number of boxes, so that a batch steps as its boxes would alone.
 constexpr int kSmallBlobs = 256;
 constexpr int kSmallTiles = 4096;  // 16 KB of LDS counts
+constexpr int kMaxTileCells = 2048;  // largest of MB_TILE_SHAPES
+// Edges whose boxes can be small (up to 192): only they have the kernels of the path.
+constexpr bool small_edge(int L) { return (int64_t)L * L * L <= (int64_t)kSmallTiles * kMaxTileCells; }
 constexpr int kExpNonfinite = 1 << 20;  // box exponent: a force of the box is not finite
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp);
 // Springs and records of small boxes, with tiles by tile (for the spreading and

@@ -1036,7 +1036,7 @@ __device__ __forceinline__ void store4(float* Ea, int i, const float (&v)[4]) {
 // block and no contribution is masked.  The box is written to the box
 // tile's slot of the box array E[a][box tile][box node]; a node of the
 // field is the sum of the entries of the (at most 8) boxes holding it
-// (box_sum), formed by the fold kernel or by the first FFT pass as it reads
+// (box_entries_sum), formed by the fold kernel or by the first FFT pass as it reads
 // the force.  Box tiles larger than the binning tiles (16^3 against 16x8x8)
 // carry less halo: 1.67 against 2.25 box entries per node, each written
 // here and read by the x pass.
