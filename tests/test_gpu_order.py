@@ -169,3 +169,100 @@ def test_stalled_scan_is_reported_by_the_next_call_that_waits(torch_cuda, waits)
     assert int(flag) == 0
     call()
     assert torch.equal(g.interpolate(q, v), ref)
+
+
+@pytest.mark.parametrize("scheme", ["euler", "midpoint"])
+def test_graph_of_many_blobs_replays_as_eager_steps(torch_cuda, scheme):
+    """Boxes of more than 256 blobs, whose captured step counts, scans, places,
+    spreads and interpolates by tiles (eager steps scan inside the kernel that
+    places the records), beside one of few: equal to eager steps bit for bit
+    after every call, with eager work on the same grids between the replays."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    from paper_1407_5600_amd.binding import step_graph
+    specs = [(32, 40, 1, "fp64", "unsteady"), (32, 24, 2, "mixed", "steady"),
+             (48, 21, 1, "mixed", "unsteady"), (24, 2, 3, "fp64", "steady")]
+    say("graph of many blobs", scheme)
+    grids, springs, forces, state = [], [], [], ([], [])
+    for L, P, nbox, prec, mode in specs:
+        rng = np.random.default_rng(L + P)
+        q0, spr = chains(rng, P * nbox, L)
+        q0 += rng.uniform(0.0, L, size=(P * nbox, 1, 3))
+        springs.append(Springs(*spr))
+        forces.append(dev(torch, rng.standard_normal((P * nbox, 3))))
+        pair = []
+        for qs in state:
+            g = Grid(L, precision=prec, mode=mode, scheme=scheme, max_blobs=P * nbox * NB,
+                     nbox=nbox)
+            qs.append((dev(torch, q0.reshape(-1, 3)), g.field()))
+            pair.append(g)
+        grids.append(pair)
+    for n in (3, 1, 5, 2):
+        qs, vs = zip(*state[0])
+        step_graph([p[0] for p in grids], springs, list(qs), list(vs), forces, None, n)
+        for (_, g), sp, F, (q, v) in zip(grids, springs, forces, state[1]):
+            g.step(sp, q, v, F, n)
+        torch.cuda.synchronize()
+        for (q, v), (qe, ve) in zip(*state):
+            assert torch.equal(q, qe) and torch.equal(v, ve)
+        for (g, _), (q, v) in zip(grids, state[0]):
+            g.interpolate(q, v)  # (bins the grid's blobs anew)
+
+
+@pytest.mark.parametrize("L,prec", [(16, "fp64"), (48, "fp64"), (48, "mixed"), (64, "fp64"),
+                                    (64, "mixed"), (72, "fp64"), (72, "mixed"), (96, "fp64"),
+                                    (96, "mixed"), (128, "mixed"), (144, "fp64")])
+def test_step_from_boxes_at_pass_shapes(torch_cuda, L, prec):
+    """One step of 299 blobs, whose forces are spread through the boxes of
+    tiles, from a random field, against the oracle, at the edges whose forward x
+    pass has rows and elements per thread of its own."""
+    torch = torch_cuda
+    import oracle
+    from paper_1407_5600_amd import Grid, Springs
+    say("step from boxes", L, prec)
+    P = 23
+    rng = np.random.default_rng(L)
+    q0, spr = chains(rng, P, L)
+    q0 += rng.uniform(0.0, L, size=(P, 1, 3))
+    F0 = rng.standard_normal((P, 3))
+    g = Grid(L, precision=prec, max_blobs=P * NB)
+    v = dev(torch, rng.standard_normal((3, L, L, L)) + 0.5).to(g.field_dtype)
+    ref = oracle.step(oracle.params(L), dict(zip(("nb", "pa", "pb", "r0", "k"), spr)),
+                      q0.reshape(-1, 3), v.double().cpu().numpy(), F0, 1)
+    g.step(Springs(*spr), dev(torch, q0.reshape(-1, 3)), v, dev(torch, F0))
+    r = np.linalg.norm(v.double().cpu().numpy() - ref["v"]) / np.linalg.norm(ref["v"])
+    say(f"{r:.2e}")
+    assert r <= (1e-12 if prec == "fp64" else 1e-5)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_few_blobs_at_192(torch_cuda, prec):
+    """247 blobs in 192^3 take the few-blob path with tiles of 32 x 8 x 8 cells
+    (3,456 tiles) and the general one with the default tiles (6,912): the same
+    spread field, velocities, derivatives and step."""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    L, P = 192, 19
+    tol = 1e-12 if prec == "fp64" else 1e-5
+    rng = np.random.default_rng(5)
+    q0, spr = chains(rng, P, L)
+    q0 += rng.uniform(-L, 2 * L, size=(P, 1, 3))
+    F0, W0 = rng.standard_normal((P, 3)), rng.standard_normal((P * NB, 3))
+    out = []
+    for few in (True, False):
+        say("few blobs at 192", prec, few)
+        g = Grid(L, precision=prec, max_blobs=P * NB)
+        if few:
+            g.set_tiles(32, 8, 8)
+        q, W, F = dev(torch, q0.reshape(-1, 3)), dev(torch, W0), dev(torch, F0)
+        v = torch.randn(g.field_shape, dtype=torch.float64, device="cuda",
+                        generator=torch.Generator("cuda").manual_seed(1)).to(g.field_dtype)
+        dq = torch.zeros_like(q)
+        got = [g.spread(q, W), g.interpolate(q, v), g.interpolate_grad(q, v, W, dq)]
+        g.step(Springs(*spr), q, v, F)
+        out.append(got + [v, q])
+    for name, a, b in zip(("f", "u", "dq", "v", "q"), *out):
+        a, b = a.double(), b.double()
+        r = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
+        say(name, f"{r:.2e}")
+        assert r <= tol
