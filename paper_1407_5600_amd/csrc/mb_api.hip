@@ -893,7 +893,9 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     if (replays > 0) {
         if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
+            for (int i = 0; i < ngrids; ++i) grids[i]->own_capture = true;
             st = one_step(cs, !tail);
+            for (int i = 0; i < ngrids; ++i) grids[i]->own_capture = false;
             hipError_t ec = hipStreamEndCapture(cs, &graph);
             if (st == MB_OK) e = ec;
         }

@@ -139,6 +139,8 @@ struct mb_grid {
                         // of each box's fixed-point force sums
     int* d_perm;        // [max_blobs] blob of each sorted record
     int64_t perm_m;     // d_perm is a permutation of [0, perm_m) (-1: none)
+    bool own_capture;   // mb_step_graph is capturing a step
+    bool replayed;      // a caller captured a call: its replays write d_perm unseen
     bool binned_small;  // the last binning was by box (small_boxes)
     void* d_rec;        // [max_blobs] records
     size_t rec_size;

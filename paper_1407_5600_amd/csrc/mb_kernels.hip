@@ -2194,6 +2194,26 @@ static void scan_tiles(mb_grid* g, hipStream_t s) {
               (int64_t)nt, g->d_bsum, g->d_offs);
 }
 
+// The stream is being captured (or cannot be asked).
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The blobs that d_perm will be a permutation of after a binning of M: none once a
+// caller has captured a call on the grid, since each replay writes d_perm, for its
+// number of blobs, without the grid seeing it, and an order taken into a capture
+// would be read there whatever has become of it by then (the graph of
+// mb_step_graph lives within its call).
+static int64_t kept_order(mb_grid* g, int64_t M, hipStream_t s) {
+    if (!g->own_capture && !g->replayed && capturing(s)) g->replayed = true;
+    return g->replayed ? -1 : M;
+}
+
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp) {
     const int64_t mbox = M / g->tiles.nbox;
     return M > 0 && mbox <= kSmallBlobs && 4 * mbox <= g->N && g->tiles.n <= kSmallTiles &&
@@ -2218,7 +2238,7 @@ static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M
     MB_LAUNCH(g, kid, s, (k_bin_box<T, SPRINGS>), g->tiles.nbox, BLK, lds, sp, bb, g->tiles, q, F,
               F2, f2scale, Fsum, 1.0 / g->d.h, g->L, fscale, rec_geo<T>(g), rec_force<T>(g),
               g->d_perm, fpart, finite_flag(g));
-    g->perm_m = M;
+    g->perm_m = kept_order(g, M, s);
     g->binned_small = true;
     return hipGetLastError();
 }
@@ -2244,7 +2264,7 @@ hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s, bool
     g->binned_small = false;
     if (M > 0 && !counted) {
         // the previous sorted order, when it is a permutation of these blobs
-        const int* order = g->perm_m == M ? g->d_perm : nullptr;
+        const int* order = kept_order(g, M, s) == M && g->perm_m == M ? g->d_perm : nullptr;
         MB_LAUNCH(g, K_BIN_COUNT, s, k_tile_count, blocks_for(M), BLK, 0, q, order, M,
                   M / g->tiles.nbox, 1.0 / g->d.h, g->L, g->tiles, g->d_count, g->d_tile,
                   g->d_rank);
@@ -2337,7 +2357,7 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
     MB_LAUNCH(g, K_BIN_SCATTER, s, k_bin_scatter<T>, blocks_for(M), BLK, 0, q, F,
               M, 1.0 / h, g->L, sc, g->d_offs, g->d_tile, g->d_rank,
               rec_geo<T>(g), rec_force<T>(g), g->d_perm, finite_flag(g), scan);
-    g->perm_m = M;
+    g->perm_m = g->replayed ? -1 : M;
     return hipGetLastError();
 }
 
@@ -2365,18 +2385,12 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
               springs_lds(sp), sp, q, Fext, Gblob, P, 1.0 / h, g->L, 1.0 / (h * h * h), g->d_offs,
               g->d_tile, g->d_rank, rec_geo<T>(g), rec_force<T>(g), g->d_perm,
               force_sums ? g->d_force_part : nullptr, finite_flag(g), sc);
-    g->perm_m = M;
+    g->perm_m = g->replayed ? -1 : M;
     return hipGetLastError();
 }
 
 bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles) {
-    if ((int64_t)g->tiles.n * g->tiles.nbox > tiles) return false;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st == hipStreamCaptureStatusNone;
+    return (int64_t)g->tiles.n * g->tiles.nbox <= tiles && !capturing(s);
 }
 
 hipError_t spring_forces(const SpringsDev& sp, int64_t P, const double* q,

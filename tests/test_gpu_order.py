@@ -266,3 +266,45 @@ def test_few_blobs_at_192(torch_cuda, prec):
         r = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
         say(name, f"{r:.2e}")
         assert r <= tol
+
+
+@pytest.mark.parametrize("P", [30, 3])
+def test_steps_between_replays_of_a_captured_step(torch_cuda, P):
+    """A caller captures one step of 390 (39) blobs and replays it between eager
+    steps of more and of fewer blobs on the same grid: every call gives what a
+    grid of its own gives, bit for bit.  (A replay sorts its blobs into the
+    grid's order without the grid seeing it, so neither side may take the order
+    that the other left.)"""
+    torch = torch_cuda
+    from paper_1407_5600_amd import Grid, Springs
+    L = 32
+    rng = np.random.default_rng(P)
+    q0, spr = chains(rng, 60, L)
+    q0 += rng.uniform(0.0, L, size=(60, 1, 3))
+    sp = Springs(*spr)
+    F = dev(torch, rng.standard_normal((60, 3)))
+
+    def start(n):
+        return dev(torch, q0[:n].reshape(-1, 3)), Grid(L).field(), F[:n].contiguous()
+
+    g = Grid(L, max_blobs=60 * NB)
+    mine, own = {}, {}
+    for n in (P, 45, 25):
+        mine[n], own[n] = start(n), start(n) + (Grid(L, max_blobs=60 * NB),)
+    say("captured step between eager ones", P)
+    g.step(sp, *mine[P], 1)  # (before the capture, as torch asks)
+    own[P][3].step(sp, *own[P][:3], 1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.step(sp, *mine[P], 1)
+    for k, n in enumerate((P, 45, P, 45, 25, P, 25, 45, P, P)):
+        say("call", k, n)
+        if n == P:
+            graph.replay()
+        else:
+            g.step(sp, *mine[n], 1)
+        own[n][3].step(sp, *own[n][:3], 1)
+        torch.cuda.synchronize()
+        for a, b in zip(mine[n], own[n]):
+            assert torch.equal(a, b)
