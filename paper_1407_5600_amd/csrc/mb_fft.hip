@@ -1093,17 +1093,18 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 }
 
 // Blocks that share the marked planes of a box (active_planes) in a pass whose
-// whole launch would be n blocks for the batch, for mbox blobs a box.  One plane
-// a block while the launch fills the chip a few times at most: blocks of planes
-// without a mark end at once, and a block that takes up to L / 8 planes runs
-// them one after another (19 particles in one 96^3 box, float32: x pass 15 us
+// whole launch would be n blocks for the batch, for about `marked` planes a box.
+// One plane a block while the launch fills the chip a few times at most: blocks of
+// planes without a mark end at once, and a block that takes up to L / 8 planes
+// runs them one after another (19 particles in one 96^3 box, float32: x pass 15 us
 // against 47, y 6.3 and 25, inverse plane 12 and 54; 4 boxes 32 and 53).  Above,
 // the empty blocks cost more than the chain (32 64^3 boxes of two particles: x
 // pass of 24,576 blocks 32 against 25; 32 48^3, 13,824: 18.6 and 16.5), at half
 // the number in the inverse plane pass, whose blocks take more LDS (32 64^3, 6,144:
-// 19 and 16).  So few blobs that at most half the planes can be marked are
-// dealt out too (one particle in 128^3: inverse plane pass 9.4 against 13.4).
-inline int plane_blocks(int64_t n, int mbox, int L) { return n <= 8192 && 8 * mbox > L ? L : 8; }
+// 19 and 16).  A few marks, at most two a block, are dealt out too (one particle in
+// each of 8 64^3 boxes, float64: a step 53.5 us against 58.5; in 128^3: inverse plane
+// pass 9.4 and 13.4).
+inline int plane_blocks(int64_t n, int marked, int L) { return n <= 8192 && 4 * marked > L ? L : 8; }
 
 template <typename T, int L>
 hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_out,
@@ -1130,7 +1131,7 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         mk.mbox = F.mbox;
         mk.fexp = g->d_rank;
         if (F.planes) mk.act = g->d_act;
-        mk.ng = plane_blocks((int64_t)G::NBX * nbox, F.mbox, L);
+        mk.ng = plane_blocks((int64_t)G::NBX * nbox, F.marked, L);
     }
     if (!small_edge(L) && F.src == SolveForce<T>::RECORDS) return hipErrorInvalidValue;
     unsigned char* act = mk.act ? g->d_act : nullptr;
@@ -1155,7 +1156,7 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
         else MB_XF(SRC_BOX, false);
     }
 #undef MB_XF
-    const int ngy = plane_blocks((int64_t)3 * L * G::NCHY * nbox, F.mbox, L);
+    const int ngy = plane_blocks((int64_t)3 * L * G::NCHY * nbox, F.marked, L);
 #define MB_Y(ID, INV, AC)                                                                 \
     MB_LAUNCH(g, ID, s, (k_y<T, L, INV, AC>), 3 * (AC ? ngy : L) * G::NCHY * nbox, G::TY, 0, \
               A, tw, (const unsigned char*)act, ngy)
@@ -1180,7 +1181,7 @@ hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_o
     }
 #undef MB_Z
     if constexpr (G::XY) {
-        const int ngx = plane_blocks((int64_t)2 * G::NBXY * nbox, F.mbox, L);
+        const int ngx = plane_blocks((int64_t)2 * G::NBXY * nbox, F.marked, L);
         if (part)
             MB_LAUNCH(g, K_FFT_XY_INV, s, (k_xy_inv<T, L, true>), 3 * ngx * nbox, G::TXY, 0,
                       A, tw, v_out, act, ngx);

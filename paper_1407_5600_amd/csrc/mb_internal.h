@@ -290,8 +290,10 @@ struct SolveForce {
     // the explicit half is left out (v_in = 0, unread)
     bool rhs_only = false;
     // RECORDS in steady flow without f: the binning marked the z planes that
-    // hold nodes of the blobs, and the transforms pass over the others
+    // hold nodes of the blobs, and the transforms pass over the others; marked:
+    // about how many of a box
     bool planes = false;
+    int marked = 0;
     // with planes: only these are written to v_out, for a field that is
     // interpolated at those blobs and then overwritten; the interpolation
     // then clears the marks (else the solve does)
