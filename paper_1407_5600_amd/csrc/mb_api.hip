@@ -861,10 +861,16 @@ mb_status mb_step_graph(int32_t ngrids, mb_grid* const* grids,
     hipStream_t caller = (hipStream_t)stream;
     int done = 0;
     // an eager first step when a grid has no sorted order from an earlier
-    // binning of these blobs, so that the captured binning uses it
+    // binning of these blobs, so that the captured binning uses it (small boxes:
+    // when the grid has not binned any, so that the first launches of its kernels
+    // are not in a capture)
     bool warm = true;
-    for (int i = 0; i < ngrids; ++i)
-        if (grids[i]->perm_m != nparticles[i] * springs[i]->nb) warm = false;
+    for (int i = 0; i < ngrids; ++i) {
+        const int64_t M = nparticles[i] * springs[i]->nb;
+        const SpringsDev sd = springs_dev(springs[i]);
+        if (small_boxes(grids[i], M, &sd) ? !grids[i]->binned_small : grids[i]->perm_m != M)
+            warm = false;
+    }
     if (!warm) {
         st = one_step(caller, nsteps == 1);
         if (st != MB_OK) return st;

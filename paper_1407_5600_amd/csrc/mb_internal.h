@@ -134,11 +134,11 @@ struct mb_grid {
     int* d_offs;        // [tiles + 1]
     int* d_bsum;        // scan block sums
     int nscan;          // scan blocks
-    int* d_tile;        // [max_blobs] tile of each blob
+    int* d_tile;        // [max_blobs] tile of each blob; small boxes: blob of each record
     int* d_rank;        // [max_blobs] place among its tile's blobs; small boxes: [nbox] exponent
                         // of each box's fixed-point force sums
     int* d_perm;        // [max_blobs] blob of each sorted record
-    int64_t perm_m;     // d_perm is a permutation of [0, perm_m) (-1: none)
+    int64_t perm_m;     // d_perm is a permutation of [0, perm_m) (-1: none; small boxes leave it)
     bool own_capture;   // mb_step_graph is capturing a step
     bool replayed;      // a caller captured a call: its replays write d_perm unseen
     bool binned_small;  // the last binning was by box (small_boxes)
@@ -253,6 +253,14 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
 constexpr int kFusedTiles = 4096;
 constexpr int kFusedScatterTiles = 1536;
 bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles);
+// Called (by fused_scan_ok) before a binning by tile: whether the stream is being
+// captured.  Where it is, by the caller, the order of the blobs that the grid keeps
+// is no more used: each replay writes d_perm, for its number of blobs, without the
+// grid seeing it, and an order taken into the graph would be read there whatever has
+// become of it by then.  (The graph of mb_step_graph lives within its call.)
+bool note_capture(mb_grid* g, hipStream_t s);
+// Blob of each record of the last binning.
+inline int* record_blobs(mb_grid* g) { return g->binned_small ? g->d_tile : g->d_perm; }
 hipError_t spring_forces(const SpringsDev& sp, int64_t P, const double* q,
                          const double* Fext, double* F, hipStream_t s,
                          mb_grid* timing_grid, const double* Gblob = nullptr);

@@ -2194,26 +2194,6 @@ static void scan_tiles(mb_grid* g, hipStream_t s) {
               (int64_t)nt, g->d_bsum, g->d_offs);
 }
 
-// The stream is being captured (or cannot be asked).
-static bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
-// The blobs that d_perm will be a permutation of after a binning of M: none once a
-// caller has captured a call on the grid, since each replay writes d_perm, for its
-// number of blobs, without the grid seeing it, and an order taken into a capture
-// would be read there whatever has become of it by then (the graph of
-// mb_step_graph lives within its call).
-static int64_t kept_order(mb_grid* g, int64_t M, hipStream_t s) {
-    if (!g->own_capture && !g->replayed && capturing(s)) g->replayed = true;
-    return g->replayed ? -1 : M;
-}
-
 bool small_boxes(const mb_grid* g, int64_t M, const SpringsDev* sp) {
     const int64_t mbox = M / g->tiles.nbox;
     return M > 0 && mbox <= kSmallBlobs && 4 * mbox <= g->N && g->tiles.n <= kSmallTiles &&
@@ -2237,8 +2217,7 @@ static hipError_t bin_boxes(mb_grid* g, int kid, const SpringsDev& sp, int64_t M
         (sort ? (size_t)((bb.n + 1) / 2) * sizeof(double) : 0) + (SPRINGS ? springs_lds(sp) : 0);
     MB_LAUNCH(g, kid, s, (k_bin_box<T, SPRINGS>), g->tiles.nbox, BLK, lds, sp, bb, g->tiles, q, F,
               F2, f2scale, Fsum, 1.0 / g->d.h, g->L, fscale, rec_geo<T>(g), rec_force<T>(g),
-              g->d_perm, fpart, finite_flag(g));
-    g->perm_m = kept_order(g, M, s);
+              g->d_tile, fpart, finite_flag(g));
     g->binned_small = true;
     return hipGetLastError();
 }
@@ -2264,7 +2243,7 @@ hipError_t bin_blobs(mb_grid* g, int64_t M, const double* q, hipStream_t s, bool
     g->binned_small = false;
     if (M > 0 && !counted) {
         // the previous sorted order, when it is a permutation of these blobs
-        const int* order = kept_order(g, M, s) == M && g->perm_m == M ? g->d_perm : nullptr;
+        const int* order = !g->replayed && g->perm_m == M ? g->d_perm : nullptr;
         MB_LAUNCH(g, K_BIN_COUNT, s, k_tile_count, blocks_for(M), BLK, 0, q, order, M,
                   M / g->tiles.nbox, 1.0 / g->d.h, g->L, g->tiles, g->d_count, g->d_tile,
                   g->d_rank);
@@ -2350,7 +2329,9 @@ hipError_t bin_records(mb_grid* g, int64_t M, const double* q, const double* F, 
         e = blob_axpy(3 * M, F2, f2scale, F, Fsum, s);
         F = Fsum;
     }
-    const bool fuse = M > 0 && fused_scan_ok(g, s, kFusedScatterTiles);
+    // (of few blobs the few blocks wait no longer than for a scan kernel: 260 in
+    // 128^3 16.2 us against 19.1)
+    const bool fuse = M > 0 && fused_scan_ok(g, s, M <= 1024 ? kFusedTiles : kFusedScatterTiles);
     if (e == hipSuccess) e = bin_blobs<T>(g, M, q, s, false, !fuse);
     if (e != hipSuccess || M == 0) return e;
     const FusedScan scan = fused_scan(g, fuse);
@@ -2389,8 +2370,20 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
     return hipGetLastError();
 }
 
+bool note_capture(mb_grid* g, hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        st = hipStreamCaptureStatusActive;  // (as if)
+    }
+    const bool cap = st != hipStreamCaptureStatusNone;
+    if (cap && !g->own_capture) g->replayed = true;
+    return cap;
+}
+
 bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles) {
-    return (int64_t)g->tiles.n * g->tiles.nbox <= tiles && !capturing(s);
+    const bool cap = note_capture(g, s);
+    return (int64_t)g->tiles.n * g->tiles.nbox <= tiles && !cap;
 }
 
 hipError_t spring_forces(const SpringsDev& sp, int64_t P, const double* q,
@@ -2582,7 +2575,7 @@ hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
     const int kid = q_update ? K_INTERP_STEP : K_INTERP;
     if (g->binned_small && !part) {
         MB_LAUNCH(g, kid, s, k_interp_direct<T>, (unsigned)((3 * M + WAVE - 1) / WAVE), WAVE, 0,
-                  rec_geo<T>(g), g->d_perm, g->L, (int)(M / g->tiles.nbox), M, v, u_out, uscale,
+                  rec_geo<T>(g), record_blobs(g), g->L, (int)(M / g->tiles.nbox), M, v, u_out, uscale,
                   q_update, g->d.dt, clear_planes ? g->d_act : nullptr);
         return hipGetLastError();
     }
@@ -2592,7 +2585,7 @@ hipError_t interpolate(mb_grid* g, int64_t M, const T* v, double* u_out,
         MB_LAUNCH(g, kid, s, (k_interp<T, decltype(X)::value, decltype(Y)::value, decltype(Z)::value>),
                   g->tiles.n * g->tiles.nbox,
                   interp_threads(decltype(X)::value * decltype(Y)::value * decltype(Z)::value),
-                  0, rec_geo<T>(g), g->d_perm,
+                  0, rec_geo<T>(g), record_blobs(g),
                   g->d_offs, g->L, g->tiles, v, u_out, uscale, q_update, g->d.dt,
                   1.0 / g->d.h, part, bn);
     });
@@ -2604,7 +2597,7 @@ hipError_t interpolate_grad(mb_grid* g, int64_t M, const T* v, const double* W, 
                             double* gout, hipStream_t s, double* u_out, double uscale) {
     if (g->binned_small) {
         MB_LAUNCH(g, K_INTERP_GRAD, s, k_interp_grad_direct<T>,
-                  (unsigned)((M + GRAD_LANES - 1) / GRAD_LANES), WAVE, 0, rec_geo<T>(g), g->d_perm,
+                  (unsigned)((M + GRAD_LANES - 1) / GRAD_LANES), WAVE, 0, rec_geo<T>(g), record_blobs(g),
                   g->L, (int)(M / g->tiles.nbox), M, v, W, wscale, 1.0 / g->d.h, gout, u_out,
                   uscale);
         return hipGetLastError();
@@ -2615,7 +2608,7 @@ hipError_t interpolate_grad(mb_grid* g, int64_t M, const T* v, const double* W, 
     }
     const bool ok = with_tile_shape(g->tiles, [&](auto X, auto Y, auto Z) {
         MB_LAUNCH(g, K_INTERP_GRAD, s, (k_interp_grad<T, decltype(X)::value, decltype(Y)::value, decltype(Z)::value>),
-                  g->tiles.n * g->tiles.nbox, BLK, 0, rec_geo<T>(g), g->d_perm,
+                  g->tiles.n * g->tiles.nbox, BLK, 0, rec_geo<T>(g), record_blobs(g),
                   g->d_offs, g->L, g->tiles, v, W, wscale, 1.0 / g->d.h, gout);
     });
     return ok ? hipGetLastError() : hipErrorInvalidValue;
