@@ -665,9 +665,9 @@ static hipError_t step_once(mb_grid* g, const SpringsDev& sd, int64_t P, int64_t
         F.mbox = (int)(M / g->tiles.nbox);
         F.planes = mark;
         F.planes_out = part;
-        // a blob's nodes lie in four planes, those of the 13 of a particle of radius
-        // one in about seven
-        if (mark) F.marked = (int)(P / g->tiles.nbox) * std::min(4 * sd.nb, 7 + sd.nb / 4);
+        // (a blob's nodes lie in four planes, those of the 13 of a particle of radius
+        // one in about seven)
+        if (mark) F.marked = (int)(P / g->tiles.nbox) * std::min(4 * sd.nb, 4 + sd.nb / 4);
         return fluid_solve<T>(g, v, F, v, s);
     };
     hipError_t e;

@@ -1101,10 +1101,13 @@ k_xy_inv(const cplx<T>* __restrict__ A, const cplx<T>* __restrict__ tw,
 // the empty blocks cost more than the chain (32 64^3 boxes of two particles: x
 // pass of 24,576 blocks 32 against 25; 32 48^3, 13,824: 18.6 and 16.5), at half
 // the number in the inverse plane pass, whose blocks take more LDS (32 64^3, 6,144:
-// 19 and 16).  A few marks, at most two a block, are dealt out too (one particle in
-// each of 8 64^3 boxes, float64: a step 53.5 us against 58.5; in 128^3: inverse plane
-// pass 9.4 and 13.4).
-inline int plane_blocks(int64_t n, int marked, int L) { return n <= 8192 && 4 * marked > L ? L : 8; }
+// 19 and 16).  Marks of at most two a block are dealt out too, unless they are all
+// the planes: the other blocks would be empty (pairs in each of 16 64^3 boxes,
+// float64: y pass 5.9 us against 8.4, inverse plane 13 and 23; one particle in each
+// of 8: a step 53 and 58; in 128^3: inverse plane 9.4 and 13.4).
+inline int plane_blocks(int64_t n, int marked, int L) {
+    return n <= 8192 && (marked > 16 || marked >= L) ? L : 8;
+}
 
 template <typename T, int L>
 hipError_t solve_sized(mb_grid* g, const T* v_in, const SolveForce<T>& F, T* v_out,
