@@ -685,23 +685,6 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
         }
         if (flag && (nonfinite(x, 3) | nonfinite(F, 3))) atomicOr(flag, 1);
     }
-    if (SPRINGS || Fext) {
-        unsigned m = 0;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const unsigned h =
-                (unsigned)__double2hiint((double)(T)(F[b] * inv_vol)) & 0x7fffffffu;
-            m = own && h > m ? h : m;
-        }
-        m = wave_max_last(m);
-        if (tid % WAVE == WAVE - 1) fmax_hi[tid / WAVE] = m;
-        __syncthreads();
-        if (tid == 0) {
-#pragma unroll
-            for (int w = 0; w < BLK / WAVE; ++w) m = fmax_hi[w] > m ? fmax_hi[w] : m;
-            bb.fexp[box] = box_exponent(m);
-        }
-    }
     int64_t pos = i0 + tid;
     if (sort) {  // (uniform over the grid)
         // rank: the blobs before this one in its tile
@@ -750,6 +733,23 @@ k_bin_box(SpringsDev sp, BoxBin bb, Tiles tl, const double* __restrict__ q,
     }
     if (own)
         write_record<T>(rec, SPRINGS || Fext ? recf : nullptr, perm, pos, i0 + tid, g, F, inv_vol);
+    if (SPRINGS || Fext) {
+        unsigned m = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const unsigned h =
+                (unsigned)__double2hiint((double)(T)(F[b] * inv_vol)) & 0x7fffffffu;
+            m = own && h > m ? h : m;
+        }
+        m = wave_max_last(m);
+        if (tid % WAVE == WAVE - 1) fmax_hi[tid / WAVE] = m;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int w = 0; w < BLK / WAVE; ++w) m = fmax_hi[w] > m ? fmax_hi[w] : m;
+            bb.fexp[box] = box_exponent(m);
+        }
+    }
     if (fpart) {
         double tot[3] = {own ? F[0] : 0.0, own ? F[1] : 0.0, own ? F[2] : 0.0};
         block_reduce3(tot, red);
