@@ -226,35 +226,43 @@ constexpr int elems_xf(int L, bool field, bool steady) {
     while (n % e != 0 || n / e > 512) ++e;
     return e;
 }
-// kx columns per block of the y pass (at least 128 B contiguous per row; the
-// last block is not left with a column or two: 64^3 33 = 17 + 16 columns, not
-// 32 + 1: 32 boxes 7.5 -> 5.6 us)
+// kx columns per block of the y pass (at least 128 B contiguous per row), dealt
+// evenly up to 96^3, so that the last block is not left with a column or two (64^3:
+// 33 = 17 + 16, not 32 + 1: 32 boxes 57 us against 84 in float64, 27 and 41 in
+// float32).  Above, the uneven share changes nothing (128^3 float32 8.3 and 8.5,
+// 144^3 12.5 and 12.1, 256^3 52.4 and 53.0, float64 15.2 and 15.4, 110.6 and 110.3).
 template <typename T>
 constexpr int cols_y(int L) {
     const int nc = L / 2 + 1;
     int w = 2048 / L;
     if (w < 1) w = 1;
     if (w >= nc) return nc;
-    if (L > 96) return w;  // (tuned as they are: 128^3, 13 columns against 16 were slower)
+    if (L > 96) return w;
     const int blocks = (nc + w - 1) / w;
     return (nc + blocks - 1) / blocks;
 }
-// Elements per thread of the z pass: shorter chains where a pass is a round or
-// two of blocks (float64 one 32^3 box 5.8 -> 4.8 us, 48^3 7.5 -> 5.9, 64^3 8.3
-// -> 7.9; float32 96^3 16.5 -> 12.4 with four columns).
+// Elements per thread of the z pass: four, a shorter chain, where a single box is a
+// round or two of blocks and has waves to spare, else eight.  Four against eight, us,
+// one box: float64 24^3 5.0 and 5.9, 32^3 5.0 and 5.5, 64^3 8.1 and 8.4, 72^3 13.8
+// and 14.8 (not taken), 96^3 21.1 and 17.6, 128^3 28.0 and 22.4, 192^3 127 and 99,
+// 256^3 430 and 321; float32 72^3 9.2 and 9.7, 96^3 12.2 and 13.3, 128^3 17.1 and
+// 14.1, 144^3 38.8 and 28.0, 256^3 150 and 100.  (32 boxes of 48^3 in float64 take
+// 44 and 35, of 64^3 74 and 72, in float32 41 and 33: the float64 ones would have
+// eight, which one box would pay for.)
 template <typename T>
 constexpr int elems_z(int L) {
     return sizeof(T) == 8 ? (L <= 64 ? 4 : EPT) : (L == 72 || L == 96 ? 4 : EPT);
 }
 // ky columns per block of the z pass (a divisor of L; LDS <= 64 KB for
-// float32, 100 KB for float64).  At 128^3 float32, eight columns give 1,040
-// blocks of 384 threads, which fill the CUs in one round (sixteen gave 520
-// blocks of 768 threads: two per CU, and a nearly empty second round;
-// sixteen with 384 threads of sixteen elements, three blocks per CU in one
-// round, 18.6 against 15.1 us; four were slower).  Float64 takes four up to
-// L = 128 (2,080 blocks of 192 threads at 128^3: 26.5 us against 38.5 us
-// with eight) and eight above, where whole 128-byte lines per z row pay
-// for one block per CU (256^3: 288 us against 424 us with four).
+// float32, 100 KB for float64).  Eight float32 columns are half a 128-byte line, four
+// float64 ones too: fewer split more lines, more leave fewer and larger blocks.  Four
+// against eight, us: float32 64^3 (32 boxes) 38 and 33, 72^3 12.3 and 9.2, 96^3 12.3
+// and 16.2 (1,176 blocks of 288 threads against 588 of 576), 128^3
+// 15.5 and 14.1, 144^3 34 and 28, 216^3 106 and 83, 256^3 149 and 100, 288^3 267 and 316
+// (not taken); float64 48^3 6.9 and 6.1, 64^3 7.7 and 8.3, 72^3 14.8 and 11.8 (not
+// taken), 96^3 18.2 and 19.7, 128^3 22.2 and 26.5, 144^3 42 and 39, 256^3 450 and 320.
+// At 128^3 float32 sixteen (520 blocks of 768 threads: two per CU, and a nearly empty
+// second round) were slower, and so were sixteen of sixteen elements (18.6 against 15.1).
 template <typename T>
 constexpr int cols_z(int L) {
     int w = sizeof(T) == 8 ? (L <= 128 && L != 48 ? 4 : 8) : (L == 96 ? 4 : 8);
