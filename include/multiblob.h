@@ -115,14 +115,15 @@ typedef enum {
  *
  * deterministic = 1: every result is the same bit for bit from run to run.
  * Spreading always sums in fixed point (independent of the order of the
- * blobs and of the atomic additions; so do the steps of boxes with few blobs,
- * whose solve forms the force from the blobs itself); the one order-dependent path, float64
- * LDS atomics for a float64 spreading box tile (16^3 cells) of more than
- * 2^20 blobs, is then replaced by two 64-bit fixed-point sums (the
- * contributions, then their rounding remainders; up to 2^25 blobs in one
- * box tile, beyond which the atomics remain), and mb_step_adjoint sums the
- * stiffness and rest-length derivatives per block in a fixed order instead
- * of with float64 atomics.  deterministic = 0 allows those paths.
+ * blobs and of the atomic additions; so do the steps of boxes with few
+ * blobs, whose solve forms the force from the blobs itself); the one
+ * order-dependent path, float64 LDS atomics for a float64 spreading box tile
+ * (16^3 cells) of more than 2^20 blobs, is then replaced by two 64-bit
+ * fixed-point sums (the contributions, then their rounding remainders; up to
+ * 2^25 blobs in one box tile, beyond which the atomics remain), and
+ * mb_step_adjoint sums the stiffness and rest-length derivatives per block
+ * in a fixed order instead of with float64 atomics.  deterministic = 0
+ * allows those paths.
  *
  * check_finite = 1: the calls that read blob positions or blob forces
  * (mb_spread, mb_interpolate, mb_interpolate_grad and every step call)

@@ -1088,6 +1088,10 @@ mb_status mb_grid_set_scheme(mb_grid* g, int32_t scheme) {
     return MB_OK;
 }
 
+#define MB_SHAPE(X, Y, Z) static_assert(X * Y * Z <= kMaxTileCells, "small_edge");
+MB_TILE_SHAPES(MB_SHAPE)
+#undef MB_SHAPE
+
 static bool tiles_fit(int L, int tx, int ty, int tz) {
     return tile_shape_supported(tx, ty, tz) && L % tx == 0 && L % ty == 0 && L % tz == 0;
 }
