@@ -226,6 +226,7 @@ constexpr int elems_xf(int L, bool field, bool steady) {
     while (n % e != 0 || n / e > 512) ++e;
     return e;
 }
+
 // kx columns per block of the y pass (at least 128 B contiguous per row), dealt
 // evenly up to 96^3, so that the last block is not left with a column or two (64^3:
 // 33 = 17 + 16, not 32 + 1: 32 boxes 57 us against 84 in float64, 27 and 41 in

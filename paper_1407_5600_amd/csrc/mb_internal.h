@@ -247,9 +247,9 @@ hipError_t scatter_springs(mb_grid* g, const SpringsDev& sp, int64_t P,
 // blocks have forces to form meanwhile; kFusedScatterTiles in the scattering
 // kernel, where the others wait for all of it: 1,300 blobs in each of 48 32^3
 // boxes, 1,536 tiles, an interpolation 32.3 -> 31.4 us, 64 boxes 38.9 -> 40.1;
-// 128^3, 2,048 tiles, 79,000 blobs 28.2 -> 30.6) and a stream not being captured (a captured launch would replay its
-// launch number; d_flag[1] is zeroed with the workspace, launch numbers
-// start at 1).
+// 128^3, 2,048 tiles, 79,000 blobs 28.2 -> 30.6) and a stream not being captured
+// (a captured launch would replay its launch number; d_flag[1] is zeroed with the
+// workspace, launch numbers start at 1).
 constexpr int kFusedTiles = 4096;
 constexpr int kFusedScatterTiles = 1536;
 bool fused_scan_ok(mb_grid* g, hipStream_t s, int tiles);
